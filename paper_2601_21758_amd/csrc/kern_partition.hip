@@ -22,7 +22,9 @@
 //   rp_refine_prune  one workgroup: Stage 1 cluster starts, Stage 2 as
 //                    level-synchronous passes (every significant gap of every
 //                    current cluster is cut in the same pass; a pass without a
-//                    new cut ends the recursion), Stage 3 greedy merges of the
+//                    new cut ends the recursion), then the leaves (the queue
+//                    table when they fit the budget).
+//   rp_merge         one workgroup: Stage 3, greedy merges of the
 //                    lowest-utility adjacent pair, then the queue table.
 //
 // Every binary64 expression is evaluated in the same order as the oracle's
@@ -65,11 +67,11 @@ struct PartWs {
   int32_t* meta;      // [16]: 0 V, 1 km_i, 2 km_j
   double* km_F;       // [kKmeansBlocks]
   int32_t* km_ij;     // [kKmeansBlocks][2]
-  int64_t* gn;        // [L] Stage-3 leaves (global mode)
-  int64_t* gS;
-  int32_t* glo;
-  int32_t* ghi;
-  Leaf* grec;         // [L] Stage-3 records when the leaves exceed LDS
+  int64_t* gN;        // [L+1] leaves: exclusive prefix sums of their counts
+  int64_t* gS;        // [L+1] ... and of their sums
+  int32_t* glo;       // [L]
+  int32_t* ghi;       // [L]
+  Leaf* grec;         // [L] Stage-3 records (or chain arrays) when the leaves exceed LDS
   uint64_t* gU;       // [L]
   int Gh;
 };
@@ -103,8 +105,8 @@ PartWs carve_part(void* ws, int64_t n, int L) {
   w.meta = reinterpret_cast<int32_t*>(take(16 * 4));
   w.km_F = reinterpret_cast<double*>(take(kKmeansBlocks * 8));
   w.km_ij = reinterpret_cast<int32_t*>(take(kKmeansBlocks * 8));
-  w.gn = reinterpret_cast<int64_t*>(take((size_t)L * 8));
-  w.gS = reinterpret_cast<int64_t*>(take((size_t)L * 8));
+  w.gN = reinterpret_cast<int64_t*>(take((size_t)(L + 1) * 8));
+  w.gS = reinterpret_cast<int64_t*>(take((size_t)(L + 1) * 8));
   w.glo = reinterpret_cast<int32_t*>(take((size_t)L * 4));
   w.ghi = reinterpret_cast<int32_t*>(take((size_t)L * 4));
   w.grec = reinterpret_cast<Leaf*>(take((size_t)L * sizeof(Leaf)));
@@ -484,12 +486,12 @@ __device__ void segment_carries(RpShared& sm, int V, int j0, int* carry_s, int* 
   *carry_e = ce < V ? ce : V;
 }
 
-// The queue table from k queue aggregates in length order.
-template <class N, class Lo>
-__device__ void write_queues(ewsjf_queue_table* tab, int k, const N* n, const N* S, const Lo* lo, const Lo* hi,
-                             int tid, int nthreads) {
+// The queue table from k queues in length order, given by the prefix sums of
+// their counts and sums and their intervals.
+__device__ void write_queues(ewsjf_queue_table* tab, int k, const int64_t* N, const int64_t* S, const int32_t* lo,
+                             const int32_t* hi, int tid, int nthreads) {
   for (int i = tid; i < k; i += nthreads) {
-    const int64_t cn = n[i], cs = S[i];
+    const int64_t cn = N[i + 1] - N[i], cs = S[i + 1] - S[i];
     const int32_t l = lo[i], h = hi[i];
     if (i > 0) tab->bounds[i - 1] = l;
     tab->lo[i] = l;
@@ -615,8 +617,7 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
 
   // ---- Leaves: one per segment, aggregates from the exact prefix sums -------
   // The segment starts are listed in order (in the Stage-3 workspace, which
-  // rp_merge rewrites later), then each thread builds whole leaves: four
-  // independent prefix-sum loads per leaf instead of a chain per thread.
+  // rp_merge rewrites later), then each thread builds whole leaves.
   int nl = 0;
   {
     int cnt = 0;
@@ -636,10 +637,14 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
     for (int i = tid; i < nl; i += kBlock) {
       const int s = starts[i];
       const int e = i + 1 < nl ? starts[i + 1] : V;
-      w.gn[i] = w.PN[e] - w.PN[s];
-      w.gS[i] = w.PS[e] - w.PS[s];
+      w.gN[i] = w.PN[s];
+      w.gS[i] = w.PS[s];
       w.glo[i] = vat(sm, s);
       w.ghi[i] = vat(sm, e - 1);
+    }
+    if (tid == 0) {
+      w.gN[nl] = w.PN[V];
+      w.gS[nl] = w.PS[V];
     }
   }
   __threadfence();
@@ -656,26 +661,38 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
   }
   // Within the queue budget: the leaves are the queues.  Otherwise Stage 3
   // (rp_merge) writes them.
-  if (nl <= p.max_queues) write_queues(tab, nl, w.gn, w.gS, w.glo, w.ghi, tid, kBlock);
+  if (nl <= p.max_queues) write_queues(tab, nl, w.gN, w.gS, w.glo, w.ghi, tid, kBlock);
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------------------
 // Stage 3: greedy merge of the adjacent pair with the smallest utility until
-// at most max_queues remain (Section 4.2, "Stage 3", Eq. 3).
+// at most max_queues remain (Section 4.2, "Stage 3", Eq. 3; ties to the
+// leftmost pair).
 //
-// The merge is sequential (each merge changes its neighbours' utilities), so
-// one wave runs it.  Leaves keep their index (a linked list replaces
-// shifting), and lane l caches the minimum utility over the pairs it owns
-// (left-leaf indices [l*P, l*P + P)).  A merge costs a two-step wave
-// reduction for the global minimum, two rounds of record reads and a rescan
-// by the few lanes whose pairs changed.  Utilities are non-negative binary64
-// values, so their bit patterns order like the values; ties go to the smaller
-// leaf index, which is the smaller position in the list.  The records live in
-// LDS, or in the workspace when there are more leaves than LDS holds.
+// The merges are sequential, but they come in chains: a merged queue is
+// sparser and further from its neighbours' means in a way that makes its next
+// pair the lowest again, so the queue that was just merged (the hot queue)
+// takes its neighbour next, almost always on the same side (of 1,421 merges
+// of a 262,144-length window in three modes, 1,419 continue the chain, 15 on
+// the other side).  A chain is not serial: after j further merges on one side
+// the hot queue is the union of j + 1 consecutive leaves, whose count and sum
+// are differences of prefix sums, so lane j evaluates the state after j
+// merges, all lanes at once (chain_merge).  The merges up to the first lane
+// where another pair is the lowest are committed together.
+//
+// Measured (rp_merge alone): the 1M window of two modes into 256 queues
+// 50 us, where one merge at a time took 253 us; a 65,536 window into 64
+// queues 30 us against 363 us; the 262,144 window of three modes into 64
+// queues 22 us against 1,119 us.  One merge at a time (merge_list) is bound
+// by latency, about 0.75 us each: two dependent divisions, two reductions
+// over the wave and three rounds of LDS reads.
+//
+// Data without chains (every merge far from the one before) goes through
+// merge_list, the linked list with a cached minimum per lane.
 // ---------------------------------------------------------------------------
-constexpr int kMergeThreads = 256;
+constexpr int kMergeThreads = kBlock;
 
 // Lowest lane holding the wave's minimum of x, and that minimum (*m).  The
 // high words are reduced first, the low words only when several lanes share
@@ -693,14 +710,22 @@ __device__ __forceinline__ int wave_argmin_u64(uint64_t x, uint64_t* m) {
   return src;
 }
 
+// One merge at a time.  Leaves keep their index (a linked list replaces
+// shifting), and lane l caches the minimum utility over the pairs it owns
+// (left-leaf indices [l*P, l*P + P)).  A merge costs a two-step wave
+// reduction for the global minimum, two rounds of record reads and a rescan
+// by the few lanes whose pairs changed.  Utilities are non-negative binary64
+// values, so their bit patterns order like the values; ties go to the smaller
+// leaf index, which is the smaller position in the list.  The records live in
+// LDS, or in the workspace when there are more leaves than LDS holds.
 template <bool kInLds>
-__device__ __forceinline__ void stage3(Leaf* rec, uint64_t* U, const PartWs& w, int nl0,
-                                       const ewsjf_partition_params& p, ewsjf_queue_table* tab, int* iscr) {
+__device__ __forceinline__ void merge_list(Leaf* rec, uint64_t* U, const PartWs& w, int nl0,
+                                           const ewsjf_partition_params& p, ewsjf_queue_table* tab, int* iscr) {
   const int tid = threadIdx.x;
   for (int i = tid; i < nl0; i += kMergeThreads) {
     Leaf r;
-    r.n = w.gn[i];
-    r.S = w.gS[i];
+    r.n = w.gN[i + 1] - w.gN[i];
+    r.S = w.gS[i + 1] - w.gS[i];
     r.lo = w.glo[i];
     r.hi = w.ghi[i];
     r.rho = (double)r.n / (double)((int64_t)r.hi - (int64_t)r.lo + 1);
@@ -709,7 +734,7 @@ __device__ __forceinline__ void stage3(Leaf* rec, uint64_t* U, const PartWs& w, 
     r.prv = i - 1;
     r.rho_n = r.mean_n = 0.0;
     if (i + 1 < nl0) {
-      const int64_t n1 = w.gn[i + 1], S1 = w.gS[i + 1];
+      const int64_t n1 = w.gN[i + 2] - w.gN[i + 1], S1 = w.gS[i + 2] - w.gS[i + 1];
       r.rho_n = (double)n1 / (double)((int64_t)w.ghi[i + 1] - (int64_t)w.glo[i + 1] + 1);
       r.mean_n = (double)S1 / (double)n1;
     }
@@ -844,17 +869,268 @@ __device__ __forceinline__ void stage3(Leaf* rec, uint64_t* U, const PartWs& w, 
   if (tid == 0) tab->k = tot;
 }
 
+// The current queues (entries) of the chain merge: prefix sums (one more than
+// entries) and intervals, the density and mean of each, the utility of each
+// entry and the next, and the running minima of the utilities from the left
+// (PM[i] = min U[0..i]) and from the right (SM[i] = min U[i..]).
+struct ChainArrays {
+  int64_t *N, *S;
+  int32_t *lo, *hi;
+  double *rho, *mean;
+  uint64_t *U, *PM, *SM;
+};
+constexpr uint64_t kNoPair = ~0ull;  // above every utility's bits, +inf included
+
+struct ChainLds {
+  int64_t N[kLeafLds + 1], S[kLeafLds + 1];
+  int32_t lo[kLeafLds], hi[kLeafLds];
+  double rho[kLeafLds], mean[kLeafLds];
+  uint64_t U[kLeafLds], PM[kLeafLds], SM[kLeafLds];
+};
+struct ListLds {
+  Leaf rec[kLeafLds];
+  uint64_t U[kLeafLds];
+};
+struct ChainState {
+  uint64_t pmin[kWavesPerBlock], smin[kWavesPerBlock];
+  double rho, mean;  // of the hot queue when its chain ended, and the utilities with its neighbours
+  uint64_t ul, ur;
+  int x, y;          // the hot queue is the union of entries x..y
+  int alive;         // queues left
+};
+
+__device__ __forceinline__ uint64_t min_u64(uint64_t a, uint64_t b) { return a < b ? a : b; }
+
+// One step of the wave scan below: the minimum with the value the DPP control
+// brings (kNoPair where it brings none).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_min_u64(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)(uint32_t)x, kCtrl, kRows, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)(uint32_t)(x >> 32), kCtrl, kRows, 0xF, false);
+  return min_u64(x, ((uint64_t)hi << 32) | lo);
+}
+
+// Inclusive running minimum over the lanes, from lane 0 up (the steps of
+// wave_incl_scan_add).
+__device__ __forceinline__ uint64_t wave_incl_min_u64(uint64_t x) {
+  x = dpp_min_u64<0x111, 0xF>(x);  // row_shr:1
+  x = dpp_min_u64<0x112, 0xF>(x);  // row_shr:2
+  x = dpp_min_u64<0x114, 0xF>(x);  // row_shr:4
+  x = dpp_min_u64<0x118, 0xF>(x);  // row_shr:8
+  x = dpp_min_u64<0x142, 0xA>(x);  // row_bcast:15
+  x = dpp_min_u64<0x143, 0xC>(x);  // row_bcast:31
+  return x;
+}
+
+// PM and SM from U[0..np), and st.x = the lowest pair, the leftmost of
+// equals.  The whole block; a tile of PM from the left and the mirrored tile
+// of SM from the right share their barriers.
+__device__ void chain_minima(const ChainArrays& c, int np, ChainState& st) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  uint64_t pc = kNoPair, sc = kNoPair;
+  for (int t0 = 0; t0 < np; t0 += kBlock) {
+    const int i = t0 + tid, j = np - 1 - i;
+    const uint64_t pm = wave_incl_min_u64(i < np ? c.U[i] : kNoPair);
+    const uint64_t sm = wave_incl_min_u64(j >= 0 ? c.U[j] : kNoPair);
+    if (lane == kWave - 1) {
+      st.pmin[wv] = pm;
+      st.smin[wv] = sm;
+    }
+    __syncthreads();
+    uint64_t pb = pc, sb = sc;
+#pragma unroll
+    for (int q = 0; q < kWavesPerBlock; ++q) {
+      const uint64_t pq = st.pmin[q], sq = st.smin[q];
+      pb = min_u64(pb, q < wv ? pq : kNoPair);
+      sb = min_u64(sb, q < wv ? sq : kNoPair);
+      pc = min_u64(pc, pq);
+      sc = min_u64(sc, sq);
+    }
+    if (i < np) c.PM[i] = min_u64(pb, pm);
+    if (j >= 0) c.SM[j] = min_u64(sb, sm);
+    __syncthreads();
+  }
+  // pc is the lowest utility: the first place where the running minimum
+  // reaches it.
+  for (int i = tid; i < np; i += kBlock)
+    if (c.PM[i] == pc && (i == 0 || c.PM[i - 1] != pc)) st.x = i;
+  __syncthreads();
+}
+
+// Entries x..x + d become entry x and the entries above move down by d
+// places, m entries left; U is moved too (the merged entry's own U, rho and
+// mean come from st).  The whole block: a tile of entries is read before it
+// is written, and tiles go up, so no entry is overwritten before it moved.
+__device__ void chain_compact(const ChainArrays& c, int x, int d, int m, const ChainState& st) {
+  for (int t0 = x; t0 <= m; t0 += kBlock) {
+    const int i = t0 + (int)threadIdx.x;  // N and S have one entry more
+    int64_t N = 0, S = 0;
+    int32_t lo = 0, hi = 0;
+    double rho = 0.0, mean = 0.0;
+    uint64_t U = 0;
+    if (i <= m) {
+      N = c.N[i + d];
+      S = c.S[i + d];
+    }
+    if (i < m) {
+      lo = c.lo[i + d];
+      hi = c.hi[i + d];
+      rho = c.rho[i + d];
+      mean = c.mean[i + d];
+    }
+    if (i + 1 < m) U = c.U[i + d];
+    __syncthreads();
+    if (i == x) {  // its start stays
+      c.hi[i] = hi;
+      c.rho[i] = st.rho;
+      c.mean[i] = st.mean;
+      if (i + 1 < m) c.U[i] = st.ur;
+      if (i > 0) c.U[i - 1] = st.ul;
+    } else {
+      if (i <= m) {
+        c.N[i] = N;
+        c.S[i] = S;
+      }
+      if (i < m) {
+        c.lo[i] = lo;
+        c.hi[i] = hi;
+        c.rho[i] = rho;
+        c.mean[i] = mean;
+      }
+      if (i + 1 < m) c.U[i] = U;
+    }
+    __syncthreads();
+  }
+}
+
+// Merges until max_queues queues are left, or until the chains turn out
+// short; returns the number of entries left (the queues, when it is at most
+// max_queues).  The whole block; c holds nl > max_queues entries' N, S, lo, hi.
+__device__ int chain_merge(const ChainArrays& c, int nl, const ewsjf_partition_params& p, ChainState& st) {
+  const int tid = threadIdx.x;
+  for (int i = tid; i < nl; i += kBlock) {
+    const int64_t n = c.N[i + 1] - c.N[i], S = c.S[i + 1] - c.S[i];
+    c.rho[i] = (double)n / (double)((int64_t)c.hi[i] - (int64_t)c.lo[i] + 1);
+    c.mean[i] = (double)S / (double)n;
+  }
+  __syncthreads();
+  for (int i = tid; i + 1 < nl; i += kBlock)
+    c.U[i] = dbits(utility_cached(c.rho[i], c.mean[i], c.rho[i + 1], c.mean[i + 1], p.eps));
+  __syncthreads();
+  int m = nl;
+  for (int chains = 1;; ++chains) {
+    chain_minima(c, m - 1, st);
+    if (tid < kWave) {
+      int x = st.x, y = x + 1, left = m - 1;
+      // st.x is read before a lane writes it again: one wave, in order
+      bool go_left = true;
+      while (left > p.max_queues) {
+        // Lane j: the hot queue after j more merges on the current side.
+        const int xj = x - (go_left ? tid : 0), yj = y + (go_left ? 0 : tid);
+        const bool in = xj >= 0 && yj < m;
+        const int a = in ? xj : x, b = in ? yj : y;
+        const int64_t n = c.N[b + 1] - c.N[a], S = c.S[b + 1] - c.S[a];
+        const double rho = (double)n / (double)((int64_t)c.hi[b] - (int64_t)c.lo[a] + 1);
+        const double mean = (double)S / (double)n;
+        const int al = a > 0 ? a - 1 : 0, br = b + 1 < m ? b + 1 : m - 1;
+        const uint64_t ul = dbits(utility_cached(c.rho[al], c.mean[al], rho, mean, p.eps));
+        const uint64_t ur = dbits(utility_cached(rho, mean, c.rho[br], c.mean[br], p.eps));
+        const uint64_t UL = a > 0 ? ul : kNoPair, UR = b + 1 < m ? ur : kNoPair;
+        const uint64_t PL = a >= 2 ? c.PM[a - 2] : kNoPair;      // the pairs left of its left neighbour
+        const uint64_t PR = b + 2 < m ? c.SM[b + 1] : kNoPair;   // the pairs right of its right neighbour
+        // the lowest pair is the one on its left / on its right (ties: the leftmost)
+        const bool lo_l = in && UL != kNoPair && UL < PL && UL <= UR && UL <= PR;
+        const bool lo_r = in && UR != kNoPair && UR < PL && UR < UL && UR <= PR;
+        const uint64_t ml = __ballot(lo_l), mr = __ballot(lo_r);
+        const uint64_t on = go_left ? ml : mr, off = go_left ? mr : ml;
+        const int len = on == ~0ull ? kWave : (int)__builtin_ctzll(~on);
+        const int run = min(len, left - p.max_queues);
+        left -= run;
+        if (go_left) x -= run;
+        else y += run;
+        if (len < kWave) {
+          if (((off >> len) & 1ull) == 0ull) {  // another pair is the lowest: the chain ends
+            if (tid == len) {                   // (read only when more merges are due, so run == len)
+              st.rho = rho;
+              st.mean = mean;
+              st.ul = UL;
+              st.ur = UR;
+            }
+            break;
+          }
+          go_left = !go_left;
+        }
+      }
+      if (tid == 0) {
+        st.x = x;
+        st.y = y;
+        st.alive = left;
+      }
+    }
+    __syncthreads();
+    const int x = st.x, d = st.y - x;
+    m -= d;
+    chain_compact(c, x, d, m, st);
+    // A new chain costs about 3 us (the scans and the move), merge_list 0.75 us
+    // a merge: chains pay from about four merges on.  Windows of the workloads
+    // start with up to 20 short chains before their long one, so the first 32
+    // are not judged; data without any chain loses about 0.1 ms here.
+    if (m <= p.max_queues || (chains >= 32 && nl - m < 4 * chains)) return m;
+  }
+}
+
 __global__ __launch_bounds__(kMergeThreads) void rp_merge(PartWs w, ewsjf_partition_params p,
                                                           ewsjf_queue_table* tab) {
-  __shared__ Leaf srec[kLeafLds];
-  __shared__ uint64_t sU[kLeafLds];
+  __shared__ union {
+    ChainLds chain;
+    ListLds list;
+  } lds;
+  __shared__ ChainState st;
   __shared__ int iscr[kMergeThreads / kWave];
   const int nl = w.meta[3];
   if (nl <= p.max_queues) return;  // rp_refine_prune wrote the queues
-  if (nl <= kLeafLds)
-    stage3<true>(srec, sU, w, nl, p, tab, iscr);
+  const int tid = threadIdx.x;
+  int m;
+  if (nl <= kLeafLds) {
+    ChainLds& cl = lds.chain;
+    for (int i = tid; i <= nl; i += kBlock) {
+      cl.N[i] = w.gN[i];
+      cl.S[i] = w.gS[i];
+      if (i < nl) {
+        cl.lo[i] = w.glo[i];
+        cl.hi[i] = w.ghi[i];
+      }
+    }
+    __syncthreads();
+    m = chain_merge(ChainArrays{cl.N, cl.S, cl.lo, cl.hi, cl.rho, cl.mean, cl.U, cl.PM, cl.SM}, nl, p, st);
+    if (m <= p.max_queues) {
+      write_queues(tab, m, cl.N, cl.S, cl.lo, cl.hi, tid, kBlock);
+      return;
+    }
+    for (int i = tid; i <= m; i += kBlock) {
+      w.gN[i] = cl.N[i];
+      w.gS[i] = cl.S[i];
+      if (i < m) {
+        w.glo[i] = cl.lo[i];
+        w.ghi[i] = cl.hi[i];
+      }
+    }
+  } else {
+    // five arrays of nl 8-byte entries in the room of nl records
+    static_assert(sizeof(Leaf) >= 5 * 8, "the chain arrays fit the records");
+    double* d = reinterpret_cast<double*>(w.grec);
+    uint64_t* u = reinterpret_cast<uint64_t*>(d + 2 * (size_t)nl);
+    m = chain_merge(ChainArrays{w.gN, w.gS, w.glo, w.ghi, d, d + nl, u, u + nl, u + 2 * (size_t)nl}, nl, p, st);
+    if (m <= p.max_queues) {
+      write_queues(tab, m, w.gN, w.gS, w.glo, w.ghi, tid, kBlock);
+      return;
+    }
+  }
+  __syncthreads();  // the chain arrays are done with (the records take their place)
+  if (m <= kLeafLds)
+    merge_list<true>(lds.list.rec, lds.list.U, w, m, p, tab, iscr);
   else
-    stage3<false>(w.grec, w.gU, w, nl, p, tab, iscr);
+    merge_list<false>(w.grec, w.gU, w, m, p, tab, iscr);
 }
 
 size_t partition_ws_bytes(int64_t n_window, const ewsjf_partition_params& p) {

@@ -1,0 +1,58 @@
+"""Refine-and-Prune's kernels at the sizes and shapes where their paths change,
+bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_21758_amd import workloads as W
+from parity_util import check_table
+
+torch = pytest.importorskip("torch")
+
+
+def _window(name):
+    rng = np.random.default_rng(sum(map(ord, name)))
+    if name == "two_modes":        # one long chain of merges
+        return W._lengths(rng, 65536, W.MIX_TWO)
+    if name == "three_modes":      # chains on both sides
+        return W._lengths(rng, 30000, W.MIX_THREE)
+    if name == "scattered":        # isolated pairs all over the axis: no chains
+        base = np.arange(1, 900) * 36
+        return np.repeat(np.concatenate([base, base + rng.integers(8, 16, base.size)]),
+                         rng.integers(1, 50, 2 * base.size)).astype(np.int32)
+    if name == "equal_gaps":       # every pair of leaves has the same utility
+        return np.repeat(np.arange(1, 1200, dtype=np.int32) * 27, 3)
+    if name == "scattered_many":   # no chains, more leaves than LDS holds
+        base = np.arange(1, 2400) * 13
+        return np.repeat(np.concatenate([base, base + rng.integers(3, 6, base.size)]),
+                         rng.integers(1, 50, 2 * base.size)).astype(np.int32)
+    if name == "many_leaves":      # chains over more leaves than LDS holds
+        return np.sort(rng.choice(np.arange(1, 32769), 9000, replace=False)).astype(np.int32)
+    if name == "all_lengths":      # every length once: the largest number of leaves
+        return np.arange(1, 32769, dtype=np.int32)
+    raise ValueError(name)
+
+
+# name, init_queues, max_queues, min_width, expected range of Stage-3 leaves
+STAGE3 = [
+    ("two_modes", 64, 64, 16, (300, 2048)),
+    ("two_modes", 64, 1, 16, (300, 2048)),
+    ("three_modes", 16, 16, 16, (300, 2048)),
+    ("scattered", 32768, 200, 0, (1500, 2048)),
+    ("equal_gaps", 32768, 37, 0, (1199, 1199)),
+    ("scattered_many", 32768, 256, 0, (2049, 32768)),
+    ("many_leaves", 32768, 50, 0, (2049, 32768)),
+    ("all_lengths", 32768, 256, 0, (32768, 32768)),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,K,mq,mw,leaves", STAGE3)
+def test_stage3_merges(name, K, mq, mw, leaves):
+    from paper_2601_21758_amd import ewsjf as E
+    win = _window(name)
+    print(f"stage 3 {name} W={win.size} max_queues={mq}", flush=True)
+    ref = oracle.partition(win, init_queues=K, max_queues=mq, min_width=mw)
+    assert leaves[0] <= ref.n_leaves <= leaves[1]
+    prm = E.params(init_queues=K, max_queues=mq, min_width=mw)
+    check_table(E.read_table(E.partition(torch.from_numpy(win).cuda(), prm)), ref)
