@@ -16,9 +16,10 @@
 //                    the lengths that leave it go to the ones that join it.
 //   rp_distinct      one workgroup: distinct values v[], counts c[] and exact
 //                    int64 prefix sums of counts and of count * value.
-//   rp_kmeans3 /     the exact 1-D 3-means initializer: every split (i, j) of
-//   rp_kmeans3_pick  the distinct values, binary64 objective, ties to the
-//                    smallest (i, j).
+//   rp_km_corners /  the exact 1-D 3-means initializer over the splits (i, j) of
+//   rp_kmeans3       the distinct values, binary64 objective, ties to the
+//                    smallest (i, j); tiles of splits that cannot hold the
+//                    maximum are skipped.
 //   rp_refine_prune  one workgroup: Stage 1 cluster starts, Stage 2 as
 //                    level-synchronous passes (every significant gap of every
 //                    current cluster is cut in the same pass; a pass without a
@@ -42,6 +43,10 @@ namespace {
 constexpr int kHistPerBlock = 16384;   // window entries per histogram workgroup
 constexpr int kMaxHistBlocks = 64;
 constexpr int kKmeansBlocks = 256;
+constexpr int kKmTile = 64;            // 3-means splits are taken in tiles of kKmTile x kKmTile
+constexpr int kKmCorners = 64;         // workgroups of the corner pass
+// tiles one workgroup of rp_kmeans3 tests
+constexpr int kKmMaxTests = (EWSJF_MAX_LEN / kKmTile) * (EWSJF_MAX_LEN / kKmTile) / kKmeansBlocks;
 constexpr int kLeafLds = 2048;         // Stage-3 leaves kept in LDS
 constexpr uint64_t kInfBits = 0x7FF0000000000000ull;  // +inf as binary64 bits
 constexpr int kBinsPerThread = EWSJF_MAX_LEN / kBlock;  // 32
@@ -64,9 +69,11 @@ struct PartWs {
   uint32_t* c;        // [L] multiplicities
   int64_t* PN;        // [L+1] prefix sums of c
   int64_t* PS;        // [L+1] prefix sums of c * v
-  int32_t* meta;      // [16]: 0 V, 1 km_i, 2 km_j
+  int32_t* meta;      // [16]: 0 V, 3 leaves
   double* km_F;       // [kKmeansBlocks]
   int32_t* km_ij;     // [kKmeansBlocks][2]
+  double* km_Q;       // [EWSJF_MAX_LEN / kKmTile] sums of squares of the value tiles
+  double* km_corner;  // [kKmCorners]
   int64_t* gN;        // [L+1] leaves: exclusive prefix sums of their counts
   int64_t* gS;        // [L+1] ... and of their sums
   int32_t* glo;       // [L]
@@ -105,6 +112,8 @@ PartWs carve_part(void* ws, int64_t n, int L) {
   w.meta = reinterpret_cast<int32_t*>(take(16 * 4));
   w.km_F = reinterpret_cast<double*>(take(kKmeansBlocks * 8));
   w.km_ij = reinterpret_cast<int32_t*>(take(kKmeansBlocks * 8));
+  w.km_Q = reinterpret_cast<double*>(take(EWSJF_MAX_LEN / kKmTile * 8));
+  w.km_corner = reinterpret_cast<double*>(take(kKmCorners * 8));
   w.gN = reinterpret_cast<int64_t*>(take((size_t)(L + 1) * 8));
   w.gS = reinterpret_cast<int64_t*>(take((size_t)(L + 1) * 8));
   w.glo = reinterpret_cast<int32_t*>(take((size_t)L * 4));
@@ -291,37 +300,133 @@ __global__ __launch_bounds__(kBlock) void rp_distinct(PartWs w, int L) {
     w.PN[V] = totN;
     w.PS[V] = totS;
     w.meta[0] = V;
-    w.meta[1] = -1;
-    w.meta[2] = -1;
   }
 }
 
-// Exact 1-D 3-means over splits 1 <= i < j <= V-1 of the distinct values.
+// ---------------------------------------------------------------------------
+// Exact 1-D 3-means over the splits 1 <= i < j <= V-1 of the distinct values:
+// the largest F(i, j) = f(0, i) + f(i, j) + f(j, V), f(x, y) = (sum)^2 / count
+// of the values x..y-1 (the least squared error), ties to the smallest (i, j).
+//
+// The splits form a V x V triangle, 148 million pairs for 17,000 values, of
+// which few can hold the maximum.  They are taken in tiles of 64 x 64.  For
+// every split of a tile the three clusters contain [0, i0), [i1, j0) and
+// [j1, V) (i0..i1 and j0..j1 the tile's ranges), and the values between add at
+// most their squares to F (adding a value to a cluster never lowers its
+// squared error), so
+//   F <= f(0, i0) + f(i1, j0) + f(j1, V) + Q(i0..i1) + Q(j0..j1),
+// Q a sum of squares.  Tiles whose bound is below the best F at any tile's
+// corner are skipped, the rest evaluated pair by pair in the definition's
+// expression order.  Of 37,128 tiles (17,362 values, a 262,144 window of three
+// modes) 256 are evaluated, of 131,328 (32,768 values, each once) 601.
+// On that window the two kernels take 19 us; every pair evaluated with three
+// divisions took 400 us (and its one-thread pick 28 us).
+// ---------------------------------------------------------------------------
 __device__ __forceinline__ bool km_better(double F, int i, int j, double bF, int bi, int bj) {
   if (F > bF) return true;
   if (F < bF) return false;
   return i < bi || (i == bi && j < bj);
 }
 
+// f(x, y) of the values x..y-1 (0 when there are none).
+__device__ __forceinline__ double km_f(const PartWs& w, int x, int y) {
+  const double n = (double)(w.PN[y] - w.PN[x]), s = (double)(w.PS[y] - w.PS[x]);
+  return y > x ? (s * s) / n : 0.0;
+}
+
+// F at one split, in the definition's order.
+__device__ __forceinline__ double km_F(double f1, double s2, double n2, double f3) {
+  return (f1 + (s2 * s2) / n2) + f3;
+}
+
+// The best F at a tile's first split, and the sum of squares of each tile's
+// values.
+__global__ __launch_bounds__(kBlock) void rp_km_corners(PartWs w) {
+  __shared__ double sF[kWavesPerBlock];
+  const int V = w.meta[0];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int nb = (V + kKmTile - 1) / kKmTile;
+  const int b = (int)blockIdx.x * kWavesPerBlock + wv;
+  static_assert(kKmCorners * kWavesPerBlock >= EWSJF_MAX_LEN / kKmTile && kKmTile == kWave, "a wave per value tile");
+  if (b < nb) {
+    const int j = b * kKmTile + lane;
+    double q = 0.0;
+    if (j < V) {
+      const double v = (double)w.v[j];
+      q = (double)w.c[j] * (v * v);
+    }
+    for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off);
+    if (lane == 0) w.km_Q[b] = q;
+  }
+  double best = 0.0;
+  for (int t = (int)blockIdx.x * kBlock + tid; t < nb * nb; t += kKmCorners * kBlock) {
+    const int ti = t / nb, tj = t - ti * nb;
+    const int i = max(ti * kKmTile, 1), j = max(tj * kKmTile, i + 1);
+    if (tj < ti || j > V - 1) continue;
+    const double F = km_F(km_f(w, 0, i), (double)(w.PS[j] - w.PS[i]), (double)(w.PN[j] - w.PN[i]), km_f(w, j, V));
+    best = F > best ? F : best;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(best, off);
+    best = o > best ? o : best;
+  }
+  if (lane == 0) sF[wv] = best;
+  __syncthreads();
+  if (tid == 0) {
+    for (int q = 1; q < kWavesPerBlock; ++q) best = sF[q] > best ? sF[q] : best;
+    w.km_corner[blockIdx.x] = best;
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void rp_kmeans3(PartWs w) {
   __shared__ double sF[kWavesPerBlock];
   __shared__ int si[kWavesPerBlock], sj[kWavesPerBlock];
+  __shared__ int tiles[kKmMaxTests];
+  __shared__ int ntiles;
   const int V = w.meta[0];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   double bF = -1.0;
   int bi = 0x7fffffff, bj = 0x7fffffff;
   if (V > 3) {
-    const double nV = (double)w.PN[V], sV = (double)w.PS[V];
-    (void)nV;
-    (void)sV;
-    for (int i = 1 + blockIdx.x; i <= V - 2; i += gridDim.x) {
-      const int64_t Ni = w.PN[i], Si = w.PS[i];
-      for (int j = i + 1 + threadIdx.x; j <= V - 1; j += kBlock) {
-        const int64_t Nj = w.PN[j], Sj = w.PS[j];
+    double best = w.km_corner[lane];
+    static_assert(kKmCorners == kWave, "one corner maximum per lane");
+    for (int off = 32; off > 0; off >>= 1) {
+      const double o = __shfl_xor(best, off);
+      best = o > best ? o : best;
+    }
+    if (tid == 0) ntiles = 0;
+    __syncthreads();
+    // Which of this workgroup's tiles can hold the maximum.  Every operand is
+    // positive, so the bound and the corner values are within 1e-14 of their
+    // exact values, far inside the margin.
+    const int nb = (V + kKmTile - 1) / kKmTile;
+    for (int t = (int)blockIdx.x + kKmeansBlocks * tid; t < nb * nb; t += kKmeansBlocks * kBlock) {
+      const int ti = t / nb, tj = t - ti * nb;
+      if (tj < ti) continue;
+      const int i0 = max(ti * kKmTile, 1), i1 = min(ti * kKmTile + kKmTile - 1, V - 2);
+      const int j0 = max(tj * kKmTile, 2), j1 = min(tj * kKmTile + kKmTile - 1, V - 1);
+      if (i0 > i1 || j0 > j1) continue;
+      const double ub = (km_f(w, 0, i0) + km_f(w, i1, j0)) + km_f(w, j1, V) +
+                        (w.km_Q[ti] + (tj > ti ? w.km_Q[tj] : 0.0));
+      if (ub * (1.0 + 1e-12) >= best) tiles[atomicAdd(&ntiles, 1)] = t;
+    }
+    __syncthreads();
+    const int64_t NV = w.PN[V], SV = w.PS[V];
+    for (int k = 0; k < ntiles; ++k) {  // a lane per j, a wave per i
+      const int ti = tiles[k] / nb, tj = tiles[k] - ti * nb;
+      const int j = tj * kKmTile + lane;
+      const bool in = j >= 2 && j <= V - 1;
+      const int64_t Nj = w.PN[in ? j : 0], Sj = w.PS[in ? j : 0];
+      const double n3 = (double)(NV - Nj), s3 = (double)(SV - Sj);
+      const double f3 = (s3 * s3) / n3;
+#pragma unroll
+      for (int r = 0; r < kKmTile / kWavesPerBlock; ++r) {
+        const int i = ti * kKmTile + r * kWavesPerBlock + wv;  // wave-uniform
+        if (i < 1 || i > V - 2) continue;
+        const int64_t Ni = w.PN[i], Si = w.PS[i];
         const double n1 = (double)Ni, s1 = (double)Si;
-        const double n2 = (double)(Nj - Ni), s2 = (double)(Sj - Si);
-        const double n3 = (double)(w.PN[V] - Nj), s3 = (double)(w.PS[V] - Sj);
-        const double F = ((s1 * s1) / n1 + (s2 * s2) / n2) + (s3 * s3) / n3;
-        if (km_better(F, i, j, bF, bi, bj)) {
+        const double F = km_F((s1 * s1) / n1, (double)(Sj - Si), (double)(Nj - Ni), f3);
+        if (in && j > i && km_better(F, i, j, bF, bi, bj)) {
           bF = F;
           bi = i;
           bj = j;
@@ -339,14 +444,13 @@ __global__ __launch_bounds__(kBlock) void rp_kmeans3(PartWs w) {
       bj = oj;
     }
   }
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
   if (lane == 0) {
     sF[wv] = bF;
     si[wv] = bi;
     sj[wv] = bj;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     for (int q = 0; q < kWavesPerBlock; ++q)
       if (km_better(sF[q], si[q], sj[q], bF, bi, bj)) {
         bF = sF[q];
@@ -359,18 +463,28 @@ __global__ __launch_bounds__(kBlock) void rp_kmeans3(PartWs w) {
   }
 }
 
-__global__ void rp_kmeans3_pick(PartWs w, int nblocks) {
-  if (threadIdx.x != 0) return;
+// The best split over rp_kmeans3's workgroups, in every lane of one wave.
+__device__ __forceinline__ void km_pick(const PartWs& w, int* ki, int* kj) {
+  const int lane = threadIdx.x & (kWave - 1);
   double bF = -1.0;
   int bi = 0x7fffffff, bj = 0x7fffffff;
-  for (int q = 0; q < nblocks; ++q)
+  for (int q = lane; q < kKmeansBlocks; q += kWave)
     if (km_better(w.km_F[q], w.km_ij[2 * q], w.km_ij[2 * q + 1], bF, bi, bj)) {
       bF = w.km_F[q];
       bi = w.km_ij[2 * q];
       bj = w.km_ij[2 * q + 1];
     }
-  w.meta[1] = bi;
-  w.meta[2] = bj;
+  for (int off = 32; off > 0; off >>= 1) {
+    const double oF = __shfl_xor(bF, off);
+    const int oi = __shfl_xor(bi, off), oj = __shfl_xor(bj, off);
+    if (km_better(oF, oi, oj, bF, bi, bj)) {
+      bF = oF;
+      bi = oi;
+      bj = oj;
+    }
+  }
+  *ki = bi;
+  *kj = bj;
 }
 
 // ---------------------------------------------------------------------------
@@ -553,7 +667,8 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
       sat(sm, j) = s;
     }
   } else {
-    const int ki = w.meta[1], kj = w.meta[2];
+    int ki, kj;
+    km_pick(w, &ki, &kj);  // every wave, the same result
     for (int j = tid; j < V; j += kBlock) {
       uint8_t s;
       if (V <= 3) s = 1;
@@ -1146,8 +1261,8 @@ hipError_t launch_stages(const PartWs& w, const ewsjf_partition_params& p, int64
   const int L = p.max_len;
   hipLaunchKernelGGL(rp_distinct, dim3(1), dim3(kBlock), 0, stream, w, L);
   if (p.init_mode == EWSJF_INIT_KMEANS3) {
+    hipLaunchKernelGGL(rp_km_corners, dim3(kKmCorners), dim3(kBlock), 0, stream, w);
     hipLaunchKernelGGL(rp_kmeans3, dim3(kKmeansBlocks), dim3(kBlock), 0, stream, w);
-    hipLaunchKernelGGL(rp_kmeans3_pick, dim3(1), dim3(64), 0, stream, w, kKmeansBlocks);
   }
   hipLaunchKernelGGL(rp_refine_prune, dim3(1), dim3(kBlock), 0, stream, w, p, n_window, table);
   hipLaunchKernelGGL(rp_merge, dim3(1), dim3(kMergeThreads), 0, stream, w, p, table);

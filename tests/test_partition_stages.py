@@ -56,3 +56,31 @@ def test_stage3_merges(name, K, mq, mw, leaves):
     assert leaves[0] <= ref.n_leaves <= leaves[1]
     prm = E.params(init_queues=K, max_queues=mq, min_width=mw)
     check_table(E.read_table(E.partition(torch.from_numpy(win).cuda(), prm)), ref)
+
+
+# Windows for the 3-means splits: one value tile and its edges (63, 64, 65
+# distinct values), a few, the most; ties between splits; one far value.
+KMEANS3 = {
+    "v2": lambda r: np.array([5, 9, 9], np.int32),
+    "v3": lambda r: np.array([5, 9, 700], np.int32),
+    "v4": lambda r: np.array([1, 2, 3, 4], np.int32),
+    "v63": lambda r: r.permutation(np.arange(1, 64, dtype=np.int32)),
+    "v64": lambda r: np.repeat(np.arange(100, 164, dtype=np.int32), 2),
+    "v65": lambda r: np.arange(1, 66, dtype=np.int32) * 500,
+    "v129_symmetric": lambda r: np.concatenate([np.arange(1, 65), [16384], 32768 - np.arange(1, 65)]).astype(np.int32),
+    "far_value": lambda r: np.concatenate([r.integers(1, 400, 5000), [32768]]).astype(np.int32),
+    "three_modes": lambda r: W._lengths(r, 20000, W.MIX_THREE),
+    "uniform": lambda r: r.integers(1, 32769, 60000).astype(np.int32),
+    "all_lengths": lambda r: np.arange(1, 32769, dtype=np.int32),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", list(KMEANS3))
+def test_kmeans3_split(name):
+    from paper_2601_21758_amd import ewsjf as E
+    win = KMEANS3[name](np.random.default_rng(7))
+    print(f"3-means {name} W={win.size}", flush=True)
+    ref = oracle.partition(win, init_mode=oracle.KMEANS3, max_queues=32)
+    prm = E.params(init_mode=1, max_queues=32)
+    check_table(E.read_table(E.partition(torch.from_numpy(win).cuda(), prm)), ref)
