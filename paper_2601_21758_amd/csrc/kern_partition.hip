@@ -491,113 +491,77 @@ __device__ __forceinline__ void km_pick(const PartWs& w, int* ki, int* kj) {
 // Stage 3 utility of the adjacent pair (a, b), Eq. 3 with density = count per
 // token of value span.  Same binary64 expression order as the definition.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double utility(int64_t na, int64_t Sa, int32_t loa, int32_t hia, int64_t nb, int64_t Sb,
-                                          int32_t lob, int32_t hib, double eps) {
-  const double rho_a = (double)na / (double)((int64_t)hia - (int64_t)loa + 1);
-  const double rho_b = (double)nb / (double)((int64_t)hib - (int64_t)lob + 1);
-  const double m_a = (double)Sa / (double)na;
-  const double m_b = (double)Sb / (double)nb;
-  return (rho_a + rho_b) / (fabs(m_b - m_a) + eps);
-}
-
-// The same expression on per-leaf densities and means computed once (the
-// division results are identical to recomputing them).
+// rho = count / (hi - lo + 1) and m = sum / count of each are computed once.
 __device__ __forceinline__ double utility_cached(double rho_a, double m_a, double rho_b, double m_b, double eps) {
   return (rho_a + rho_b) / (fabs(m_b - m_a) + eps);
 }
 
 __device__ __forceinline__ uint64_t dbits(double x) { return (uint64_t)__double_as_longlong(x); }
 
+// ---------------------------------------------------------------------------
+// Stages 1 and 2, one workgroup.  The distinct values sit in LDS; segment
+// (cluster) starts are bits of 64-bit words, one word per 64 consecutive
+// values (a wave's group), so the segment of a value is a count of bits.
+//
+// A level of Stage 2 cuts every gap g of a segment of VC values over a span
+// with g (VC - 1) > alpha span (binary64, in this order).  The left side never
+// falls as g grows, so a segment's test is a whole-number threshold on its
+// gaps, found once per segment (a thread each) from a quotient and corrected
+// with the test itself; a level is then one compare per value against its
+// segment's threshold.  With the test evaluated for every gap a level took
+// 14 us (two conversions and two binary64 products per gap, 32 gaps per
+// thread whatever V), the kernel 78-87 us; it takes 36-51 us now.
+// ---------------------------------------------------------------------------
+constexpr int kGroups = EWSJF_MAX_LEN / kWave;  // 512
+constexpr int kNoCut = 0xFFFF;                  // above every gap
+constexpr int kGroupBatch = 4;                  // groups a wave has in flight
 
-struct ArgMin {
-  double u;
-  int i;
-};
-
-__device__ __forceinline__ ArgMin argmin_pick(ArgMin a, ArgMin b) {
-  if (b.u < a.u || (b.u == a.u && b.i < a.i)) return b;
-  return a;
-}
-
-__device__ ArgMin block_argmin(ArgMin x, double* su, int* si) {
-  for (int off = 32; off > 0; off >>= 1) {
-    ArgMin o;
-    o.u = __shfl_xor(x.u, off);
-    o.i = __shfl_xor(x.i, off);
-    x = argmin_pick(x, o);
-  }
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane == 0) {
-    su[wv] = x.u;
-    si[wv] = x.i;
-  }
-  __syncthreads();
-  ArgMin r{su[0], si[0]};
-  for (int q = 1; q < kWavesPerBlock; ++q) r = argmin_pick(r, ArgMin{su[q], si[q]});
-  __syncthreads();
-  return r;
-}
-
-// The distinct values and the cluster-start flags sit in LDS padded by 4
-// bytes per 32 entries (vat / sat): a thread owns 32 consecutive entries,
-// and without the padding the lanes of a wave read them 64 (values) or 32
-// (flags) bytes apart, 16- and 8-way bank conflicts.
 struct RpShared {
-  union {
-    struct {
-      uint16_t v[EWSJF_MAX_LEN + 2 * (EWSJF_MAX_LEN / 32)];
-      uint8_t start[EWSJF_MAX_LEN + 4 * (EWSJF_MAX_LEN / 32)];
-    } a;
-  } u;
-  int64_t scr64[kWavesPerBlock];
-  double su[kWavesPerBlock];
-  int si[kWavesPerBlock];
+  uint16_t v[EWSJF_MAX_LEN];
+  uint16_t seg[EWSJF_MAX_LEN];  // of each segment: its start, then the gap threshold
+  uint64_t start[kGroups];      // bit l of word g: value 64 g + l starts a segment
+  uint64_t cut[kGroups];        // bit l of word g: the gap after value 64 g + l is cut
+  uint16_t first[kGroups];      // segments that start before the group
   int iscr[kWavesPerBlock];
-  int flag;
 };
 
-__device__ __forceinline__ uint16_t& vat(RpShared& sm, int j) { return sm.u.a.v[j + 2 * (j >> 5)]; }
-__device__ __forceinline__ uint8_t& sat(RpShared& sm, int j) { return sm.u.a.start[j + 4 * (j >> 5)]; }
-
-// For thread-owned index ranges [j0, j0 + 32): carry_s = the last segment
-// start before j0 (-1 if none), carry_e = the first segment start after the
-// range (V if none).
-__device__ void segment_carries(RpShared& sm, int V, int j0, int* carry_s, int* carry_e) {
-  const int tid = threadIdx.x;
-  int last = -1, first = 0x7fffffff;
-  for (int q = 0; q < kBinsPerThread; ++q) {
-    const int j = j0 + q;
-    if (j < V && sat(sm, j)) {
-      last = j;
-      if (first == 0x7fffffff) first = j;
+// The segments' starts in order, sm.seg[0..nseg), from the start bits `mine`
+// of group tid (tid < kGroups, also in sm.start); returns nseg.
+__device__ int list_segments(RpShared& sm, uint64_t mine, int ng) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  int nseg = 0;
+  const int before = block_exclusive_scan((int)__popcll(mine), sm.iscr, &nseg);
+  if (tid < kGroups) sm.first[tid] = (uint16_t)before;  // below 32768 wherever the group has a start
+  __syncthreads();
+  for (int g0 = wv; g0 < ng; g0 += kGroupBatch * kWavesPerBlock) {
+    uint64_t m[kGroupBatch];
+    int f[kGroupBatch];
+#pragma unroll
+    for (int u = 0; u < kGroupBatch; ++u) {
+      const int g = min(g0 + u * kWavesPerBlock, kGroups - 1);
+      m[u] = sm.start[g];
+      f[u] = sm.first[g];
+    }
+#pragma unroll
+    for (int u = 0; u < kGroupBatch; ++u) {
+      const int g = g0 + u * kWavesPerBlock;
+      if (g < ng && ((m[u] >> lane) & 1ull)) sm.seg[f[u] + lanes_below(m[u])] = (uint16_t)(g * kWave + lane);
     }
   }
-  const int lane = tid & (kWave - 1), wv = tid / kWave;
-  int incl = last;
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int y = __shfl_up(incl, off);
-    if (lane >= off) incl = incl > y ? incl : y;
-  }
-  int rincl = first;
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int y = __shfl_down(rincl, off);
-    if (lane + off < kWave) rincl = rincl < y ? rincl : y;
-  }
   __syncthreads();
-  if (lane == kWave - 1) sm.iscr[wv] = incl;
-  if (lane == 0) sm.si[wv] = rincl;
-  __syncthreads();
-  int wmax = -1, wmin = 0x7fffffff;
-  for (int q = 0; q < wv; ++q) wmax = sm.iscr[q] > wmax ? sm.iscr[q] : wmax;
-  for (int q = wv + 1; q < kWavesPerBlock; ++q) wmin = sm.si[q] < wmin ? sm.si[q] : wmin;
-  const int prev_in_wave = __shfl_up(incl, 1);
-  const int next_in_wave = __shfl_down(rincl, 1);
-  const int cs = lane > 0 ? (prev_in_wave > wmax ? prev_in_wave : wmax) : wmax;
-  const int ce = lane < kWave - 1 ? (next_in_wave < wmin ? next_in_wave : wmin) : wmin;
-  __syncthreads();
-  *carry_s = cs;
-  *carry_e = ce < V ? ce : V;
+  return nseg;
+}
+
+// The largest gap that a segment of VC values over `span` (mm1: its VC - 1,
+// or its entries - 1 in the multiset reading) does not cut.
+__device__ __forceinline__ int gap_threshold(double alpha, int span, double mm1) {
+  const double rhs = alpha * (double)span;
+  const double q = rhs / mm1;
+  if (!(q < 40000.0)) return kNoCut;
+  int t = (int)q;
+  while (t < 40000 && !((double)(t + 1) * mm1 > rhs)) ++t;
+  while (t > 0 && (double)t * mm1 > rhs) --t;
+  return t;
 }
 
 // The queue table from k queues in length order, given by the prefix sums of
@@ -620,7 +584,7 @@ __device__ void write_queues(ewsjf_queue_table* tab, int k, const int64_t* N, co
 __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partition_params p, int64_t n_window,
                                                           ewsjf_queue_table* tab) {
   __shared__ RpShared sm;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   const int V = w.meta[0];
   const int L = p.max_len;
   if (V == 0) {
@@ -639,138 +603,122 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
     return;
   }
 
-  // ---- Stage 1: coarse cluster starts -------------------------------------
   {
-    // Every load is issued before the first store (bounded: past V they read 0).
+    // Eight loads in flight per thread (bounded: past V they read 0).
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(w.v, (short)0, V * 4, kBufferWord3);
-    uint32_t x[kBinsPerThread];
+    for (int j0 = tid; j0 < V; j0 += 8 * kBlock) {
+      uint32_t x[8];
 #pragma unroll
-    for (int k = 0; k < kBinsPerThread; ++k)
-      x[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, (tid + k * kBlock) * 4, 0, 0);
+      for (int k = 0; k < 8; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, (j0 + k * kBlock) * 4, 0, 0);
 #pragma unroll
-    for (int k = 0; k < kBinsPerThread; ++k)
-      if (tid + k * kBlock < V) vat(sm, tid + k * kBlock) = (uint16_t)x[k];
+      for (int k = 0; k < 8; ++k)
+        if (j0 + k * kBlock < V) sm.v[j0 + k * kBlock] = (uint16_t)x[k];
+    }
   }
+  if (tid < kGroups) sm.start[tid] = 0ull;
   __syncthreads();
-  const int64_t vlo = vat(sm, 0), vhi = vat(sm, V - 1);
+  const int ng = (V + kWave - 1) / kWave;  // groups in use
+
+  // ---- Stage 1: coarse cluster starts -------------------------------------
   if (p.init_mode == EWSJF_INIT_EQUAL_WIDTH) {
-    const int64_t width = vhi - vlo + 1;
-    for (int j = tid; j < V; j += kBlock) {
-      uint8_t s = 1;
-      if (j > 0) {
-        // (v - lo) K < 2^30 (values and K are at most 32768): the 32-bit
-        // quotient is the exact floor of the int64 definition.
-        const uint32_t b1 = (uint32_t)(vat(sm, j) - vlo) * (uint32_t)p.init_queues / (uint32_t)width;
-        const uint32_t b0 = (uint32_t)(vat(sm, j - 1) - vlo) * (uint32_t)p.init_queues / (uint32_t)width;
-        s = b1 != b0;
-      }
-      sat(sm, j) = s;
+    // (v - lo) K < 2^30 (values and K are at most 32768): the 32-bit quotient
+    // is the exact floor of the int64 definition.
+    const uint32_t vlo = sm.v[0], width = (uint32_t)sm.v[V - 1] - vlo + 1u;
+    auto bin = [&](int j) { return ((uint32_t)sm.v[j] - vlo) * (uint32_t)p.init_queues / width; };
+    const int per = (ng + kWavesPerBlock - 1) / kWavesPerBlock;  // consecutive groups per wave
+    const int g0 = wv * per, g1 = min(ng, g0 + per);
+    uint32_t before = g0 > 0 && g0 < g1 ? bin(g0 * kWave - 1) : 0xFFFFFFFFu;  // the bin of the value before the group
+    for (int g = g0; g < g1; ++g) {
+      const int j = g * kWave + lane;
+      const uint32_t b = bin(min(j, V - 1));
+      const uint32_t up = (uint32_t)__shfl_up((int)b, 1);
+      const uint64_t m = __ballot(j < V && b != (lane > 0 ? up : before));
+      if (lane == 0) sm.start[g] = m;
+      before = (uint32_t)__builtin_amdgcn_readlane((int)b, kWave - 1);
     }
   } else {
     int ki, kj;
     km_pick(w, &ki, &kj);  // every wave, the same result
-    for (int j = tid; j < V; j += kBlock) {
-      uint8_t s;
-      if (V <= 3) s = 1;
-      else s = (j == 0 || j == ki || j == kj) ? 1 : 0;
-      sat(sm, j) = s;
+    for (int g = wv; g < ng; g += kWavesPerBlock) {
+      const int j = g * kWave + lane;
+      const uint64_t m = __ballot(j < V && (V <= 3 || j == 0 || j == ki || j == kj));
+      if (lane == 0) sm.start[g] = m;
     }
   }
   __syncthreads();
-  int n_coarse = 0;
-  {
-    int cnt = 0;
-    for (int j = tid; j < V; j += kBlock) cnt += sat(sm, j);
-    int tot = 0;
-    block_exclusive_scan(cnt, sm.iscr, &tot);
-    n_coarse = tot;
-  }
+  uint64_t mine = tid < kGroups ? sm.start[tid] : 0ull;  // the start bits of group tid
+  int nl = list_segments(sm, mine, ng);
+  const int n_coarse = nl;
 
   // ---- Stage 2: level-synchronous refinement --------------------------------
-  // Thread t owns distinct indices [32t, 32t + 32).
-  const int j0 = tid * kBinsPerThread;
-  const int min_distinct = p.gap_mode == EWSJF_GAPS_DISTINCT ? 3 : 2;
-  int carry_s = -1, carry_e = V;
+  const bool distinct = p.gap_mode == EWSJF_GAPS_DISTINCT;
+  const int min_distinct = distinct ? 3 : 2;
   for (;;) {
-    segment_carries(sm, V, j0, &carry_s, &carry_e);
-    // This thread's segment starts as a bit mask (bit q: index j0 + q); the
-    // segment [s, e) holding index j0 + q starts at the highest set bit <= q
-    // (else carry_s) and ends at the lowest set bit > q (else carry_e).
-    // Branch-free and unrolled, so the LDS reads of all 32 gaps are issued
-    // together; indices of gaps that are not tested are clamped to 0.
-    uint32_t mask = 0u;
-#pragma unroll
-    for (int q = 0; q < kBinsPerThread; ++q) mask |= (uint32_t)(j0 + q < V && sat(sm, j0 + q)) << q;
-    uint32_t newcuts = 0;
-#pragma unroll
-    for (int q = 0; q < kBinsPerThread; ++q) {
-      const int j = j0 + q;
-      const uint32_t below = mask & (0xFFFFFFFFu >> (31 - q));
-      const int s = below ? j0 + 31 - __clz((int)below) : carry_s;
-      const uint32_t above = q < 31 ? mask >> (q + 1) : 0u;
-      const int e = above ? j + __ffs((int)above) : carry_e;
-      // the gap between j and j+1 inside the segment [s, e)
-      const bool gap = j + 1 < e;  // (e <= V, so j + 1 < V)
-      const int VC = e - s;
-      const int64_t span = (int64_t)vat(sm, gap ? e - 1 : 0) - (int64_t)vat(sm, gap ? s : 0);
-      const bool test = gap && VC >= min_distinct && span >= (int64_t)p.min_width;
-      // span, the gap and VC - 1 fit in int32 (values are at most 32768), so
-      // they convert to binary64 in one exact step; the count-mode m - 1 is
-      // an int64 count.
-      const double mm1 = p.gap_mode == EWSJF_GAPS_DISTINCT ? (double)(VC - 1)
-                                                           : (double)(test ? (w.PN[e] - w.PN[s]) - 1 : 0);
-      const double rhs = p.alpha * (double)(int)span;
-      const double lhs = (double)((int)vat(sm, gap ? j + 1 : 0) - (int)vat(sm, gap ? j : 0)) * mm1;
-      if (test && lhs > rhs) newcuts |= 1u << q;
+    // The threshold of every segment takes the place of its start (a tile of
+    // starts is read, with the next segment's, before it is overwritten).
+    for (int i0 = 0; i0 < nl; i0 += kBlock) {
+      const int i = i0 + tid;
+      int t = kNoCut;
+      if (i < nl) {
+        const int j = sm.seg[i], e = i + 1 < nl ? (int)sm.seg[i + 1] : V;
+        const int span = (int)sm.v[e - 1] - (int)sm.v[j];
+        if (e - j >= min_distinct && span >= p.min_width)
+          t = gap_threshold(p.alpha, span, distinct ? (double)(e - j - 1) : (double)((w.PN[e] - w.PN[j]) - 1));
+      }
+      __syncthreads();
+      if (i < nl) sm.seg[i] = (uint16_t)t;
     }
-    const int any = __syncthreads_or(newcuts != 0);
-    if (!any) break;
-    for (int q = 0; q < kBinsPerThread; ++q)
-      if (newcuts & (1u << q)) sat(sm, j0 + q + 1) = 1;
     __syncthreads();
+    // Every gap against its segment's threshold.
+    for (int g0 = wv; g0 < ng; g0 += kGroupBatch * kWavesPerBlock) {
+      int gap[kGroupBatch], thr[kGroupBatch];
+#pragma unroll
+      for (int u = 0; u < kGroupBatch; ++u) {
+        const int g = min(g0 + u * kWavesPerBlock, ng - 1);
+        const int j = g * kWave + lane;
+        gap[u] = (int)sm.v[min(j + 1, V - 1)] - (int)sm.v[min(j, V - 1)];  // 0 past the last value: never cut
+        const uint64_t upto = sm.start[g] & (~0ull >> (kWave - 1 - lane));
+        thr[u] = sm.seg[(int)sm.first[g] + (int)__popcll(upto) - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kGroupBatch; ++u) {
+        const uint64_t cm = __ballot(gap[u] > thr[u]);
+        if (lane == 0 && g0 + u * kWavesPerBlock < ng) sm.cut[g0 + u * kWavesPerBlock] = cm;
+      }
+    }
+    __syncthreads();
+    // A cut gap starts a segment at the next value (a gap between two
+    // segments is one already).
+    uint64_t now = mine;
+    if (tid < ng) now |= (sm.cut[tid] << 1) | (tid > 0 ? sm.cut[tid - 1] >> 63 : 0ull);
+    const int any = __syncthreads_or(now != mine);
+    mine = now;
+    if (tid < ng) sm.start[tid] = mine;
+    __syncthreads();
+    nl = list_segments(sm, mine, ng);
+    if (!any) break;
   }
 
   // ---- Leaves: one per segment, aggregates from the exact prefix sums -------
-  // The segment starts are listed in order (in the Stage-3 workspace, which
-  // rp_merge rewrites later), then each thread builds whole leaves.
-  int nl = 0;
-  {
-    int cnt = 0;
-    for (int q = 0; q < kBinsPerThread; ++q) {
-      const int j = j0 + q;
-      if (j < V) cnt += sat(sm, j);
-    }
-    int tot = 0;
-    int pos = block_exclusive_scan(cnt, sm.iscr, &tot);
-    nl = tot;
-    int32_t* starts = reinterpret_cast<int32_t*>(w.gU);
-    for (int q = 0; q < kBinsPerThread; ++q) {
-      const int j = j0 + q;
-      if (j < V && sat(sm, j)) starts[pos++] = j;
-    }
-    __syncthreads();
-    for (int i = tid; i < nl; i += kBlock) {
-      const int s = starts[i];
-      const int e = i + 1 < nl ? starts[i + 1] : V;
-      w.gN[i] = w.PN[s];
-      w.gS[i] = w.PS[s];
-      w.glo[i] = vat(sm, s);
-      w.ghi[i] = vat(sm, e - 1);
-    }
-    if (tid == 0) {
-      w.gN[nl] = w.PN[V];
-      w.gS[nl] = w.PS[V];
-    }
+  for (int i = tid; i < nl; i += kBlock) {
+    const int j = sm.seg[i], e = i + 1 < nl ? (int)sm.seg[i + 1] : V;
+    w.gN[i] = w.PN[j];
+    w.gS[i] = w.PS[j];
+    w.glo[i] = sm.v[j];
+    w.ghi[i] = sm.v[e - 1];
+  }
+  if (tid == 0) {
+    w.gN[nl] = w.PN[V];
+    w.gS[nl] = w.PS[V];
   }
   __threadfence();
   __syncthreads();
-  const int n_leaves = nl;
   if (tid == 0) {
-    w.meta[3] = n_leaves;
+    w.meta[3] = nl;
     tab->max_len = L;
     tab->n_distinct = V;
     tab->n_coarse = n_coarse;
-    tab->n_leaves = n_leaves;
+    tab->n_leaves = nl;
     tab->gapped = 0;
     tab->n_window = n_window >= 0 ? n_window : w.PN[V];
   }

@@ -84,3 +84,34 @@ def test_kmeans3_split(name):
     ref = oracle.partition(win, init_mode=oracle.KMEANS3, max_queues=32)
     prm = E.params(init_mode=1, max_queues=32)
     check_table(E.read_table(E.partition(torch.from_numpy(win).cuda(), prm)), ref)
+
+
+def _stage2_window(name):
+    rng = np.random.default_rng(sum(map(ord, name)))
+    if name.startswith("v"):  # that many distinct values, irregular gaps, repeated counts
+        n = int(name[1:])
+        v = np.sort(rng.choice(np.arange(1, 32769), n, replace=False))
+        return np.repeat(v, rng.integers(1, 4, n)).astype(np.int32)
+    if name == "clusters":    # gaps inside gaps: several levels of refinement
+        v = [a * 8192 + b * 512 + c * 32 + d for a in range(4) for b in (0, 1, 2, 9) for c in (0, 1, 5) for d in (0, 1, 2)]
+        return (np.array(v) + 1).astype(np.int32)
+    if name == "on_the_line":  # gaps equal to alpha times the mean gap are not cut
+        return np.cumsum([1] + [1, 1, 4, 1, 1, 4, 1, 1, 2] * 40).astype(np.int32)
+    raise ValueError(name)
+
+
+STAGE2 = [f"v{n}" for n in (1, 2, 3, 63, 64, 65, 128, 1023, 1025, 4097, 32768)] + ["clusters", "on_the_line"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("gap_mode", [0, 1])
+@pytest.mark.parametrize("name", STAGE2)
+def test_stage2_cuts(name, gap_mode):
+    """Segment words and their edges, one and several levels, both gap readings, three ratios alpha."""
+    from paper_2601_21758_amd import ewsjf as E
+    win = _stage2_window(name)
+    for alpha, K, mw in ((2.0, 16, 16), (1.01, 1, 0), (3.7, 200, 3)):
+        print(f"stage 2 {name} gap_mode={gap_mode} alpha={alpha} K={K}", flush=True)
+        ref = oracle.partition(win, init_queues=K, max_queues=256, min_width=mw, alpha=alpha, gap_mode=gap_mode)
+        prm = E.params(init_queues=K, max_queues=256, min_width=mw, alpha=alpha, gap_mode=gap_mode)
+        check_table(E.read_table(E.partition(torch.from_numpy(win).cuda(), prm)), ref)
