@@ -24,7 +24,7 @@ default all; `--no-extra` for none): "small_configs" -- the same step on
 the 4,096-request and 262,144-request pools; "tactical" -- Algorithm 1's own
 batch rule on the 4M pool (ewsjf_tactical_step); "batched_theta" -- one
 1,048,576-request pool scored and selected under 256 parameter vectors per
-step (top-256 each), with its VALU roofline from the committed counters;
+step (top-256 each);
 "streaming" -- 10,000 steps of the streaming scheduler (1,048,576-slot
 ring, 4,096 arrivals and 512 admissions per step, Refine-and-Prune over the
 last 65,536 arrivals every 100 steps on a side stream), per-step device
@@ -60,11 +60,7 @@ METRIC = "pending requests routed+scored+selected per sec at 4M pool; % HBM peak
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_REQUEST = 8  # int32 prompt length + float32 arrival, each read once
 PROFILE = os.path.join(ROOT, "profiles", "fused_step_large_mixed_4m.pmc.txt")
-PROFILE_BATCHED = os.path.join(ROOT, "profiles", "batched_theta_1m.pmc.txt")
 KERNEL_SOURCES = ("paper_2601_21758_amd/csrc/kern_select.hip", "paper_2601_21758_amd/csrc/ewsjf_device.h")
-# VALU issue peak: 256 CUs x 4 SIMDs, one wave64 VALU instruction per SIMD
-# every 4 cycles (16 lanes wide), at 2.4 GHz.
-VALU_PEAK_G = 256 * 4 * 2.4 / 4
 
 
 def kernel_source_hash() -> str:
@@ -262,25 +258,10 @@ def batched_theta_bench(hip, steps: int = 20):
     out = {"workload": "batched_theta_1m: 1,048,576 requests (3-mode lognormal mix), 64-queue policy, "
                        "256 parameter vectors drawn in the stated ranges, top B=256 per vector",
            "ms_per_step": ms, "request_theta_pairs_per_s": n * nt / (ms * 1e-3),
-           "kernels_ms": {"local_candidates_multi": k1, "merge_candidates": k2}, "steps": steps,
-           "input_sha256": pool.digest()[:16], "roofline": None}
-    # The many-vector kernel does ~20 VALU operations per (request, vector)
-    # pair on 8 bytes per request: the VALU, not HBM, bounds it.  Its
-    # instruction counts come from the committed counter run (counts do not
-    # depend on timing), the duration from the events above.
-    kv = read_pmc(PROFILE_BATCHED)
-    if kv is not None:
-        valu = float(kv["local_candidates_multi.SQ_INSTS_VALU"])
-        ach = valu / (k1 * 1e-3) / 1e9
-        out["roofline"] = {
-            "bound": "alu", "kernel": "local_candidates_multi (route+score+local top-B, 16 vectors per workgroup)",
-            "achieved": ach, "peak": VALU_PEAK_G, "unit": "G VALU wave64 instructions/s", "frac": ach / VALU_PEAK_G,
-            "valu_insts_per_launch": valu, "kernel_ms": k1,
-            "lds_insts_per_launch": float(kv["local_candidates_multi.SQ_INSTS_LDS"]),
-            "lds_util": float(kv["local_candidates_multi.lds_util"]),
-            "lds_bank_conflict_per_access": float(kv["local_candidates_multi.lds_bank_conflict_per_access"]),
-            "hbm_frac": 8 * n / (k1 * 1e-3) / 1e9 / HBM_PEAK_GBS,
-            "counters": os.path.relpath(PROFILE_BATCHED, ROOT)}
+           "kernels_ms": {"pool_filter": k1, "theta_select": k2}, "steps": steps,
+           "input_sha256": pool.digest()[:16],
+           # one read of the pool; the step is a chain of six short kernels
+           "step_hbm_frac": 8 * n / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
     return out
 
 

@@ -315,7 +315,9 @@ ewsjf_status ewsjf_step(int32_t* len, const float* arrival, int64_t n, float now
 /* ewsjf_step that also times its two kernels with four caller-created events
  * (hipEventCreate, timing enabled): marks[0]/marks[1] take the start/end of
  * the streaming kernel (routing, scoring and per-workgroup candidates),
- * marks[2]/marks[3] the start/end of the merge kernel (exact top-B).  For
+ * marks[2]/marks[3] the start/end of the merge kernel (exact top-B).  Where
+ * several vectors share one filter of the pool, these are the filter's pass
+ * over the pool and the kernel that selects each vector's top-B.  For
  * per-phase timing by a monitor; marks == NULL behaves as ewsjf_step. */
 ewsjf_status ewsjf_step_timed(int32_t* len, const float* arrival, int64_t n, float now, const void* table,
                               const ewsjf_theta* theta, int32_t n_theta, const ewsjf_cost* cost, int32_t B,

@@ -1013,8 +1013,10 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
 // ---------------------------------------------------------------------------
 constexpr int kThetaPerBlock = 16;
 
+// only: NULL, or take the vectors t with only[t] < 0 alone (the ones the
+// filter below has not answered).
 __global__ __launch_bounds__(kBlock) void local_candidates_multi(PoolSource src, int64_t n, int n_theta, int G,
-                                                                 int lg, int M, CandBufs cb) {
+                                                                 int lg, int M, CandBufs cb, const int32_t* only) {
   __shared__ uint64_t route[kRouteWords];
   __shared__ QParams qp[kThetaPerBlock][EWSJF_MAX_QUEUES];
   __shared__ ListShared ls;
@@ -1022,6 +1024,10 @@ __global__ __launch_bounds__(kBlock) void local_candidates_multi(PoolSource src,
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   const int t0 = blockIdx.y * kThetaPerBlock;
   const int nt = n_theta - t0 < kThetaPerBlock ? n_theta - t0 : kThetaPerBlock;
+  if (only != nullptr) {  // uniform
+    static_assert(kThetaPerBlock <= kWave, "one flag per lane");
+    if (__ballot(lane < nt && only[t0 + (lane < nt ? lane : 0)] < 0) == 0ull) return;
+  }
 
   // This wave's four chunks first (the longest wait), then the table and the
   // block's parameter vectors into LDS.
@@ -1059,6 +1065,15 @@ __global__ __launch_bounds__(kBlock) void local_candidates_multi(PoolSource src,
   uint64_t* const region = ls.list + wv * kWaveCap;
   for (int tt = 0; tt < nt; ++tt) {
     const int t = t0 + tt, pb = tt & 1;
+    if (only != nullptr && only[t] >= 0) {  // uniform: answered already; leave the counters as the next vector expects
+      __syncthreads();
+      if (tid == 0) {
+        s_ovf[pb ^ 1] = 0;
+        s_nout[pb ^ 1] = 0;
+      }
+      __syncthreads();
+      continue;
+    }
     uint32_t key[kElemsPerLane];
 #pragma unroll
     for (int e = 0; e < kElemsPerLane; ++e) {
@@ -1155,16 +1170,16 @@ struct MergeShared {
 };
 
 // Exact top-B of the nonzero entries of X[0..U) (distinct composites; when
-// U <= B every entry must be nonzero), sorted descending into X[0..min(U, B)).
-// Returns the number selected.  When U > B the candidates at or above
-// a histogram cut (between B and kSortMax of them) are gathered first; the
-// gathered set is then ordered by a counting sort.
+// U <= max(B, kSortMax) every entry must be nonzero), sorted descending into
+// X[0..min(U, B)).  Returns the number selected.  More than kSortMax of them:
+// the candidates at or above a histogram cut (between B and kSortMax) are
+// gathered first.  The set is then ordered by a counting sort.
 __device__ inline int select_top(MergeShared& ms, int U, int B) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   if (U == 0) return 0;
   const uint64_t* src = ms.X;
   int nS = U;
-  if (U > B) {
+  if (U > B && U > kSortMax) {
     const uint64_t cut = find_cut(ms.X, U, B, kSortMax, ms.cnt, ms.iscan, ms.red);
     if (tid == 0) ms.cntS = 0;
     __syncthreads();
@@ -1240,6 +1255,258 @@ __device__ inline int merge_new(MergeShared& ms, int U0, int k, int B) {
   for (int i = tid; i < total; i += kBlock) ms.X[i] = ms.S[i];
   __syncthreads();
   return total;
+}
+
+// ---------------------------------------------------------------------------
+// Many parameter vectors, filtered (ewsjf_step with n_theta > 1 over a pool
+// that is large beside B; the rule is filter_plan's).
+//
+// Scoring every request under every vector is bound by VALU issue (256
+// vectors over 1M requests: 268M pairs at 23 instructions, 276 us), and
+// nearly all of it is for requests that no vector admits.  So:
+//
+//   theta_threshold  per vector t, tau_t = a score that about r / m of the
+//                    pool reaches: the r-th largest of 1,024 lane maxima over
+//                    a sample of m = 8,192 requests (16 at a time, evenly
+//                    spread), r a few above the sample's share of the B.
+//   theta_bound      per queue, the largest weights over the vectors, each in
+//                    units of its tau_t: u = max_t w_t / tau_t, 0 at least.
+//   pool_filter      one pass over the pool: with the request's three terms
+//                    x >= 0 (phi_terms), Phi_t / tau_t = w_t x / tau_t <= u x
+//                    for every t, so a request with u x < 1 scores below
+//                    tau_t under all of them.  The others are the survivors.
+//   theta_select     per vector: the survivors' keys (the same two functions
+//                    as everywhere), those at or above tau_t, their exact
+//                    top B.  At least B of them: the answer.  Otherwise, and
+//                    when the survivors exceed their buffer or tau_t says
+//                    nothing, n_sel[t] = -1.
+//   local_candidates_multi + merge_candidates  for the vectors left at -1
+//                    (launched always: the host does not wait to know; the
+//                    workgroups of answered vectors leave at once).
+//
+// Scores of one pool under the vectors of a meta-optimizer's batch order it
+// alike (the wait dominates), so survivors are few: 1,300-1,800 of 1M for 256
+// vectors with B = 256, where each vector has that many at or above tau_t.
+// 256 vectors over 1M requests take 32 us a step, where the plain kernels
+// took 278: 9.0 us for the thresholds, 3.4 for the bounds, 7.6 for the pass
+// over the pool, 11.1 for the vectors' top B, 5.3 for the two that find nothing
+// to do.
+// ---------------------------------------------------------------------------
+constexpr int kSample = 8192;        // requests in the sample, 8 per thread of theta_threshold
+constexpr int kSampleRun = 16;       // consecutive requests of one sample place
+constexpr int kSampleMaxRank = 700;  // largest r (of 1,024 lane maxima)
+constexpr int kFilterLds = 4096;     // survivors one workgroup of pool_filter holds
+constexpr int kFilterMax = 65536;    // survivors kept
+constexpr int64_t kFilterFewMax = 262144;  // pools up to this are filtered for any number of vectors
+constexpr float kFilterSlack = 1e-5f;  // relative; every rounding here is below 1e-6
+
+struct Survivor {
+  int32_t len;
+  float arrival;
+  int32_t id;
+};
+
+// In the candidate buffers' room (written only by the fallback, after the
+// last use of these).
+struct FilterBufs {
+  float* tau;       // [n_theta]: 0 = says nothing
+  f32x4* u;         // [EWSJF_MAX_QUEUES]: base, urgency, fairness (log2) weights over tau
+  int32_t* count;   // survivors found (more than cap: some were dropped)
+  Survivor* list;   // [cap]
+  int cap;
+};
+
+// The k-th largest of the wave's 16 x 64 keys to 20 bits, rounded down (at
+// least k keys are at or above it); 0 when fewer than k are above 0x80000000,
+// the key of a zero score.
+__device__ __forceinline__ uint32_t wave_kth_of_1024(const uint32_t* key, int k) {
+  uint32_t prefix = 0x80000000u;
+  for (int bit = 30; bit >= 12; --bit) {
+    const uint32_t cand = prefix | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < kWavesPerBlock; ++e) c += (int)__popcll(__ballot(key[e] >= cand));
+    if (c >= k) prefix = cand;
+  }
+  return prefix == 0x80000000u ? 0u : prefix;
+}
+
+__global__ __launch_bounds__(kBlock) void theta_threshold(PoolSource src, int64_t n, int rank, float* tau) {
+  __shared__ PoolSource::Shared sh;
+  __shared__ uint32_t best[kBlock];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), t = blockIdx.x;
+  // Sample place g holds the requests from g * stride on; four lanes read one
+  // place, 16 bytes each.
+  constexpr int kPlaces = kSample / kSampleRun, kLoads = kSample / (4 * kBlock);
+  const int64_t stride = (n / kPlaces) & ~(int64_t)3;
+  PoolSource::Raw raw[kLoads];
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    const int64_t i = (int64_t)(tid / 4 + j * (kBlock / 4)) * stride + (tid & 3) * 4;  // i + 3 < n: stride >= kSampleRun
+    raw[j].l = load_i32x4(src.len + i);
+    raw[j].a = load_f32x4(src.arrival + i);
+  }
+  if (tid < kStageThreads) {
+    PoolSource::Stage st;
+    src.stage_load(st, t);
+    src.stage_store(sh, st);
+  }
+  __syncthreads();
+  const auto km = src.key_mode(sh);
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    uint32_t key[4];
+    src.keys4(raw[j], sh, km, key);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = key[e] > m ? key[e] : m;
+  }
+  best[tid] = m;
+  __syncthreads();
+  if (tid < kWave) {
+    uint32_t key[kWavesPerBlock];
+#pragma unroll
+    for (int e = 0; e < kWavesPerBlock; ++e) key[e] = best[e * kWave + lane];
+    const uint32_t kth = wave_kth_of_1024(key, rank);
+    const float x = kth != 0u ? float_of_ukey(kth) : 0.0f;
+    if (tid == 0) tau[t] = x > 1e-30f && x < 1e30f ? x : 0.0f;  // finite, and no w / tau can overflow into doubt
+  }
+}
+
+constexpr int kBoundThreads = 256;
+__global__ __launch_bounds__(kBoundThreads) void theta_bound(const ewsjf_queue_table* __restrict__ tab,
+                                                             const ewsjf_theta* __restrict__ theta, int n_theta,
+                                                             FilterBufs fb) {
+  __shared__ float red[3][kBoundThreads / kWave];
+  const int q = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  if (q == 0 && tid == 0) *fb.count = 0;
+  if (q >= tab->k) return;  // uniform
+  const double mean = tab->mean[q];
+  float u[3] = {0.0f, 0.0f, 0.0f};
+  for (int t = tid; t < n_theta; t += kBoundThreads) {
+    const float x = fb.tau[t];
+    if (x > 0.0f) {
+      const QParams w = make_qparams(theta[t], mean, q);
+      const float inv = 1.0f / x;
+      const float r[3] = {w.wb * inv, w.wu * inv, w.wf2 * inv};
+#pragma unroll
+      for (int c = 0; c < 3; ++c) u[c] = fmaxf(u[c], r[c] + kFilterSlack * fabsf(r[c]));
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    for (int off = 32; off > 0; off >>= 1) u[c] = fmaxf(u[c], __shfl_xor(u[c], off));
+    if (lane == 0) red[c][wv] = u[c];
+  }
+  __syncthreads();
+  if (tid == 0) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      for (int i = 1; i < kBoundThreads / kWave; ++i) u[c] = fmaxf(u[c], red[c][i]);
+    fb.u[q] = f32x4{u[0], u[1], u[2], 0.0f};
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void pool_filter(PoolSource src, int64_t n, int G, FilterBufs fb) {
+  __shared__ uint64_t route[kRouteWords];
+  __shared__ f32x4 u[EWSJF_MAX_QUEUES];
+  __shared__ Survivor out[kFilterLds];
+  __shared__ int nout, base;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const int k = src.table->k, L = src.table->max_len;
+  {
+    const i32x4* lsrc = reinterpret_cast<const i32x4*>(src.table->route);
+    i32x4* ldst = reinterpret_cast<i32x4*>(route);
+    for (int i = tid; i < kRouteWords / 2; i += kBlock) ldst[i] = lsrc[i];
+    if (tid < k) u[tid] = fb.u[tid];
+  }
+  if (tid == 0) nout = 0;
+  __syncthreads();
+  for (int64_t lc0 = wv;; lc0 += kChunksPerPass * kWavesPerBlock) {
+    const int64_t c0 = (int64_t)blockIdx.x + (int64_t)G * lc0;
+    if (c0 >= nchunks) break;
+    PoolSource::Raw raw[kChunksPerPass];
+#pragma unroll
+    for (int j = 0; j < kChunksPerPass; ++j)  // chunks past the end read zeros
+      raw[j] = src.load_chunk(c0 + (int64_t)G * kWavesPerBlock * j, n, lane);
+#pragma unroll
+    for (int j = 0; j < kChunksPerPass; ++j) {
+      const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
+      if (first >= n) break;  // uniform
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int b = raw[j].l[e];
+        const float a = raw[j].a[e];
+        const PhiTerms x = phi_terms(b, a, src.now, src.cost);
+        const f32x4 w = u[route_queue(route, min(max(b, 1), L))];
+        const float bound = __builtin_fmaf(__builtin_fmaf(w.z, x.lg, w.x), x.al, w.y * x.be);
+        const bool p = b > 0 && !(bound < 1.0f - kFilterSlack);
+        const uint64_t sm = __ballot(p);
+        if (sm != 0ull) {
+          int at = 0;
+          if (lane == 0) at = atomicAdd(&nout, (int)__popcll(sm));
+          at = __builtin_amdgcn_readfirstlane(at) + lanes_below(sm);  // lane 0 (the whole wave is active)
+          if (p && at < kFilterLds) out[at] = Survivor{b, a, (int32_t)(first + 4 * lane + e)};
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int cnt = nout;
+  if (tid == 0 && cnt > 0) base = atomicAdd(fb.count, cnt <= kFilterLds ? cnt : fb.cap + 1);  // too many: over the cap
+  __syncthreads();
+  if (cnt <= kFilterLds)
+    for (int i = tid; i < cnt; i += kBlock)
+      if (base + i < fb.cap) fb.list[base + i] = out[i];
+}
+
+__global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, FilterBufs fb, int32_t* __restrict__ ids,
+                                                       float* __restrict__ top, int32_t* __restrict__ n_sel) {
+  __shared__ MergeShared ms;
+  __shared__ PoolSource::Shared sh;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), t = blockIdx.x;
+  const int S = *fb.count;
+  const float tau = fb.tau[t];
+  if (S < B || S > fb.cap || tau == 0.0f) {  // uniform
+    if (tid == 0) n_sel[t] = -1;
+    return;
+  }
+  if (tid < kStageThreads) {
+    PoolSource::Stage st;
+    src.stage_load(st, t);
+    src.stage_store(sh, st);
+  }
+  if (tid == 0) ms.cntX = 0;
+  __syncthreads();
+  const uint32_t low = ukey_of(tau);
+  const int L = __builtin_amdgcn_readfirstlane(sh.L);
+  for (int i0 = 0; i0 < S; i0 += kBlock) {
+    const int i = i0 + tid;
+    const Survivor s = fb.list[min(i, S - 1)];
+    const uint32_t key = src.key1<false, false>(s.len, s.arrival, sh, L);
+    const bool p = i < S && key >= low;
+    const uint64_t sm = __ballot(p);
+    if (sm != 0ull) {
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&ms.cntX, (int)__popcll(sm));
+      at = __builtin_amdgcn_readfirstlane(at) + lanes_below(sm);  // lane 0 (the whole wave is active)
+      if (p && at < kMergeCap) ms.X[at] = make_comp(key, (uint32_t)s.id);
+    }
+  }
+  __syncthreads();
+  const int U = ms.cntX;
+  if (U < B || U > kMergeCap) {  // uniform
+    if (tid == 0) n_sel[t] = -1;
+    return;
+  }
+  select_top(ms, U, B);
+  for (int r = tid; r < B; r += kBlock) {
+    const uint64_t x = ms.X[r];
+    ids[(size_t)t * B + r] = (int32_t)comp_id(x);
+    top[(size_t)t * B + r] = float_of_ukey((uint32_t)(x >> 32));
+  }
+  if (tid == 0) n_sel[t] = B;
 }
 
 // LDS of the exact merge.
@@ -1530,8 +1797,9 @@ __device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int
 template <class Src>
 __global__ __launch_bounds__(kBlock) void merge_candidates(Src src0, int64_t n, int G, int M, int B, CandBufs cb,
                                                            int32_t* __restrict__ ids, float* __restrict__ top,
-                                                           int32_t* __restrict__ n_sel, int32_t* tomb_len) {
+                                                           int32_t* n_sel, int32_t* tomb_len, const int32_t* only) {
   __shared__ MergeLds<Src> lds;
+  if (only != nullptr && only[blockIdx.x] >= 0) return;  // uniform; only may be n_sel (each row reads its own entry first)
   merge_exact(src0, (int)blockIdx.x, n, G, M, B, cb, ids, top, n_sel, tomb_len, lds);
 }
 
@@ -1788,8 +2056,58 @@ static bool step_packed(int64_t n, int32_t n_theta) {
   return n_theta > 1 && nchunks <= (int64_t)kMaxGrid * kWavesPerBlock * kChunksPerPass;
 }
 
+// The sample's rank for the filtered many-vector step, or 0 where the plain
+// kernels run.
+//  - The rank: the mean number of the B in the sample (about a Poisson count),
+//    four standard deviations and a few more, so that the threshold lies above
+//    the B-th score about once in a million steps (then, as for every other
+//    reason, the plain kernels answer).  It must leave room below the 1,024
+//    lane maxima it is taken from.
+//  - The requests at or above the threshold: a lane maximum of 8 requests is
+//    at or above it with probability rank / 1,024, a request with
+//    1 - (1 - rank / 1,024)^(1/8).  They must fit theta_select's list, and
+//    three times as many the survivors' room.
+//  - Six launches against two, and one read of the pool either way: measured
+//    (us a step, B = 128, filtered / plain) 26 / 71 at 131,072 requests and 2
+//    vectors, 26 / 36 at 262,144 and 2, 28 / 21 at 524,288 and 2, 31 / 29 at 1M
+//    and 4, 31 / 37 at 1M and 6, 41 / 34 at 4M and 4, 41 / 42 at 4M and 6.
+struct FilterPlan {
+  int rank = 0;         // 0: not filtered
+  size_t head = 0;      // bytes before the survivors
+  size_t ws_bytes = 0;  // workspace it needs
+};
+static FilterPlan filter_plan(int64_t n, int32_t n_theta, int32_t B) {
+  FilterPlan f;
+  if (n_theta < 2 || n < kSample || (n_theta < 6 && n > kFilterFewMax) || !step_packed(n, n_theta)) return f;
+  const double share = (double)B * kSample / (double)n;
+  const int rank = (int)std::ceil(share + 4.0 * std::sqrt(share) + 8.0);
+  if (rank > kSampleMaxRank) return f;
+  const double above = (double)n * -std::expm1(std::log1p(-(double)rank / kBlock) / (kSample / kBlock));
+  if (1.25 * above > kMergeCap) return f;
+  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  f.rank = rank;
+  f.head = 256 + up((size_t)n_theta * sizeof(float)) + EWSJF_MAX_QUEUES * sizeof(f32x4);
+  f.ws_bytes = f.head + up((size_t)(3.0 * above) * sizeof(Survivor));
+  return f;
+}
+
+static FilterBufs carve_filter(const FilterPlan& f, int32_t n_theta, size_t ws_bytes, void* ws) {
+  char* b = static_cast<char*>(ws);
+  FilterBufs fb;
+  fb.count = reinterpret_cast<int32_t*>(b);
+  fb.tau = reinterpret_cast<float*>(b + 256);
+  fb.u = reinterpret_cast<f32x4*>(b + f.head - EWSJF_MAX_QUEUES * sizeof(f32x4));
+  fb.list = reinterpret_cast<Survivor*>(b + f.head);
+  const size_t room = (ws_bytes - f.head) / sizeof(Survivor);
+  fb.cap = room < (size_t)kFilterMax ? (int)room : kFilterMax;
+  return fb;
+}
+
 SelectPlan plan_step(int64_t n, int32_t n_theta, int32_t B) {
-  return plan_select(n, n_theta, B, step_packed(n, n_theta));
+  SelectPlan p = plan_select(n, n_theta, B, step_packed(n, n_theta));
+  const FilterPlan f = filter_plan(n, n_theta, B);  // few vectors over a small pool: little else to hold
+  if (f.ws_bytes > p.ws_bytes) p.ws_bytes = f.ws_bytes;
+  return p;
 }
 
 // Trials: each pool gets the workgroups that give every wave one full pass
@@ -1815,10 +2133,33 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
   src.now = now;
   src.cost = CostF{(float)cost.c0, (float)cost.c1, (float)cost.c2};
   const dim3 multi_grid(p.G, (n_theta + kThetaPerBlock - 1) / kThetaPerBlock);
+  const FilterPlan f = filter_plan(n, n_theta, B);
+  if (f.rank > 0) {
+    const FilterBufs fb = carve_filter(f, n_theta, plan_step(n, n_theta, B).ws_bytes, ws);
+    const int64_t nchunks = (n + kChunk - 1) / kChunk;
+    const int64_t wgs = (nchunks + kWavesPerBlock - 1) / kWavesPerBlock;
+    const int fg = wgs < kMaxGrid ? (int)wgs : kMaxGrid;
+    hipLaunchKernelGGL(theta_threshold, dim3(n_theta), dim3(kBlock), 0, stream, src, n, f.rank, fb.tau);
+    hipLaunchKernelGGL(theta_bound, dim3(EWSJF_MAX_QUEUES), dim3(kBoundThreads), 0, stream, table, theta, n_theta,
+                       fb);
+    if (marks == nullptr) {
+      hipLaunchKernelGGL(pool_filter, dim3(fg), dim3(kBlock), 0, stream, src, n, fg, fb);
+      hipLaunchKernelGGL(theta_select, dim3(n_theta), dim3(kBlock), 0, stream, src, B, fb, ids, top, n_sel);
+    } else {
+      hipExtLaunchKernelGGL(pool_filter, dim3(fg), dim3(kBlock), 0, stream, marks[0], marks[1], 0, src, n, fg, fb);
+      hipExtLaunchKernelGGL(theta_select, dim3(n_theta), dim3(kBlock), 0, stream, marks[2], marks[3], 0, src, B, fb,
+                            ids, top, n_sel);
+    }
+    hipLaunchKernelGGL(local_candidates_multi, multi_grid, dim3(kBlock), 0, stream, src, n, n_theta, p.G, p.lg, p.M,
+                       cb, n_sel);
+    hipLaunchKernelGGL(merge_candidates<PoolSource>, dim3(n_theta), dim3(kBlock), 0, stream, src, n, p.G, p.M, B, cb,
+                       ids, top, n_sel, tomb_len, n_sel);
+    return hipGetLastError();
+  }
   if (marks == nullptr) {
     if (packed)
       hipLaunchKernelGGL(local_candidates_multi, multi_grid, dim3(kBlock), 0, stream, src, n, n_theta, p.G, p.lg,
-                         p.M, cb);
+                         p.M, cb, nullptr);
     else
       hipLaunchKernelGGL(local_candidates<PoolSource>, dim3(p.G, n_theta), dim3(kBlock), 0, stream, src, n, p.G,
                          p.lg, p.M, cb);
@@ -1828,14 +2169,14 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
       launch_merge_rank(p, stream, nullptr, nullptr, src, n, B, cb, ids, top, n_sel, tomb_len);
     else
       hipLaunchKernelGGL(merge_candidates<PoolSource>, dim3(n_theta), dim3(kBlock), 0, stream, src, n, p.G, p.M,
-                         B, cb, ids, top, n_sel, tomb_len);
+                         B, cb, ids, top, n_sel, tomb_len, nullptr);
     return hipGetLastError();
   }
   // The events take the start and end timestamps of each kernel's own
   // dispatch.
   if (packed)
     hipExtLaunchKernelGGL(local_candidates_multi, multi_grid, dim3(kBlock), 0, stream, marks[0], marks[1], 0, src, n,
-                          n_theta, p.G, p.lg, p.M, cb);
+                          n_theta, p.G, p.lg, p.M, cb, nullptr);
   else
     hipExtLaunchKernelGGL(local_candidates<PoolSource>, dim3(p.G, n_theta), dim3(kBlock), 0, stream, marks[0],
                           marks[1], 0, src, n, p.G, p.lg, p.M, cb);
@@ -1845,7 +2186,7 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
     launch_merge_rank(p, stream, marks[2], marks[3], src, n, B, cb, ids, top, n_sel, tomb_len);
   else
     hipExtLaunchKernelGGL(merge_candidates<PoolSource>, dim3(n_theta), dim3(kBlock), 0, stream, marks[2], marks[3],
-                          0, src, n, p.G, p.M, B, cb, ids, top, n_sel, tomb_len);
+                          0, src, n, p.G, p.M, B, cb, ids, top, n_sel, tomb_len, nullptr);
   return hipGetLastError();
 }
 
@@ -1910,7 +2251,7 @@ hipError_t launch_trial_select(int32_t* len, float* arrival, int64_t capacity, i
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_candidates<TrialSource>, dim3(n_pools), dim3(kBlock), 0, stream, src, capacity, p.G, p.M,
-                     B, cb, ids, top, n_sel, nullptr);
+                     B, cb, ids, top, n_sel, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -1929,7 +2270,7 @@ hipError_t launch_fifo_select(const int32_t* len, const float* arrival, int64_t 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_candidates<FifoSource>, dim3(kTacticalRows), dim3(kBlock), 0, stream, src, n, p.G, p.M,
-                     B, cb, ids, top, n_sel, nullptr);
+                     B, cb, ids, top, n_sel, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -1948,7 +2289,7 @@ hipError_t launch_select(const float* score, int64_t n, int32_t n_theta, int32_t
     launch_merge_rank(p, stream, nullptr, nullptr, src, n, B, cb, ids, top, n_sel, nullptr);
   else
     hipLaunchKernelGGL(merge_candidates<ScoreSource>, dim3(n_theta), dim3(kBlock), 0, stream, src, n, p.G, p.M,
-                       B, cb, ids, top, n_sel, nullptr);
+                       B, cb, ids, top, n_sel, nullptr, nullptr);
   return hipGetLastError();
 }
 
