@@ -457,6 +457,7 @@ struct ListShared {
   int iscan[kWavesPerBlock];
   int rank[kShortList];  // ranks of a short list, summed over the waves
   uint32_t bar[kWavesPerBlock];
+  uint32_t thr[kWavesPerBlock];  // local_stream: the threshold each wave has listed down to
   int wcnt[kWavesPerBlock];
   int wkeep[kWavesPerBlock];
   int ovf;
@@ -627,6 +628,76 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
   for (int o = 1; o < tpe; o <<= 1) rank += (int)xor_lane_u32_dyn((uint32_t)rank, o);
   if (e < cnt && part == 0) place(x, rank);
   if (threadIdx.x == 0) cb.over_cnt[slot] = (uint32_t)(listed - M);
+}
+
+// The closing of a workgroup's list (every wave's region holds every element
+// of the wave at or above its bar): the bound, the entries at or above it in
+// list2, and the publication.  bar_l: wave (lane mod 16)'s bar; reg_l: this
+// wave's region entry `lane` (valid below wcnt).  kKeys && keys_held: key holds
+// all keys of the share (a single pass).
+template <bool kKeys>
+__device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, bool keys_held, int wcnt, uint32_t bar_l,
+                                           uint64_t reg_l, int G, int M, size_t slot, const CandBufs& cb) {
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  // The workgroup's bound would be the largest wave bar t1 (lane i < 16
+  // reads wave i's).  One wave holding a few high keys in each of its lane
+  // groups sets t1 alone, and t1 can then exceed the B-th key of the whole
+  // pool, which sends the merge back to the share.  So in a single pass
+  // (the keys are still in registers) the wave holding t1 also lists its
+  // keys in [t2, t1), t2 the second largest bar, and the bound drops to t2.
+  // Each wave keeps its entries at or above the bound; a scan of the kept
+  // counts over the waves places them in list2.
+  const uint32_t b = lane < kWavesPerBlock ? bar_l : 0u;
+  const uint32_t t1 = wave_max_u32(b);
+  const int v1 = (int)__builtin_ctzll(__ballot(lane < kWavesPerBlock && b == t1));
+  const uint32_t t2 = wave_max_u32(lane != v1 ? b : 0u);
+  const bool lower = kKeys && keys_held && t2 != 0u && t2 < t1;  // uniform
+  const uint32_t T_bar = lower ? t2 : t1;
+  const uint64_t lowc = (uint64_t)T_bar << 32;
+  const uint64_t x = lane < wcnt ? reg_l : 0ull;
+  const bool keep = x >= lowc && x != 0ull;
+  const uint64_t km = __ballot(keep);
+  if (lane == 0) ls.wkeep[wv] = __popcll(km);
+  // The wave holding t1 hands its keys to the workgroup (key e of lane l
+  // at e * kWave + l); after the barrier wave w filters keys e = w, so the
+  // extra keys cost every wave a few instructions rather than one wave a
+  // long serial run.
+  uint32_t* const held = reinterpret_cast<uint32_t*>(ls.spill);
+  static_assert(kElemsPerLane == kWavesPerBlock && kElemsPerLane * kWave * 4 <= sizeof(ls.spill),
+                "one handed-over key per wave and lane");
+  if (lower && wv == v1) {  // uniform
+#pragma unroll
+    for (int e = 0; e < kElemsPerLane; ++e) held[e * kWave + lane] = key[e];
+  }
+  __syncthreads();
+  const int kc = lane < kWavesPerBlock ? ls.wkeep[lane] : 0;
+  const int incl = wave_incl_scan_add(kc);
+  const int nreg = __builtin_amdgcn_readlane(incl, kWavesPerBlock - 1);
+  const int off = __builtin_amdgcn_readlane(incl - kc, wv);
+  if (keep) ls.list2[off + lanes_below(km)] = x;  // nreg <= kListCap: at most kWave per wave
+  if (lower) {  // uniform
+    // Keys of wave v1 in [t2, t1) go after the regions' entries, in any
+    // order (the list is ranked by value when published).
+    const uint32_t k = held[wv * kWave + lane];
+    const bool p = k >= t2 && k < t1;
+    const uint64_t sm = __ballot(p);
+    if (sm != 0ull) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&ls.nout, __popcll(sm));
+      base = __builtin_amdgcn_readfirstlane(base);  // lane 0 (the whole wave is active)
+      const int at = nreg + base + lanes_below(sm);
+      // the chunk that element e = wv of wave v1 came from (single pass)
+      const int64_t c = (int64_t)blockIdx.x + (int64_t)G * (v1 + kWavesPerBlock * (wv / 4));
+      if (p && at < kListCap) ls.list2[at] = make_comp(k, (uint32_t)(c * kChunk + lane * 4 + (wv & 3)));
+    }
+  }
+  __syncthreads();
+  // more than kListCap entries only with many extra keys: publish_list
+  // then marks the list incomplete
+  const int total = nreg + (lower ? ls.nout : 0);
+  EWSJF_STAMP(kStampLocal, 4);
+  EWSJF_STAMP_VALUE(kStampLocal, 6, total);
+  publish_list<false>(ls, total, lowc, M, slot, cb);
 }
 
 // Chunks each wave has in flight when it starts scoring (2, 3 or 4).
@@ -863,65 +934,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
     return;
   }
   if constexpr (!Src::kClustered) {
-    // The workgroup's bound would be the largest wave bar t1 (lane i < 16
-    // reads wave i's).  One wave holding a few high keys in each of its lane
-    // groups sets t1 alone, and t1 can then exceed the B-th key of the whole
-    // pool, which sends the merge back to the share.  So in a single pass
-    // (the keys are still in registers) the wave holding t1 also lists its
-    // keys in [t2, t1), t2 the second largest bar, and the bound drops to t2.
-    // Each wave keeps its entries at or above the bound; a scan of the kept
-    // counts over the waves places them in list2.
-    const uint32_t b = lane < kWavesPerBlock ? bar_l : 0u;
-    const uint32_t t1 = wave_max_u32(b);
-    const int v1 = (int)__builtin_ctzll(__ballot(lane < kWavesPerBlock && b == t1));
-    const uint32_t t2 = wave_max_u32(lane != v1 ? b : 0u);
-    const bool lower = passes == 1 && t2 != 0u && t2 < t1;  // uniform
-    const uint32_t T_bar = lower ? t2 : t1;
-    const uint64_t lowc = (uint64_t)T_bar << 32;
-    const uint64_t x = lane < wcnt ? reg_l : 0ull;
-    const bool keep = x >= lowc && x != 0ull;
-    const uint64_t km = __ballot(keep);
-    if (lane == 0) ls.wkeep[wv] = __popcll(km);
-    // The wave holding t1 hands its keys to the workgroup (key e of lane l
-    // at e * kWave + l); after the barrier wave w filters keys e = w, so the
-    // extra keys cost every wave a few instructions rather than one wave a
-    // long serial run.
-    uint32_t* const held = reinterpret_cast<uint32_t*>(ls.spill);
-    static_assert(kElemsPerLane == kWavesPerBlock && kElemsPerLane * kWave * 4 <= sizeof(ls.spill),
-                  "one handed-over key per wave and lane");
-    if (lower && wv == v1) {  // uniform
-#pragma unroll
-      for (int e = 0; e < kElemsPerLane; ++e) held[e * kWave + lane] = key[e];
-    }
-    __syncthreads();
-    const int kc = lane < kWavesPerBlock ? ls.wkeep[lane] : 0;
-    const int incl = wave_incl_scan_add(kc);
-    const int nreg = __builtin_amdgcn_readlane(incl, kWavesPerBlock - 1);
-    const int off = __builtin_amdgcn_readlane(incl - kc, wv);
-    if (keep) ls.list2[off + lanes_below(km)] = x;  // nreg <= kListCap: at most kWave per wave
-    if (lower) {  // uniform
-      // Keys of wave v1 in [t2, t1) go after the regions' entries, in any
-      // order (the list is ranked by value when published).
-      const uint32_t k = held[wv * kWave + lane];
-      const bool p = k >= t2 && k < t1;
-      const uint64_t sm = __ballot(p);
-      if (sm != 0ull) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&ls.nout, __popcll(sm));
-        base = __builtin_amdgcn_readfirstlane(base);  // lane 0 (the whole wave is active)
-        const int at = nreg + base + lanes_below(sm);
-        // the chunk that element e = wv of wave v1 came from (single pass)
-        const int64_t c = (int64_t)blockIdx.x + (int64_t)G * (v1 + kWavesPerBlock * (wv / 4));
-        if (p && at < kListCap) ls.list2[at] = make_comp(k, (uint32_t)(c * kChunk + lane * 4 + (wv & 3)));
-      }
-    }
-    __syncthreads();
-    // more than kListCap entries only with many extra keys: publish_list
-    // then marks the list incomplete
-    const int total = nreg + (lower ? ls.nout : 0);
-    EWSJF_STAMP(kStampLocal, 4);
-    EWSJF_STAMP_VALUE(kStampLocal, 6, total);
-    publish_list<false>(ls, total, lowc, M, slot, cb);
+    close_list<true>(ls, key, passes == 1, wcnt, bar_l, reg_l, G, M, slot, cb);
     EWSJF_STAMP(kStampLocal, 5);
     EWSJF_STAMP_FLUSH(kStampLocal);
     return;
@@ -996,6 +1009,204 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
   EWSJF_STAMP_FLUSH(kStampLocal);
 }
 
+
+// ---------------------------------------------------------------------------
+// local_candidates for shares of more than one pass (pools beyond 4M requests
+// per row), for the sources whose high keys do not cluster.  The same lists
+// and bounds, but a wave walks its chunks one after the other with kFlight of
+// them in flight, and after the first chunks there is no workgroup barrier on
+// the way: waves tell each other their bars through LDS.  A wave's bar comes
+// from the lane maxima of all its keys so far; it lists down to the second
+// largest bar of the workgroup (the largest alone could lie above the pool's
+// B-th key, see close_list).  Bars only grow and any value of them is a valid
+// threshold, so a late or early read changes how much is listed, never whether
+// the list is complete: the bound is the largest threshold any wave used.  A
+// full region raises the wave's threshold to its 32nd largest key.
+//
+// Bound by HBM, the scoring (about 640 VALU instructions per wave and four
+// chunks) and, before, by the lists: bars from three chunks per pass, the
+// largest of them the bound, left about 360 entries to rank at 9.4M requests
+// and B = 1,500 (38 us; 21 us now, 3.6 TB/s).
+// ---------------------------------------------------------------------------
+constexpr int kFlight = 4;
+
+__device__ __forceinline__ uint32_t lds_peek(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_poke(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The k-th largest of the wave's N x 64 keys (0 when fewer are nonzero).
+template <int N>
+__device__ __forceinline__ uint32_t wave_kth_of(const uint32_t* key, int k) {
+  uint32_t prefix = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = prefix | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) c += (int)__popcll(__ballot(key[e] >= cand));
+    if (c >= k) prefix = cand;
+  }
+  return prefix;
+}
+
+template <class Src>
+__global__ __launch_bounds__(kBlock) void local_stream(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
+  static_assert(!Src::kClustered, "clustered sources use local_candidates");
+  __shared__ typename Src::Shared sh;
+  __shared__ ListShared ls;
+  const int t = blockIdx.y;
+  const Src src = bind_theta(src0, t);
+  const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const int64_t my_chunks = nchunks > blockIdx.x ? (nchunks - blockIdx.x + G - 1) / G : 0;
+  const int mine = (int)((my_chunks - wv + kWavesPerBlock - 1) / kWavesPerBlock);  // this wave's chunks (uniform)
+  auto chunk_at = [&](int i) { return (int64_t)blockIdx.x + (int64_t)G * (wv + (int64_t)kWavesPerBlock * i); };
+
+  const bool stager = wv < kStageWaves;
+  typename Src::Stage st;
+  if (stager) src.stage_load(st, t);
+  __builtin_amdgcn_s_barrier();  // the table's loads ahead of every pool load
+  typename Src::Raw raw[kFlight];
+#pragma unroll
+  for (int j = 0; j < kFlight; ++j) raw[j] = src.load_chunk(chunk_at(j), n, lane);  // past the end: zeros
+  if (stager) src.stage_store(sh, st);
+  if (threadIdx.x == 0) {
+    ls.ovf = 0;
+    ls.nout = 0;
+  }
+  if (threadIdx.x < kWavesPerBlock) ls.bar[threadIdx.x] = 0u;
+  if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
+  __syncthreads();
+  const auto km = src.key_mode(sh);
+
+  uint64_t* const region = ls.list + wv * kWaveCap;
+  uint32_t my_bar = 0;  // this wave's threshold: every key at or above it is listed
+  int wcnt = 0;
+  bool wovf = false;
+  uint32_t lmax = 0;  // the lane's largest key so far
+  // The second largest bar of the workgroup, as far as the waves have told.
+  auto second_bar = [&]() {
+    const uint32_t b = lane < kWavesPerBlock ? lds_peek(&ls.bar[lane & (kWavesPerBlock - 1)]) : 0u;
+    const int top = (int)__builtin_ctzll(__ballot(b == wave_max_u32(b)));
+    return wave_max_u32(lane != top ? b : 0u);
+  };
+  // Entries below the bar leave the region.
+  auto compact = [&]() {
+    const uint64_t x = lane < wcnt ? region[lane] : 0ull;
+    const bool keep = (uint32_t)(x >> 32) >= my_bar && x != 0ull;
+    const uint64_t m = __ballot(keep);
+    if (keep) region[lanes_below(m)] = x;
+    wcnt = (int)__popcll(m);
+  };
+  auto emit = [&](const uint32_t key[4], int64_t c) {
+    const uint32_t thr = my_bar > 1u ? my_bar : 1u;
+    uint64_t m[4];
+    int hits = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      m[e] = __ballot(key[e] >= thr);
+      hits += (int)__popcll(m[e]);
+    }
+    if (hits == 0) return;
+    if (wcnt + hits > kWaveCap) {
+      // The 32nd largest of the region and this chunk becomes the bar (one
+      // above it if equal keys would still not fit).
+      uint32_t k5[5] = {key[0], key[1], key[2], key[3], lane < wcnt ? (uint32_t)(region[lane] >> 32) : 0u};
+      const uint32_t kth = wave_kth_of<5>(k5, kWaveCap / 2);
+      int c2 = 0;
+#pragma unroll
+      for (int e = 0; e < 5; ++e) c2 += (int)__popcll(__ballot(k5[e] >= kth));
+      if (c2 <= kWaveCap) {
+        my_bar = kth > my_bar ? kth : my_bar;
+      } else if (kth != 0xFFFFFFFFu) {
+        my_bar = kth + 1u;
+      } else {
+        wovf = true;  // that many keys of the largest value: the list cannot hold them
+      }
+      compact();
+      const uint32_t thr2 = my_bar > 1u ? my_bar : 1u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = __ballot(key[e] >= thr2);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (m[e] != 0ull) {
+        const int pos = wcnt + lanes_below(m[e]);
+        if (((m[e] >> lane) & 1ull) && pos < kWaveCap)
+          region[pos] = make_comp(key[e], (uint32_t)(c * kChunk + lane * 4 + e));
+        wcnt += (int)__popcll(m[e]);
+      }
+    }
+    if (wcnt > kWaveCap) {
+      wovf = true;
+      wcnt = kWaveCap;
+    }
+  };
+
+  {
+    uint32_t key[kFlight][4];
+#pragma unroll
+    for (int j = 0; j < kFlight; ++j) {
+      src.keys4(raw[j], sh, km, key[j]);
+      if (j + kFlight < mine) raw[j] = src.load_chunk(chunk_at(j + kFlight), n, lane);
+    }
+#pragma unroll
+    for (int j = 0; j < kFlight; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lmax = key[j][e] > lmax ? key[j][e] : lmax;
+    const uint32_t bar = wave_group_bar(lmax, lg);
+    if (lane == 0) lds_poke(&ls.bar[wv], bar);
+    __syncthreads();
+    my_bar = second_bar();
+#pragma unroll
+    for (int j = 0; j < kFlight; ++j) emit(key[j], chunk_at(j));
+  }
+  for (int i0 = kFlight; i0 < mine; i0 += kFlight) {
+    const uint32_t bar = second_bar();
+    if (bar > my_bar) {
+      my_bar = bar;
+      compact();
+    }
+#pragma unroll
+    for (int j = 0; j < kFlight; ++j) {
+      if (i0 + j < mine) {  // uniform
+        uint32_t key[4];
+        src.keys4(raw[j], sh, km, key);
+        if (i0 + j + kFlight < mine) raw[j] = src.load_chunk(chunk_at(i0 + j + kFlight), n, lane);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lmax = key[e] > lmax ? key[e] : lmax;
+        emit(key, chunk_at(i0 + j));
+      }
+    }
+    const uint32_t grown = wave_group_bar(lmax, lg);
+    if (lane == 0) lds_poke(&ls.bar[wv], grown);
+  }
+  if (lane == 0) {
+    ls.thr[wv] = my_bar;
+    ls.wcnt[wv] = wcnt;
+    if (wovf) ls.ovf = 1;
+  }
+  __syncthreads();
+  const size_t slot = (size_t)t * G + blockIdx.x;
+  // The bound: the largest threshold, or the second largest final bar where
+  // that is higher.
+  const uint32_t final_bar = second_bar(), used = ls.thr[lane & (kWavesPerBlock - 1)];
+  const uint32_t bar_l = used > final_bar ? used : final_bar;
+  const uint64_t reg_l = region[lane];
+  if (ls.ovf != 0) {
+    for (int i = threadIdx.x; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
+    if (threadIdx.x == 0) {
+      cb.counts[slot] = 0u;
+      cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
+      cb.bounds2[slot] = ~0ull;
+      cb.over_cnt[slot] = 0u;
+    }
+    return;
+  }
+  close_list<false>(ls, nullptr, false, wcnt, bar_l, reg_l, G, M, slot, cb);
+}
 
 // ---------------------------------------------------------------------------
 // Many parameter vectors over one pool (ewsjf_step with n_theta > 1).  Each
@@ -1810,7 +2021,7 @@ __global__ __launch_bounds__(kBlock) void merge_candidates(Src src0, int64_t n, 
 // and an entry's output position is the number of larger entries.  That
 // holds when the largest bound T satisfies T <= 1 (every share listed all of
 // its elements) or at least B entries are >= T.  Each workgroup ranks
-// kRankPer own slots against all G x M slots, counting with wave ballots,
+// its own slots against all G x M slots, counting with wave ballots,
 // and writes the entries of rank < B to their positions; no workgroup waits
 // for another.  Only own slots at or above T are ranked (below T an entry
 // has at least B entries above it), all in one pass; correctness needs no
@@ -1819,26 +2030,31 @@ __global__ __launch_bounds__(kBlock) void merge_candidates(Src src0, int64_t n, 
 // and the others leave.  Every workgroup reaches the same decision from the
 // same slots and bounds.
 // ---------------------------------------------------------------------------
-constexpr int kRankPer = 16;
+// Own slots per workgroup: 16 up to 4,096 slots in all, so that the workgroups
+// fill the chip; 32 above, because the exact merge's LDS admits one workgroup
+// per compute unit and 16 own slots each would take two rounds of them
+// (8,192 slots: 12.0 us, 7.4 us with 32).
+constexpr int kRankPer = 16, kRankPerMany = 32;
 constexpr int kRankR = (kMergeCap + kBlock - 1) / kBlock;  // most slots per thread
 
-// NR: slots per thread, a compile-time bound >= ceil(G M / kBlock).
-template <class Src, int NR>
+// NR: slots per thread, a compile-time bound >= ceil(G M / kBlock).  PER: own
+// slots per workgroup.
+template <class Src, int NR, int PER>
 __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, int M, int B, CandBufs cb,
                                                      int32_t* __restrict__ ids, float* __restrict__ top,
                                                      int32_t* __restrict__ n_sel, int32_t* tomb_len) {
   __shared__ MergeLds<Src> lds;
-  __shared__ uint64_t s_c[kRankPer];
+  __shared__ uint64_t s_c[PER];
   // per-wave partials, each reduced by every wave itself (no LDS atomics and
   // no barrier to clear them first): largest bound, nonzero slots, slots >= T
   __shared__ uint64_t s_wT[kWavesPerBlock];
   __shared__ int s_wnz[kWavesPerBlock], s_wge[kWavesPerBlock];
-  __shared__ int s_rank[kRankPer];
+  __shared__ int s_rank[PER];
   EWSJF_STAMP(kStampMergeRank, 0);
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   const bool pl = lane < kWavesPerBlock;  // lane i reads wave i's partial
   const int GM = G * M;
-  const int p0 = (int)blockIdx.x * kRankPer;
+  const int p0 = (int)blockIdx.x * PER;
 
   // One round trip: the slots (slot tid + r kBlock in v[r]; past GM reads 0),
   // the bounds and this workgroup's own slots.
@@ -1850,18 +2066,18 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
     v[r] = ((uint64_t)w[1] << 32) | w[0];
   }
   const uint64_t bnd = tid < G ? cb.bounds[tid] : 0ull;
-  // Own slots: with M = kRankPer and G a multiple of it, workgroup w takes
+  // Own slots: with M = PER and G a multiple of it, workgroup w takes
   // entry k of list 16 (w / 16) + (w + k) % 16, one entry of each rank from
   // 16 lists (a bijection on each group of 16 lists).  Lists hold their
   // entries by rank, so every workgroup gets a similar number of slots at or
   // above T to count, rather than all of one list's.
   int os = p0 + tid;
-  if (M == kRankPer && (G & (kRankPer - 1)) == 0) {
+  if (M == PER && (G & (PER - 1)) == 0) {
     const int w = (int)blockIdx.x;
-    os = ((w & ~(kRankPer - 1)) | ((w + tid) & (kRankPer - 1))) * M + tid;
+    os = ((w & ~(PER - 1)) | ((w + tid) & (PER - 1))) * M + tid;
   }
-  const uint64_t own = tid < kRankPer && os < GM ? cb.lists[os] : 0ull;
-  if (tid < kRankPer) {
+  const uint64_t own = tid < PER && os < GM ? cb.lists[os] : 0ull;
+  if (tid < PER) {
     s_c[tid] = own;
     s_rank[tid] = 0;
   }
@@ -1883,9 +2099,9 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
   // This wave's count of slots larger than own slot p (wave-uniform: ballots
   // counted on the scalar unit, beside the compares on the vector unit),
   // summed over the waves in LDS.
-  uint64_t c[kRankPer];
+  uint64_t c[PER];
 #pragma unroll
-  for (int p = 0; p < kRankPer; ++p) c[p] = s_c[p];
+  for (int p = 0; p < PER; ++p) c[p] = s_c[p];
   // When the merge is safe (below), an entry under T has at least B entries
   // above it, so own slots under T are not ranked (and not written); when it
   // is not, no count is used.
@@ -1895,7 +2111,7 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
     // p (few own slots reach T).
     int mine = 0;
 #pragma unroll
-    for (int p = 0; p < kRankPer; ++p) {
+    for (int p = 0; p < PER; ++p) {
       if (c[p] > below_T) {  // uniform
         int cnt = 0;
 #pragma unroll
@@ -1903,7 +2119,7 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
         mine = lane == p ? cnt : mine;
       }
     }
-    if (lane < kRankPer && mine != 0) atomicAdd(&s_rank[lane], mine);
+    if (lane < PER && mine != 0) atomicAdd(&s_rank[lane], mine);
   }
   __syncthreads();
   EWSJF_STAMP(kStampMergeRank, 2);
@@ -1920,7 +2136,7 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
   EWSJF_STAMP(kStampMergeRank, 3);
   const int nnz = (int)__ockl_wfred_add_u32(pl ? (uint32_t)s_wnz[lane] : 0u);
   const int sel = nnz < B ? nnz : B;
-  if (tid < kRankPer) {
+  if (tid < PER) {
     const uint64_t x = s_c[tid];
     const int rank = s_rank[tid];
     if (x > out_bar && rank < B) {
@@ -1942,13 +2158,33 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
   EWSJF_STAMP_FLUSH(kStampMergeRank);
 }
 
+// Launches the streaming kernel of a source whose high keys do not cluster:
+// one pass per workgroup when its share fits (kept keys let it lower its
+// bound), else local_stream.
+template <class Src>
+static void launch_local(const SelectPlan& p, int rows, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const Src& src,
+                         int64_t n, const CandBufs& cb) {
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const bool one_pass = (nchunks + p.G - 1) / p.G <= kWavesPerBlock * kChunksPerPass;
+  const dim3 grid(p.G, rows), block(kBlock);
+  auto go = [&](auto kern) {
+    if (e0 != nullptr)
+      hipExtLaunchKernelGGL(kern, grid, block, 0, stream, e0, e1, 0, src, n, p.G, p.lg, p.M, cb);
+    else
+      hipLaunchKernelGGL(kern, grid, block, 0, stream, src, n, p.G, p.lg, p.M, cb);
+  };
+  if (one_pass) go(local_candidates<Src>);
+  else go(local_stream<Src>);
+}
+
 // Launches merge_rank with the smallest compiled slots-per-thread bound.
 template <class Src>
 static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const Src& src,
                               int64_t n, int B, const CandBufs& cb, int32_t* ids, float* top, int32_t* n_sel,
                               int32_t* tomb_len) {
   const int nr = (p.G * p.M + kBlock - 1) / kBlock;
-  const dim3 grid((p.G * p.M + kRankPer - 1) / kRankPer), block(kBlock);
+  const int per = nr <= 4 ? kRankPer : kRankPerMany;
+  const dim3 grid((p.G * p.M + per - 1) / per), block(kBlock);
   auto go = [&](auto kern) {
     if (e0 != nullptr)
       hipExtLaunchKernelGGL(kern, grid, block, 0, stream, e0, e1, 0, src, n, p.G, p.M, B, cb, ids, top, n_sel,
@@ -1956,10 +2192,11 @@ static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_
     else
       hipLaunchKernelGGL(kern, grid, block, 0, stream, src, n, p.G, p.M, B, cb, ids, top, n_sel, tomb_len);
   };
-  if (nr <= 1) go(merge_rank<Src, 1>);
-  else if (nr <= 2) go(merge_rank<Src, 2>);
-  else if (nr <= 4) go(merge_rank<Src, 4>);
-  else go(merge_rank<Src, kRankR>);
+  if (nr <= 1) go(merge_rank<Src, 1, kRankPer>);
+  else if (nr <= 2) go(merge_rank<Src, 2, kRankPer>);
+  else if (nr <= 4) go(merge_rank<Src, 4, kRankPer>);
+  else if (nr <= 8) go(merge_rank<Src, 8, kRankPerMany>);
+  else go(merge_rank<Src, kRankR, kRankPerMany>);
 }
 
 // ---------------------------------------------------------------------------
@@ -1967,23 +2204,21 @@ static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_
 // ---------------------------------------------------------------------------
 // For a source whose highest keys fall anywhere in the pool (no cluster in
 // one share): the smallest lg in [2, worst] for which bars above the pool's
-// B-th key are rare.  A wave's bar (the least of 2^lg lane-group maxima
-// over its first three chunks) lies above that key when every group holds
-// one of the B; with the B spread at density d = B / n, a group of E / 2^lg
-// keys holds one with probability 1 - exp(-d E / 2^lg).  In a single pass
-// the workgroup's bound is its second largest bar, so two such waves in one
-// workgroup are needed, else one wave anywhere; either must be expected in
-// fewer than one step in a thousand.  Data that breaks the assumption only
-// sends the merge back to the share (exact, slower).
-static int spread_lg(int64_t n, int G, int B, int passes, int64_t chunks_per_wave, int worst) {
+// B-th key are rare.  A wave's bar (the least of 2^lg lane-group maxima over
+// its keys: its first three chunks in a single pass, all of them beyond) lies
+// above that key when every group holds one of the B; with the B spread at
+// density d = B / n, a group of E / 2^lg keys holds one with probability
+// 1 - exp(-d E / 2^lg).  The workgroup's bound is its second largest bar, so
+// two such waves in one workgroup are needed, which must be expected in fewer
+// than one step in a thousand.  Data that breaks the assumption only sends the
+// merge back to the share (exact, slower).
+static int spread_lg(int64_t n, int G, int B, bool one_pass, int64_t chunks_per_wave, int worst) {
   const double d = (double)B / (double)n;
-  const double E = (double)kChunk * (double)(chunks_per_wave < 3 ? chunks_per_wave : 3);
-  const double waves = (double)G * kWavesPerBlock * passes;
+  const double E = (double)kChunk * (double)(one_pass && chunks_per_wave > 3 ? 3 : chunks_per_wave);
   for (int lg = 2; lg < worst; ++lg) {
     const double g = (double)(1 << lg);
     const double pw = std::pow(-std::expm1(-d * E / g), g);  // one wave's bar above the B-th key
-    const double fail = passes == 1 ? (double)G * (kWavesPerBlock * (kWavesPerBlock - 1) / 2) * pw * pw : waves * pw;
-    if (fail <= 1e-3) return lg;
+    if ((double)G * (kWavesPerBlock * (kWavesPerBlock - 1) / 2) * pw * pw <= 1e-3) return lg;
   }
   return worst;
 }
@@ -2009,8 +2244,7 @@ SelectPlan plan_select(int64_t n, int32_t n_theta, int32_t B, bool packed, int m
   if (spread && !packed && n > 0) {
     const int64_t my_chunks = (nchunks + G - 1) / G;
     const int64_t per_pass = (int64_t)kWavesPerBlock * kChunksPerPass;
-    const int passes = (int)((my_chunks + per_pass - 1) / per_pass);
-    lg = spread_lg(n, p.G, B, passes, (my_chunks + kWavesPerBlock - 1) / kWavesPerBlock, lg);
+    lg = spread_lg(n, p.G, B, my_chunks <= per_pass, (my_chunks + kWavesPerBlock - 1) / kWavesPerBlock, lg);
   }
   p.lg = lg;
   int M = pow2_ceil(4 * per);
@@ -2161,8 +2395,7 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
       hipLaunchKernelGGL(local_candidates_multi, multi_grid, dim3(kBlock), 0, stream, src, n, n_theta, p.G, p.lg,
                          p.M, cb, nullptr);
     else
-      hipLaunchKernelGGL(local_candidates<PoolSource>, dim3(p.G, n_theta), dim3(kBlock), 0, stream, src, n, p.G,
-                         p.lg, p.M, cb);
+      launch_local(p, n_theta, stream, nullptr, nullptr, src, n, cb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (n_theta == 1)
@@ -2178,8 +2411,7 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
     hipExtLaunchKernelGGL(local_candidates_multi, multi_grid, dim3(kBlock), 0, stream, marks[0], marks[1], 0, src, n,
                           n_theta, p.G, p.lg, p.M, cb, nullptr);
   else
-    hipExtLaunchKernelGGL(local_candidates<PoolSource>, dim3(p.G, n_theta), dim3(kBlock), 0, stream, marks[0],
-                          marks[1], 0, src, n, p.G, p.lg, p.M, cb);
+    launch_local(p, n_theta, stream, marks[0], marks[1], src, n, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (n_theta == 1)
@@ -2214,8 +2446,7 @@ hipError_t launch_ring_step(int32_t* ring_len, float* ring_arrival, int64_t capa
   src.new_len = new_len;
   src.new_arrival = new_arrival;
   src.n_new = n_new;
-  hipLaunchKernelGGL(local_candidates<RingSource>, dim3(p.G, 1), dim3(kBlock), 0, stream, src, capacity, p.G, p.lg,
-                     p.M, cb);
+  launch_local(p, 1, stream, nullptr, nullptr, src, capacity, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   launch_merge_rank(p, stream, nullptr, nullptr, src, capacity, B, cb, ids, top, n_sel, tomb_len);
@@ -2246,8 +2477,7 @@ hipError_t launch_trial_select(int32_t* len, float* arrival, int64_t capacity, i
   src.new_arrival = new_arrival;
   src.n_new = n_new;
   src.stride = capacity;
-  hipLaunchKernelGGL(local_candidates<TrialSource>, dim3(p.G, n_pools), dim3(kBlock), 0, stream, src, capacity, p.G,
-                     p.lg, p.M, cb);
+  launch_local(p, n_pools, stream, nullptr, nullptr, src, capacity, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_candidates<TrialSource>, dim3(n_pools), dim3(kBlock), 0, stream, src, capacity, p.G, p.M,
@@ -2281,8 +2511,7 @@ hipError_t launch_select(const float* score, int64_t n, int32_t n_theta, int32_t
   ScoreSource src;
   src.score = score;
   src.n = n;
-  hipLaunchKernelGGL(local_candidates<ScoreSource>, dim3(p.G, n_theta), dim3(kBlock), 0, stream, src, n, p.G,
-                     p.lg, p.M, cb);
+  launch_local(p, n_theta, stream, nullptr, nullptr, src, n, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (n_theta == 1)
