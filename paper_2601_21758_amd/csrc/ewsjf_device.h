@@ -610,9 +610,6 @@ __device__ __forceinline__ PhiTerms phi_terms(int b, float arrival, float now, c
 __device__ __forceinline__ float phi_of(const QParams& p, const PhiTerms& t) {
   return __builtin_fmaf(__builtin_fmaf(p.wf2, t.lg, p.wb), t.al, p.wu * t.be);
 }
-__device__ __forceinline__ float phi_f32(int b, float arrival, float now, const QParams& p, const CostF& c) {
-  return phi_of(p, phi_terms(b, arrival, now, c));
-}
 
 // Order-preserving key of a score computed in registers: NaN -> -inf,
 // -0 -> +0, then the sign-magnitude flip.  Never 0 (0 marks "no element").
@@ -638,31 +635,12 @@ __device__ __forceinline__ int clamp_len(int b, int L) {
   return r;
 }
 
-// Stage the routing lut and per-queue constants of one parameter vector into
-// LDS.  lut: kLutBytes bytes; qp: EWSJF_MAX_QUEUES entries.
-__device__ inline void stage_policy(const ewsjf_queue_table* tab, const ewsjf_theta* theta, uint8_t* lut,
-                                    QParams* qp) {
-  const int L = tab->max_len;
-  const int k = tab->k;
-  const uint4* src = reinterpret_cast<const uint4*>(tab->lut);
-  uint4* dst = reinterpret_cast<uint4*>(lut);
-  const int nvec = (L + 1 + 15) / 16;
-  for (int i = threadIdx.x; i < nvec; i += blockDim.x) dst[i] = src[i];
-  if (theta != nullptr) {
-    for (int q = threadIdx.x; q < k; q += blockDim.x) qp[q] = make_qparams(*theta, tab->mean[q], q);
-  }
-}
-
 // Queue of length b in [1, L] from the table's compact routing map: the
 // queue of length 32 (b / 32) - 1 plus the rises at lengths 32 (b / 32) .. b.
 constexpr int kRouteWords = EWSJF_ROUTE_WORDS;
 __device__ __forceinline__ int route_queue(const uint64_t* route, int b) {
   const uint64_t w = route[b >> 5];
   return (int)(uint32_t)(w >> 32) + __builtin_popcount((uint32_t)w << (31 - (b & 31)));
-}
-
-__device__ __forceinline__ int route_lut(int b, int L, const uint8_t* lut) {
-  return b <= 0 ? -1 : (int)lut[b < L ? b : L];
 }
 
 }  // namespace ewsjf

@@ -43,6 +43,8 @@ SelectPlan plan_select(int64_t n, int32_t n_theta, int32_t B, bool packed = fals
 // The plan ewsjf_step uses: packed for several vectors over a pool that fits
 // one pass per workgroup.
 SelectPlan plan_step(int64_t n, int32_t n_theta, int32_t B);
+// The plan ewsjf_select uses.
+SelectPlan plan_scores(int64_t n, int32_t n_theta, int32_t B);
 
 // Tactical step (Algorithm 1): the batch plan computed on the device after
 // the head-of-line pass.  Row 0 of the queue-order selection drains q_sel[0]

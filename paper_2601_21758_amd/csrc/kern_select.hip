@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "ewsjf_device.h"
@@ -2241,7 +2242,7 @@ SelectPlan plan_select(int64_t n, int32_t n_theta, int32_t B, bool packed, int m
   if (m > 64) m = 64;
   int lg = 0;
   while ((2 << lg) <= m) ++lg;
-  if (spread && !packed && n > 0) {
+  if (spread && n > 0 && (!packed || G < (nchunks + per_wg - 1) / per_wg)) {
     const int64_t my_chunks = (nchunks + G - 1) / G;
     const int64_t per_pass = (int64_t)kWavesPerBlock * kChunksPerPass;
     lg = spread_lg(n, p.G, B, my_chunks <= per_pass, (my_chunks + kWavesPerBlock - 1) / kWavesPerBlock, lg);
@@ -2344,12 +2345,34 @@ SelectPlan plan_step(int64_t n, int32_t n_theta, int32_t B) {
   return p;
 }
 
-// Trials: each pool gets the workgroups that give every wave one full pass
-// (four chunks in flight), the shape of the 4M-pool step, rather than one per
-// CU and row: a workgroup's table staging and list publication are then paid
-// once per 16,384 requests.
+// Trials: as many workgroups per pool as make one round of the chip, each
+// walking its share with chunks in flight (local_stream), so a workgroup's
+// table staging and list publication are paid once per compute unit; at least
+// one per 32 admissions (a wave's region holds 64 entries) and no more than
+// one full pass each needs.  16 pools of 1M slots: 37.8 us (3.6 TB/s) with 16
+// workgroups per pool, 57.6 us with one pass each (64 per pool, four rounds).
 SelectPlan plan_trial(int64_t capacity, int32_t n_pools, int32_t B) {
-  return plan_select(capacity, n_pools, B, true);
+  const int64_t per_pass = (int64_t)kWavesPerBlock * kChunksPerPass * kChunk;
+  const int full = (int)std::min<int64_t>((capacity + per_pass - 1) / per_pass, kMaxGrid);
+  int G = std::max(kMaxGrid / n_pools, (B + 31) / 32);
+  G = std::max(1, std::min(G, full));
+  return plan_select(capacity, n_pools, B, true, G, true);
+}
+
+// Scores given by the caller: one row takes a workgroup per 16 chunks (one
+// chunk per wave); several rows take up to four chunks per wave when that
+// leaves one round of the
+// chip: four rows of 1,000,003 scores
+// take 10.1 us with four chunks per wave (248 workgroups), 23.2 us with one
+// (980: four rounds, each with its own list to close).
+SelectPlan plan_scores(int64_t n, int32_t n_theta, int32_t B) {
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  int per_wave = 1;
+  while (per_wave < kChunksPerPass && (nchunks / (kWavesPerBlock * per_wave)) * n_theta > kMaxGrid) per_wave *= 2;
+  const int64_t G = (nchunks + kWavesPerBlock * per_wave - 1) / (kWavesPerBlock * per_wave);
+  SelectPlan p = plan_select(n, n_theta, B, false, (int)std::max<int64_t>(1, std::min<int64_t>(G, kMaxGrid)));
+  p.ws_bytes = std::max(p.ws_bytes, plan_select(n, n_theta, B).ws_bytes);
+  return p;
 }
 
 hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, float now,
@@ -2506,7 +2529,7 @@ hipError_t launch_fifo_select(const int32_t* len, const float* arrival, int64_t 
 
 hipError_t launch_select(const float* score, int64_t n, int32_t n_theta, int32_t B, int32_t* ids, float* top,
                          int32_t* n_sel, void* ws, hipStream_t stream) {
-  const SelectPlan p = plan_select(n, n_theta, B);
+  const SelectPlan p = plan_scores(n, n_theta, B);
   const CandBufs cb = carve(p, ws);
   ScoreSource src;
   src.score = score;
