@@ -215,9 +215,9 @@ class StreamingScheduler:
         """One scheduling step over the ring: (ids[1,B], top[1,B], n_sel[1]).
         With length/arrival, the step's arrivals are inserted first, inside
         the step's kernels (same effect as insert() then step())."""
-        main = torch.cuda.current_stream(self.device)
         if self.pending is not None and (self.handover == "next_step" or self.pending.query()):
-            main.wait_event(self.pending)  # free once the partition has finished (when_ready)
+            # free once the partition has finished (when_ready)
+            torch.cuda.current_stream(self.device).wait_event(self.pending)
             self.cur = 1 - self.cur
             self.pending = None
             self.swaps.append(self.steps_done)
