@@ -1417,6 +1417,173 @@ __device__ inline int select_top(MergeShared& ms, int U, int B) {
   return nS < B ? nS : B;
 }
 
+// Exact top-B of the block's entries v (0 = none; entry r of thread tid has the
+// place tid + r * kBlock < places <= kMergeCap): sorted descending into
+// ms.X[0..U), U = min(B, entries), returned.  A histogram of 4,096 linear
+// buckets over the entries' range, the bucket where the count from the top
+// reaches B, a scatter of the entries at or above it, and each one's rank
+// inside its bucket.  *max_bound = the largest `bound` of the block.
+template <int kR>
+__device__ __forceinline__ int rank_registers(MergeShared& ms, const uint64_t (&v)[kR], int places, int B,
+                                              uint64_t bound, uint64_t* max_bound) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  // Exact range and count (registers -> wave -> LDS) while the histogram is
+  // cleared.
+  uint64_t mx = 0, mn = ~0ull;
+  int nz = 0;
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    mx = v[r] > mx ? v[r] : mx;
+    mn = (v[r] != 0ull && v[r] < mn) ? v[r] : mn;
+    nz += v[r] != 0ull;
+  }
+  mx = wave_max_u64(mx);
+  mn = wave_min_u64(mn);
+  nz = (int)__ockl_wfred_add_u32((uint32_t)nz);
+  const uint64_t tb = wave_max_u64(bound);
+  for (int i = tid; i < 4096; i += kBlock) ms.cnt[i] = 0u;
+  if (lane == 0) {
+    ms.wmax[wv] = mx;
+    ms.wmin[wv] = mn;
+    ms.iscan[wv] = nz;
+    ms.wbound[wv] = tb;
+  }
+  __syncthreads();
+  // Every wave reduces the kWavesPerBlock partials itself, one per lane.
+  static_assert(kWavesPerBlock <= kWave, "one partial per lane");
+  const bool pl = lane < kWavesPerBlock;
+  const int total = (int)__ockl_wfred_add_u32(pl ? (uint32_t)ms.iscan[lane] : 0u);
+  *max_bound = wave_max_u64(pl ? ms.wbound[lane] : 0ull);
+  if (total == 0) return 0;
+  const uint64_t hi = wave_max_u64(pl ? ms.wmax[lane] : 0ull);
+  const uint64_t lo = wave_min_u64(pl ? ms.wmin[lane] : ~0ull);
+  const uint64_t diff = hi - lo;
+  const int bits = diff == 0 ? 0 : 64 - __clzll((long long)diff);
+  const int shift = bits > 12 ? bits - 12 : 0;
+#pragma unroll
+  for (int r = 0; r < kR; ++r)
+    if (v[r] != 0ull) atomicAdd(&ms.cnt[(int)((v[r] - lo) >> shift)], 1u);
+  __syncthreads();
+  // Bucket offsets from the top: this thread's 4 buckets, a wave scan, then
+  // the waves' totals (one per lane) for the offset of this wave.
+  const int want = B < total ? B : total;
+  uint32_t cb[4];
+  int s4 = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    cb[q] = ms.cnt[4095 - 4 * tid - q];
+    s4 += (int)cb[q];
+  }
+  const int incl = wave_incl_scan_add(s4);
+  if (lane == kWave - 1) ms.wtot[wv] = incl;
+  __syncthreads();
+  const int wt = pl ? ms.wtot[lane] : 0;
+  const int wincl = wave_incl_scan_add(wt);
+  const int before = __builtin_amdgcn_readlane(wincl - wt, wv);  // totals of the waves before this one
+  int run = before + incl - s4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = 4095 - 4 * tid - q;
+    ms.cnt[b] = (uint32_t)run;  // bucket start, used as a cursor
+    if (run < want && run + (int)cb[q] >= want) {
+      ms.cut_bin = b;
+      ms.cut_cnt = run + (int)cb[q];
+    }
+    run += (int)cb[q];
+  }
+  __syncthreads();
+  const int cstar = ms.cut_bin, cum_at = ms.cut_cnt;
+  if (cum_at > kSortMax) {  // uniform: too many in the cut's bucket
+#pragma unroll
+    for (int r = 0; r < kR; ++r)
+      if (tid + r * kBlock < places) ms.X[tid + r * kBlock] = v[r];
+    __syncthreads();
+    return select_top(ms, places, B);
+  }
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    if (v[r] != 0ull) {
+      const int b = (int)((v[r] - lo) >> shift);
+      if (b >= cstar) ms.S[atomicAdd(&ms.cnt[b], 1u)] = v[r];
+    }
+  }
+  __syncthreads();
+  // ms.cnt[b] is now the end of bucket b, and the end of bucket b+1 is its
+  // start: rank each element inside its bucket.
+  for (int i = tid; i < cum_at; i += kBlock) {
+    const uint64_t x = ms.S[i];
+    const int b = (int)((x - lo) >> shift);
+    const int start = b == 4095 ? 0 : (int)ms.cnt[b + 1];
+    const int end = (int)ms.cnt[b];
+    int rank = 0;
+    for (int j = start; j < end; ++j) rank += ms.S[j] > x;
+    ms.X[start + rank] = x;
+  }
+  __syncthreads();
+  return want;
+}
+
+// The rows' outputs from the sorted entries ms.X[0..sel).
+__device__ __forceinline__ void publish_row(const MergeShared& ms, int sel, int B, int t, int32_t* __restrict__ ids,
+                                            float* __restrict__ top, int32_t* n_sel, int32_t* tomb_len) {
+  int32_t* ids_t = ids + (size_t)t * B;
+  float* top_t = top + (size_t)t * B;
+  for (int r = threadIdx.x; r < B; r += kBlock) {
+    if (r < sel) {
+      const uint64_t x = ms.X[r];
+      ids_t[r] = (int32_t)comp_id(x);
+      top_t[r] = float_of_ukey((uint32_t)(x >> 32));
+      if (tomb_len != nullptr) tomb_len[comp_id(x)] = 0;
+    } else {
+      ids_t[r] = -1;
+      top_t[r] = __builtin_nanf("");
+    }
+  }
+  if (threadIdx.x == 0) n_sel[t] = sel;
+}
+
+// ---------------------------------------------------------------------------
+// A pool that one workgroup holds in registers (up to kSmallPool requests):
+// the keys of every request and their exact top B in one launch, a workgroup
+// per row.  Bound by latency: the table and the pool arrive together, then six
+// barriers.  4,096 requests: 5.9 us, where local_candidates (one workgroup) and
+// merge_rank took 7.1 and 3.8 us and a second launch.
+// ---------------------------------------------------------------------------
+constexpr int kSmallPool = 8192;
+static_assert(kSmallPool <= kMergeCap, "every request can be a candidate");
+
+template <class Src, int kChunks>
+__global__ __launch_bounds__(kBlock) void select_small(Src src0, int64_t n, int B, int32_t* __restrict__ ids,
+                                                       float* __restrict__ top, int32_t* __restrict__ n_sel,
+                                                       int32_t* tomb_len) {
+  __shared__ MergeShared ms;
+  __shared__ typename Src::Shared sh;
+  const int t = blockIdx.x, lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const Src src = bind_theta(src0, t);
+  const bool stager = wv < kStageWaves;
+  typename Src::Stage st;
+  if (stager) src.stage_load(st, t);
+  typename Src::Raw raw[kChunks];
+#pragma unroll
+  for (int j = 0; j < kChunks; ++j) raw[j] = src.load_chunk(wv + j * kWavesPerBlock, n, lane);  // past the end: zeros
+  if (stager) src.stage_store(sh, st);
+  __syncthreads();
+  const auto km = src.key_mode(sh);
+  uint64_t v[4 * kChunks];
+#pragma unroll
+  for (int j = 0; j < kChunks; ++j) {
+    uint32_t key[4];
+    src.keys4(raw[j], sh, km, key);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[4 * j + e] = key[e] != 0u ? make_comp(key[e], (uint32_t)((wv + j * kWavesPerBlock) * kChunk + 4 * lane + e)) : 0ull;
+  }
+  uint64_t unused;
+  const int sel = rank_registers(ms, v, 4 * kChunks * kBlock, B, 0ull, &unused);
+  publish_row(ms, sel, B, t, ids, top, n_sel, tomb_len);
+}
+
 // Count of entries greater than v in the descending array a[0..len).
 __device__ __forceinline__ int count_greater_desc(const uint64_t* a, int len, uint64_t v) {
   int lo = 0, hi = len;
@@ -1713,12 +1880,7 @@ __global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, Fi
     return;
   }
   select_top(ms, U, B);
-  for (int r = tid; r < B; r += kBlock) {
-    const uint64_t x = ms.X[r];
-    ids[(size_t)t * B + r] = (int32_t)comp_id(x);
-    top[(size_t)t * B + r] = float_of_ukey((uint32_t)(x >> 32));
-  }
-  if (tid == 0) n_sel[t] = B;
+  publish_row(ms, B, B, t, ids, top, n_sel, nullptr);
 }
 
 // LDS of the exact merge.
@@ -1774,103 +1936,8 @@ __device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int
     sT[tid] = Tw;
     sT2[tid] = Tw2;
   }
-  // Exact range and count of the candidates (registers -> wave -> LDS)
-  // while the slots go to LDS and the histogram is cleared.
-  uint64_t mx = 0, mn = ~0ull;
-  int nz = 0;
-#pragma unroll
-  for (int r = 0; r < kR; ++r) {
-    const int idx = tid + r * kBlock;
-    if (idx < GM) ms.X[idx] = v[r];
-    mx = v[r] > mx ? v[r] : mx;
-    mn = (v[r] != 0ull && v[r] < mn) ? v[r] : mn;
-    nz += v[r] != 0ull;
-  }
-  mx = wave_max_u64(mx);
-  mn = wave_min_u64(mn);
-  nz = (int)__ockl_wfred_add_u32((uint32_t)nz);
-  const uint64_t tb = wave_max_u64(Tw);
-  for (int i = tid; i < 4096; i += kBlock) ms.cnt[i] = 0u;
-  if (lane == 0) {
-    ms.wmax[wv] = mx;
-    ms.wmin[wv] = mn;
-    ms.iscan[wv] = nz;
-    ms.wbound[wv] = tb;
-  }
-  __syncthreads();
-  // Every wave reduces the kWavesPerBlock partials itself, one per lane.
-  static_assert(kWavesPerBlock <= kWave, "one partial per lane");
-  const bool pl = lane < kWavesPerBlock;
-  const int total = (int)__ockl_wfred_add_u32(pl ? (uint32_t)ms.iscan[lane] : 0u);
-  // The largest bound of all shares: the recovery below runs only when it
-  // lies above the cut (it usually does not).
-  const uint64_t max_bound = wave_max_u64(pl ? ms.wbound[lane] : 0ull);
-  int U = 0;
-  if (total > 0) {
-    const uint64_t hi = wave_max_u64(pl ? ms.wmax[lane] : 0ull);
-    const uint64_t lo = wave_min_u64(pl ? ms.wmin[lane] : ~0ull);
-    const uint64_t diff = hi - lo;
-    const int bits = diff == 0 ? 0 : 64 - __clzll((long long)diff);
-    const int shift = bits > 12 ? bits - 12 : 0;
-#pragma unroll
-    for (int r = 0; r < kR; ++r)
-      if (v[r] != 0ull) atomicAdd(&ms.cnt[(int)((v[r] - lo) >> shift)], 1u);
-    __syncthreads();
-    // Bucket offsets from the top: this thread's 4 buckets, a wave scan, then
-    // the waves' totals (one per lane) for the offset of this wave.
-    const int want = B < total ? B : total;
-    uint32_t cb[4];
-    int s4 = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      cb[q] = ms.cnt[4095 - 4 * tid - q];
-      s4 += (int)cb[q];
-    }
-    const int incl = wave_incl_scan_add(s4);
-    if (lane == kWave - 1) ms.wtot[wv] = incl;
-    __syncthreads();
-    const int wt = pl ? ms.wtot[lane] : 0;
-    const int wincl = wave_incl_scan_add(wt);
-    const int before = __builtin_amdgcn_readlane(wincl - wt, wv);  // totals of the waves before this one
-    int run = before + incl - s4;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int b = 4095 - 4 * tid - q;
-      ms.cnt[b] = (uint32_t)run;  // bucket start, used as a cursor
-      if (run < want && run + (int)cb[q] >= want) {
-        ms.cut_bin = b;
-        ms.cut_cnt = run + (int)cb[q];
-      }
-      run += (int)cb[q];
-    }
-    __syncthreads();
-    const int cstar = ms.cut_bin, cum_at = ms.cut_cnt;
-    if (cum_at <= kSortMax) {
-#pragma unroll
-      for (int r = 0; r < kR; ++r) {
-        if (v[r] != 0ull) {
-          const int b = (int)((v[r] - lo) >> shift);
-          if (b >= cstar) ms.S[atomicAdd(&ms.cnt[b], 1u)] = v[r];
-        }
-      }
-      __syncthreads();
-      // ms.cnt[b] is now the end of bucket b, and the end of bucket b+1 is
-      // its start: rank each element inside its bucket.
-      for (int i = tid; i < cum_at; i += kBlock) {
-        const uint64_t x = ms.S[i];
-        const int b = (int)((x - lo) >> shift);
-        const int start = b == 4095 ? 0 : (int)ms.cnt[b + 1];
-        const int end = (int)ms.cnt[b];
-        int rank = 0;
-        for (int j = start; j < end; ++j) rank += ms.S[j] > x;
-        ms.X[start + rank] = x;
-      }
-      __syncthreads();
-      U = want;
-    } else {
-      U = select_top(ms, GM, B);  // X holds all G x M slots; empty slots are 0
-    }
-  }
+  uint64_t max_bound;
+  int U = rank_registers(ms, v, GM, B, Tw, &max_bound);
   uint64_t tau = (U >= B) ? ms.X[B - 1] : 0ull;
   EWSJF_STAMP(kStampMergeExact, 1);
 
@@ -1984,24 +2051,7 @@ __device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int
     __syncthreads();
   }
 
-  // Publish.
-  const int sel = U < B ? U : B;
-  int32_t* ids_t = ids + (size_t)t * B;
-  float* top_t = top + (size_t)t * B;
-  for (int r = tid; r < B; r += kBlock) {
-    if (r < sel) {
-      const uint64_t x = ms.X[r];
-      ids_t[r] = (int32_t)comp_id(x);
-      top_t[r] = float_of_ukey((uint32_t)(x >> 32));
-    } else {
-      ids_t[r] = -1;
-      top_t[r] = __builtin_nanf("");
-    }
-  }
-  if (tid == 0) n_sel[t] = sel;
-  if (tomb_len != nullptr) {
-    for (int r = tid; r < sel; r += kBlock) tomb_len[comp_id(ms.X[r])] = 0;
-  }
+  publish_row(ms, U < B ? U : B, B, t, ids, top, n_sel, tomb_len);
   EWSJF_STAMP(kStampMergeExact, 2);
   EWSJF_STAMP_FLUSH(kStampMergeExact);
 }
@@ -2178,6 +2228,20 @@ static void launch_local(const SelectPlan& p, int rows, hipStream_t stream, hipE
   else go(local_stream<Src>);
 }
 
+// Launches select_small where the rule holds.
+template <class Src>
+static void launch_small(int rows, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const Src& src, int64_t n, int B,
+                         int32_t* ids, float* top, int32_t* n_sel, int32_t* tomb_len) {
+  auto go = [&](auto kern) {
+    if (e0 != nullptr)
+      hipExtLaunchKernelGGL(kern, dim3(rows), dim3(kBlock), 0, stream, e0, e1, 0, src, n, B, ids, top, n_sel, tomb_len);
+    else
+      hipLaunchKernelGGL(kern, dim3(rows), dim3(kBlock), 0, stream, src, n, B, ids, top, n_sel, tomb_len);
+  };
+  if (n <= kChunk * kWavesPerBlock) go(select_small<Src, 1>);
+  else go(select_small<Src, 2>);
+}
+
 // Launches merge_rank with the smallest compiled slots-per-thread bound.
 template <class Src>
 static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const Src& src,
@@ -2313,7 +2377,7 @@ struct FilterPlan {
 };
 static FilterPlan filter_plan(int64_t n, int32_t n_theta, int32_t B) {
   FilterPlan f;
-  if (n_theta < 2 || n < kSample || (n_theta < 6 && n > kFilterFewMax) || !step_packed(n, n_theta)) return f;
+  if (n_theta < 2 || n <= kSmallPool || (n_theta < 6 && n > kFilterFewMax) || !step_packed(n, n_theta)) return f;
   const double share = (double)B * kSample / (double)n;
   const int rank = (int)std::ceil(share + 4.0 * std::sqrt(share) + 8.0);
   if (rank > kSampleMaxRank) return f;
@@ -2389,6 +2453,15 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
   src.theta = theta;
   src.now = now;
   src.cost = CostF{(float)cost.c0, (float)cost.c1, (float)cost.c2};
+  if (n <= kSmallPool) {
+    launch_small(n_theta, stream, marks ? marks[0] : nullptr, marks ? marks[1] : nullptr, src, n, B, ids, top, n_sel,
+                 tomb_len);
+    hipError_t e = hipGetLastError();
+    // no second kernel: its events take one moment
+    if (marks != nullptr && e == hipSuccess) e = hipEventRecord(marks[2], stream);
+    if (marks != nullptr && e == hipSuccess) e = hipEventRecord(marks[3], stream);
+    return e;
+  }
   const dim3 multi_grid(p.G, (n_theta + kThetaPerBlock - 1) / kThetaPerBlock);
   const FilterPlan f = filter_plan(n, n_theta, B);
   if (f.rank > 0) {
@@ -2534,6 +2607,10 @@ hipError_t launch_select(const float* score, int64_t n, int32_t n_theta, int32_t
   ScoreSource src;
   src.score = score;
   src.n = n;
+  if (n <= kSmallPool) {
+    launch_small(n_theta, stream, nullptr, nullptr, src, n, B, ids, top, n_sel, nullptr);
+    return hipGetLastError();
+  }
   launch_local(p, n_theta, stream, nullptr, nullptr, src, n, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

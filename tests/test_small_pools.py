@@ -1,0 +1,44 @@
+"""Pools one workgroup answers (up to 8,192 requests): chunk edges, more
+admissions than requests, equal keys, several vectors, tombstones, and the
+same through ewsjf_select."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2601_21758_amd import workloads as W
+from parity_util import check_admission
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["mixed", "all_equal", "tombstones", "oldest_first", "over_max"])
+@pytest.mark.parametrize("n,nt,B", [(0, 2, 5), (1, 1, 1), (255, 1, 300), (4096, 1, 64), (4097, 3, 4096), (8191, 2, 700),
+                                    (8192, 1, 4096), (8193, 1, 64)])
+def test_small_pool(n, nt, B, kind):
+    from paper_2601_21758_amd import ewsjf as E
+    if kind == "mixed":
+        p = W.make_pool("three", max(n, 1), 4, arrivals="uniform", horizon=300.0, K=16)
+        L, A, now = p.length[:n], p.arrival[:n], p.now
+    else:
+        L, A, now = W.adversarial(kind, max(n, 1), 4)
+        L, A = L[:n], A[:n]
+    print(f"small pool n={n} vectors={nt} B={B} {kind}", flush=True)
+    theta = np.concatenate([W.THETA_MID.reshape(1, 6), W.config(3).theta[:nt - 1]]).astype(np.float32)
+    t = oracle.partition(np.clip(np.append(L, 5), 1, None), init_queues=16, max_queues=16)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    tab = E.upload_table(t.bounds, t.mean, 32768, t.lo, t.hi, t.count, t.sum)
+    Ld = dev(L)
+    ids, top, nsel = (x.cpu().numpy() for x in E.step(Ld, dev(A), now, tab, dev(theta), B, tombstone=nt == 1))
+    rids, rtop, rnsel, rs = oracle.step(L, A, now, t, theta, B)
+    for ti in range(nt):
+        check_admission(ids[ti], top[ti], nsel[ti], rids[ti], rtop[ti], rnsel[ti], rs[ti])
+    if nt == 1:
+        left = L.copy()
+        left[ids[0][:nsel[0]]] = 0
+        assert np.array_equal(Ld.cpu().numpy(), left)
+    if n:
+        s = E.score(dev(L), dev(A), now, tab, dev(theta))
+        i2, t2, n2 = (x.cpu().numpy() for x in E.select(s, B))
+        assert np.array_equal(i2, ids) and np.array_equal(n2, nsel)
+        assert np.array_equal(t2.view(np.int32), top.view(np.int32))
