@@ -60,7 +60,8 @@ METRIC = "pending requests routed+scored+selected per sec at 4M pool; % HBM peak
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_REQUEST = 8  # int32 prompt length + float32 arrival, each read once
 PROFILE = os.path.join(ROOT, "profiles", "fused_step_large_mixed_4m.pmc.txt")
-KERNEL_SOURCES = ("paper_2601_21758_amd/csrc/kern_select.hip", "paper_2601_21758_amd/csrc/ewsjf_device.h")
+KERNEL_SOURCES = ("paper_2601_21758_amd/csrc/kern_select.hip", "paper_2601_21758_amd/csrc/ewsjf_merge.h",
+                  "paper_2601_21758_amd/csrc/ewsjf_device.h")
 
 
 def kernel_source_hash() -> str:

@@ -8,9 +8,13 @@
 //   tac_plan    (1 workgroup)   empty counters, ArgMax queue, how many
 //                               requests GreedyFill and Backfill take from the
 //                               queue and its two neighbours.
-//   queue-order selection       local_candidates / merge_candidates with
-//                               FifoSource: the oldest requests of each of
-//                               the (up to) three queues.
+//   queue-order selection       the oldest requests of each of the (up to)
+//                               three queues.  Large pools: tac_scan collects a
+//                               sample, tac_reduce takes an age threshold per
+//                               queue from it, tac_gather lists the members
+//                               at or above it, tac_finish orders them.
+//                               Otherwise local_candidates /
+//                               merge_candidates with FifoSource.
 //   tac_finish  (1 workgroup)   the batch in order, tombstones, and the
 //                               removal of queues empty past the threshold
 //                               (re-absorbed by the neighbour of lower Eq. 3
@@ -24,15 +28,38 @@
 // index first, and the last queue is never removed.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "ewsjf_device.h"
 #include "ewsjf_launch.h"
 #include "ewsjf_lut.h"
+#include "ewsjf_merge.h"
 
 namespace ewsjf {
 namespace {
 
 constexpr int kLutVecs = kLutBytes / 16;
 constexpr int kReduceThreads = 256;
+constexpr int kCountCopies = 8;        // of each queue's counter in tac_scan, by lane
+constexpr int kSampledChunks = 65536;  // at most, two requests of each
+constexpr int kSampleMax = 2 * kSampledChunks;
+constexpr int kGatherLds = 2048;       // members of one row that one workgroup of tac_gather holds
+
+// The oldest members of the plan's queues by an age threshold.
+struct Gather {
+  // Sample s sits at place 16 (s mod 2^lg_p) + s / 2^lg_p, so the 16 a thread
+  // loads as vectors are far apart in the pool.
+  uint32_t* skey;   // [kSampleMax] FIFO keys of the sampled requests (0 = empty slot)
+  uint8_t* sq;      // [kSampleMax] their queues
+  uint64_t* tau;    // [EWSJF_MAX_QUEUES] the queue's members at or above it hold its oldest B
+  int32_t* count;   // [kTacticalRows] members found (more than kMergeCap: some were dropped)
+  uint64_t* list;   // [kTacticalRows][kMergeCap]
+  int lg_step;      // every 2^lg_step-th chunk is sampled
+  int lg_p;         // 16 << lg_p places
+  int n;            // samples, two per sampled chunk
+  int rank;         // members of the sample the thresholds lie at; 0: not used
+};
 
 struct TacWs {
   uint32_t* part_cnt;   // [EWSJF_MAX_QUEUES][G]
@@ -44,6 +71,7 @@ struct TacWs {
   int32_t* row_ids;     // [kTacticalRows][B]
   float* row_top;       // [kTacticalRows][B]
   int32_t* row_n;       // [kTacticalRows]
+  Gather g;
   void* select_ws;
 };
 
@@ -56,6 +84,34 @@ int scan_grid(int64_t n) {
 }
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// The sampled places of a chunk, by its number among the sampled chunks: at
+// and 128 + at, at in 0..127.
+__device__ __forceinline__ uint32_t sample_place(uint32_t i) { return i * 0x9E3779B1u >> 25; }
+
+int sample_step(int64_t n) {
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  int lg = 0;
+  while ((nchunks >> lg) > kSampledChunks) ++lg;
+  return lg;
+}
+
+// The rank of a queue's age threshold among its sampled members, or 0 where the
+// gather is not used.  The rank: the mean number of the B oldest in the sample
+// (about a Poisson count), four standard deviations and a few more.  The
+// members at or above the threshold (rank / density of them) must fit a
+// workgroup's list with five standard deviations to spare (B up to about 1,500
+// for pools up to 16M), unless every queue fits it anyway.  Measured (us a step,
+// random / arrival order, gathered against local_candidates and
+// merge_candidates with FifoSource): 32 / 35 against 54 / 39 at 4,096 requests
+// and B = 64, 36 / 33 against 55 / 60 at 65,536 and 64, 37 / 36 against 42 / 84
+// at 1M and 1,024, 57 / 57 against 61 / 105 at 8M and 256.
+int gather_rank(int64_t n, int32_t B) {
+  const double density = 2.0 / ((double)kChunk * (double)(1 << sample_step(n)));
+  const double mean = B * density;
+  const int rank = (int)std::ceil(mean + 4.0 * std::sqrt(mean) + 8.0);
+  return n <= kMergeCap || (rank + 5.0 * std::sqrt((double)rank)) / density <= kMergeCap ? rank : 0;
+}
 
 size_t carve_tac(int64_t n, int32_t B, void* ws, TacWs* w) {
   const int G = scan_grid(n);
@@ -76,6 +132,16 @@ size_t carve_tac(int64_t n, int32_t B, void* ws, TacWs* w) {
   t.row_ids = reinterpret_cast<int32_t*>(take((size_t)kTacticalRows * B * 4));
   t.row_top = reinterpret_cast<float*>(take((size_t)kTacticalRows * B * 4));
   t.row_n = reinterpret_cast<int32_t*>(take(kTacticalRows * 4));
+  t.g.skey = reinterpret_cast<uint32_t*>(take(kSampleMax * sizeof(uint32_t)));
+  t.g.sq = reinterpret_cast<uint8_t*>(take(kSampleMax));
+  t.g.tau = reinterpret_cast<uint64_t*>(take(EWSJF_MAX_QUEUES * sizeof(uint64_t)));
+  t.g.count = reinterpret_cast<int32_t*>(take(kTacticalRows * sizeof(int32_t)));
+  t.g.list = reinterpret_cast<uint64_t*>(take((size_t)kTacticalRows * kMergeCap * sizeof(uint64_t)));
+  t.g.lg_step = sample_step(n);
+  t.g.n = 2 * (int)(((n + kChunk - 1) / kChunk + (1ll << t.g.lg_step) - 1) >> t.g.lg_step);
+  t.g.lg_p = 0;
+  while ((16 << t.g.lg_p) < t.g.n) ++t.g.lg_p;
+  t.g.rank = gather_rank(n, B);
   t.select_ws = take(plan_select(n, kTacticalRows, B).ws_bytes);
   if (w) *w = t;
   return o;
@@ -83,13 +149,20 @@ size_t carve_tac(int64_t n, int32_t B, void* ws, TacWs* w) {
 
 // ---------------------------------------------------------------------------
 // Head-of-line pass.  Chunk c of workgroup w at local index lc is
-// c = w + G * lc; each wave keeps four chunks in flight.
+// c = w + G * lc; each wave keeps four chunks in flight.  Counters are kept
+// once per lane of eight: most requests of a workload fall in a few queues, and
+// lanes adding to one counter are served one after the other (4M requests: 12.4
+// us, 14.5 us with one counter per queue, the sample included).
+//
+// Two requests of every sampled chunk go to the sample, 128 slots apart, at a
+// place of the chunk that varies from chunk to chunk.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tac_scan(const int32_t* __restrict__ len, const float* __restrict__ arrival,
                                                    int64_t n, const ewsjf_queue_table* __restrict__ tab, int G,
-                                                   uint32_t* __restrict__ part_cnt, uint64_t* __restrict__ part_head) {
+                                                   uint32_t* __restrict__ part_cnt, uint64_t* __restrict__ part_head,
+                                                   Gather g) {
   __shared__ uint8_t lut[kLutBytes];
-  __shared__ uint32_t cnt[EWSJF_MAX_QUEUES];
+  __shared__ uint32_t cnt[EWSJF_MAX_QUEUES * kCountCopies];
   __shared__ uint64_t head[EWSJF_MAX_QUEUES];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   {
@@ -97,13 +170,12 @@ __global__ __launch_bounds__(kBlock) void tac_scan(const int32_t* __restrict__ l
     i32x4* dst = reinterpret_cast<i32x4*>(lut);
     for (int i = tid; i < kLutVecs; i += kBlock) dst[i] = src[i];
   }
-  if (tid < EWSJF_MAX_QUEUES) {
-    cnt[tid] = 0u;
-    head[tid] = ~0ull;
-  }
+  for (int i = tid; i < EWSJF_MAX_QUEUES * kCountCopies; i += kBlock) cnt[i] = 0u;
+  if (tid < EWSJF_MAX_QUEUES) head[tid] = ~0ull;
   const int L = tab->max_len, k = tab->k;
   __syncthreads();
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  const int copy = lane & (kCountCopies - 1);
   for (int64_t lc0 = wv;; lc0 += 4 * kWavesPerBlock) {
     const int64_t c0 = (int64_t)blockIdx.x + (int64_t)G * lc0;
     if (c0 >= nchunks) break;
@@ -116,30 +188,50 @@ __global__ __launch_bounds__(kBlock) void tac_scan(const int32_t* __restrict__ l
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int64_t first = ((int64_t)blockIdx.x + (int64_t)G * (lc0 + (int64_t)j * kWavesPerBlock)) * kChunk;
+      const int64_t c = (int64_t)blockIdx.x + (int64_t)G * (lc0 + (int64_t)j * kWavesPerBlock);
+      const int64_t first = c * kChunk;
+      // the sampled element of lanes with this low part, -1 elsewhere
+      int pick = -1;
+      if (g.rank > 0 && c < nchunks && (c & ((1ll << g.lg_step) - 1)) == 0) {  // uniform
+        const uint32_t at = sample_place((uint32_t)(c >> g.lg_step));
+        pick = (int)(at >> 2) == (lane & 31) ? (int)(at & 3u) : -1;
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int b = l[j][e];
+        const int q = b > 0 ? (int)lut[min(b, L)] : 0xFFFF;
+        const uint32_t ak = arrival_key(__int_as_float(a[j][e]));
+        const uint32_t id = (uint32_t)(first + 4 * lane + e);
         if (b > 0) {
-          const int q = lut[min(b, L)];
-          atomicAdd(&cnt[q], 1u);
-          const uint64_t hk = ((uint64_t)arrival_key(__int_as_float(a[j][e])) << 32) |
-                              (uint64_t)(first + 4 * lane + e);
+          atomicAdd(&cnt[q * kCountCopies + copy], 1u);
+          const uint64_t hk = ((uint64_t)ak << 32) | (uint64_t)id;
           if (hk < head[q]) atomicMin(reinterpret_cast<unsigned long long*>(&head[q]), (unsigned long long)hk);
+        }
+        if (pick == e) {
+          const int s = 2 * (int)(c >> g.lg_step) + (lane >> 5);
+          const int place = 16 * (s & ((1 << g.lg_p) - 1)) + (s >> g.lg_p);
+          g.skey[place] = b > 0 ? ~ak : 0u;
+          g.sq[place] = (uint8_t)q;
         }
       }
     }
   }
   __syncthreads();
   if (tid < k) {
-    part_cnt[(size_t)tid * G + blockIdx.x] = cnt[tid];
+    uint32_t c = 0;
+#pragma unroll
+    for (int i = 0; i < kCountCopies; ++i) c += cnt[tid * kCountCopies + i];
+    part_cnt[(size_t)tid * G + blockIdx.x] = c;
     part_head[(size_t)tid * G + blockIdx.x] = head[tid];
   }
 }
 
 // ---------------------------------------------------------------------------
-// Per queue: totals over the workgroups, and the head's score in binary64
-// (Eq. 1 / Eq. 4, the oracle's expression order; no contraction).
+// Per queue: totals over the workgroups, the head's score in binary64 (Eq. 1 /
+// Eq. 4, the oracle's expression order; no contraction) and, for the gather,
+// the age threshold.  Every queue's threshold is taken here, on as many compute
+// units, before the plan knows the queues it needs: one workgroup reading the
+// whole sample after the plan took 10 us more.
 // ---------------------------------------------------------------------------
 __device__ float head_phi(int32_t len, float arrival, float now, int q, double mean, const ewsjf_theta& th,
                           const ewsjf_cost& c) {
@@ -159,36 +251,79 @@ __device__ float head_phi(int32_t len, float arrival, float now, int q, double m
   return key != key ? -__builtin_huge_valf() : key;
 }
 
-__global__ __launch_bounds__(kReduceThreads) void tac_reduce(const uint32_t* __restrict__ part_cnt,
-                                                             const uint64_t* __restrict__ part_head, int G,
-                                                             const int32_t* __restrict__ len,
-                                                             const float* __restrict__ arrival, float now,
-                                                             const ewsjf_queue_table* __restrict__ tab,
-                                                             const ewsjf_theta* __restrict__ theta, ewsjf_cost cost,
-                                                             uint32_t* cnt, uint64_t* head, float* score) {
+// The age threshold of a queue: the composite at the rank among its sampled
+// members, taken from the maxima of 256 groups of samples (two of the oldest
+// in one group put the threshold one place deeper).
+constexpr int kPlanGroups = 4;  // groups per lane of the wave that searches
+
+// A threshold that at least k of the wave's kPlanGroups x 64 composites reach:
+// the k-th largest high word, with the low word resolved only where so many
+// share that high word that it would let too many through; 1 (everything) when
+// fewer than k are nonzero.
+__device__ uint64_t wave_threshold(const uint64_t* x, int k) {
+  uint32_t hi = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = hi | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < kPlanGroups; ++e) c += (int)__popcll(__ballot((uint32_t)(x[e] >> 32) >= cand));
+    if (c >= k) hi = cand;
+  }
+  if (hi == 0) return 1ull;
+  int above = 0, same = 0;
+#pragma unroll
+  for (int e = 0; e < kPlanGroups; ++e) {
+    above += (int)__popcll(__ballot((uint32_t)(x[e] >> 32) > hi));
+    same += (int)__popcll(__ballot((uint32_t)(x[e] >> 32) == hi));
+  }
+  // (the pool may hold far more of an equal arrival than the groups show)
+  if (same == 1) return (uint64_t)hi << 32;
+  uint32_t lo = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = lo | (1u << bit);
+    int c = above;
+#pragma unroll
+    for (int e = 0; e < kPlanGroups; ++e)
+      c += (int)__popcll(__ballot((uint32_t)(x[e] >> 32) == hi && (uint32_t)x[e] >= cand));
+    if (c >= k) lo = cand;
+  }
+  return ((uint64_t)hi << 32) | lo;
+}
+
+__global__ __launch_bounds__(kBlock) void tac_reduce(const uint32_t* __restrict__ part_cnt,
+                                                     const uint64_t* __restrict__ part_head, int G,
+                                                     const int32_t* __restrict__ len,
+                                                     const float* __restrict__ arrival, float now,
+                                                     const ewsjf_queue_table* __restrict__ tab,
+                                                     const ewsjf_theta* __restrict__ theta, ewsjf_cost cost,
+                                                     uint32_t* cnt, uint64_t* head, float* score, Gather g) {
   __shared__ uint32_t sc[kReduceThreads / kWave];
   __shared__ uint64_t sh[kReduceThreads / kWave];
+  __shared__ uint64_t oldest[kBlock];
   const int q = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   if (q >= tab->k) return;  // uniform over the workgroup
   uint32_t c = 0;
   uint64_t h = ~0ull;
-  for (int w = tid; w < G; w += kReduceThreads) {
+  for (int w = tid; w < G; w += kBlock) {
     c += part_cnt[(size_t)q * G + w];
     const uint64_t x = part_head[(size_t)q * G + w];
     h = x < h ? x : h;
   }
   c = __ockl_wfred_add_u32(c);
   h = wave_min_u64(h);
-  if (lane == 0) {
+  if (lane == 0 && wv < kReduceThreads / kWave) {  // (the partials are at most one per thread of these)
     sc[wv] = c;
     sh[wv] = h;
   }
   __syncthreads();
-  if (tid == 0) {
-    for (int i = 1; i < kReduceThreads / kWave; ++i) {
-      c += sc[i];
-      h = sh[i] < h ? sh[i] : h;
-    }
+  c = sc[0];
+  h = sh[0];
+#pragma unroll
+  for (int i = 1; i < kReduceThreads / kWave; ++i) {
+    c += sc[i];
+    h = sh[i] < h ? sh[i] : h;
+  }
+  if (tid == kWave) {  // (not the wave that searches below)
     cnt[q] = c;
     head[q] = h;
     float s = __builtin_nanf("");
@@ -197,6 +332,46 @@ __global__ __launch_bounds__(kReduceThreads) void tac_reduce(const uint32_t* __r
       s = head_phi(len[id], arrival[id], now, q, tab->mean[q], theta[0], cost);
     }
     score[q] = s;
+  }
+  if (g.rank == 0) return;  // uniform
+  if (c <= (uint32_t)kMergeCap) {  // uniform: all of them fit the list
+    if (tid == 0) g.tau[q] = 1ull;
+    return;
+  }
+  // The largest composite (the oldest) of this queue among each thread's
+  // samples, neighbours in the pool in different threads.
+  uint64_t best = 0;
+  const i32x4* kv = reinterpret_cast<const i32x4*>(g.skey);
+  const i32x4* qv = reinterpret_cast<const i32x4*>(g.sq);
+  for (int v = tid; v < (1 << g.lg_p); v += kBlock) {
+    const i32x4 sq = qv[v];
+    i32x4 key[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) key[u] = kv[4 * v + u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int s = v + ((4 * u + e) << g.lg_p);
+        if (s < g.n && (int)(((uint32_t)sq[u] >> (8 * e)) & 0xFFu) == q && key[u][e] != 0) {
+          const uint32_t i = (uint32_t)s >> 1;  // its chunk among the sampled ones
+          const uint32_t id = ((i << g.lg_step) * (uint32_t)kChunk) + sample_place(i) + 128u * ((uint32_t)s & 1u);
+          const uint64_t x = make_comp((uint32_t)key[u][e], id);
+          best = x > best ? x : best;
+        }
+      }
+  }
+  oldest[tid] = best;
+  __syncthreads();
+  if (wv == 0) {
+    uint64_t m[kPlanGroups] = {};
+#pragma unroll
+    for (int e = 0; e < kWavesPerBlock; ++e) {
+      const uint64_t o = oldest[e * kWave + lane];
+      m[e % kPlanGroups] = o > m[e % kPlanGroups] ? o : m[e % kPlanGroups];
+    }
+    const uint64_t tau = wave_threshold(m, g.rank);
+    if (lane == 0) g.tau[q] = tau;
   }
 }
 
@@ -207,15 +382,20 @@ __global__ __launch_bounds__(EWSJF_MAX_QUEUES) void tac_plan(const ewsjf_queue_t
                                                              const uint32_t* __restrict__ cnt,
                                                              const float* __restrict__ score, int32_t B,
                                                              int32_t empty_threshold, int32_t* empty_cnt,
-                                                             TacticalPlan* plan, int32_t* q_prim, float* head_score) {
+                                                             TacticalPlan* plan, int32_t* q_prim, float* head_score, Gather g) {
   __shared__ uint64_t wbest[EWSJF_MAX_QUEUES / kWave];
   __shared__ int nmark[EWSJF_MAX_QUEUES / kWave];
+  __shared__ uint32_t qcnt[EWSJF_MAX_QUEUES];
+  __shared__ float qscore[EWSJF_MAX_QUEUES];
   const int q = threadIdx.x, lane = q & (kWave - 1), wv = q / kWave;
   const int k = tab->k;
   const bool live = q < k;
   const uint32_t c = live ? cnt[q] : 0u;
   const float s = live ? score[q] : __builtin_nanf("");
   bool mark = false;
+  qcnt[q] = c;
+  qscore[q] = s;
+  if (q < kTacticalRows) g.count[q] = 0;  // tac_gather's
   if (live) {
     const int ec = c > 0 ? 0 : empty_cnt[q] + 1;
     empty_cnt[q] = ec;
@@ -251,20 +431,20 @@ __global__ __launch_bounds__(EWSJF_MAX_QUEUES) void tac_plan(const ewsjf_queue_t
       const int prim = p.q_prim;
       p.q_sel[0] = prim;
       int64_t left = B;
-      const int64_t t0 = (int64_t)cnt[prim] < left ? (int64_t)cnt[prim] : left;
+      const int64_t t0 = (int64_t)qcnt[prim] < left ? (int64_t)qcnt[prim] : left;
       p.take[0] = (int)t0;
       left -= t0;
       // Backfill: the non-empty neighbours, higher head score first.
       int nb[2], nn = 0;
-      if (prim > 0 && cnt[prim - 1] > 0) nb[nn++] = prim - 1;
-      if (prim + 1 < k && cnt[prim + 1] > 0) nb[nn++] = prim + 1;
-      if (nn == 2 && score[nb[1]] > score[nb[0]]) {
+      if (prim > 0 && qcnt[prim - 1] > 0) nb[nn++] = prim - 1;
+      if (prim + 1 < k && qcnt[prim + 1] > 0) nb[nn++] = prim + 1;
+      if (nn == 2 && qscore[nb[1]] > qscore[nb[0]]) {
         const int x = nb[0];
         nb[0] = nb[1];
         nb[1] = x;
       }
       for (int i = 0; i < nn; ++i) {
-        const int64_t ti = (int64_t)cnt[nb[i]] < left ? (int64_t)cnt[nb[i]] : left;
+        const int64_t ti = (int64_t)qcnt[nb[i]] < left ? (int64_t)qcnt[nb[i]] : left;
         p.q_sel[1 + i] = nb[i];
         p.take[1 + i] = (int)ti;
         left -= ti;
@@ -274,6 +454,123 @@ __global__ __launch_bounds__(EWSJF_MAX_QUEUES) void tac_plan(const ewsjf_queue_t
     *q_prim = p.q_prim;
   }
 }
+
+// ---------------------------------------------------------------------------
+// The members of the plan's queues at or above their thresholds, one pass over
+// the pool (four chunks in flight).  4M requests: 10.9 us (3.1 TB/s), and
+// tac_finish orders the 2,000 to 4,500 members in 5 us more than it took; the
+// lists of local_candidates took 16.9 us and their merge 24 to 40 us, since the
+// oldest of a queue sit together in a pool in arrival order.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__ len, const float* __restrict__ arrival,
+                                                     int64_t n, const ewsjf_queue_table* __restrict__ tab, int G,
+                                                     const TacticalPlan* __restrict__ plan, Gather g) {
+  __shared__ uint64_t route[kRouteWords];
+  __shared__ uint64_t out[kTacticalRows][kGatherLds];
+  __shared__ int nout[kTacticalRows], base[kTacticalRows];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const i32x4* lsrc = reinterpret_cast<const i32x4*>(tab->route);
+  for (int i = tid; i < kRouteWords / 2; i += kBlock) reinterpret_cast<i32x4*>(route)[i] = lsrc[i];
+  const int L = tab->max_len;
+  int qs[kTacticalRows];
+  uint64_t tau[kTacticalRows];
+#pragma unroll
+  for (int r = 0; r < kTacticalRows; ++r) {
+    qs[r] = plan->take[r] > 0 ? plan->q_sel[r] : -2;  // no request's queue
+    tau[r] = qs[r] >= 0 ? g.tau[qs[r]] : ~0ull;
+  }
+  if (tid < kTacticalRows) nout[tid] = 0;
+  __syncthreads();
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  for (int64_t lc0 = wv;; lc0 += 4 * kWavesPerBlock) {
+    const int64_t c0 = (int64_t)blockIdx.x + (int64_t)G * lc0;
+    if (c0 >= nchunks) break;
+    i32x4 l[4], a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {  // chunks past the end read zeros
+      const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
+      l[j] = chunk_load_i32x4(chunk_rsrc(len + first, n - first), lane);
+      a[j] = chunk_load_i32x4(chunk_rsrc(arrival + first, n - first), lane);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
+      if (first >= n) break;  // uniform
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int b = l[j][e];
+        const int q = b > 0 ? route_queue(route, min(b, L)) : -1;
+        const uint64_t x = make_comp(fifo_key(__int_as_float(a[j][e])), (uint32_t)(first + 4 * lane + e));
+        int row = -1;
+#pragma unroll
+        for (int r = 0; r < kTacticalRows; ++r) row = q == qs[r] && x >= tau[r] ? r : row;  // the rows' queues differ
+        if (__ballot(row >= 0) != 0ull) {
+          for (int r = 0; r < kTacticalRows; ++r) {
+            const uint64_t m = __ballot(row == r);
+            if (m == 0ull) continue;
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&nout[r], (int)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);  // lane 0 (the whole wave is active)
+            if (row == r && at < kGatherLds) out[r][at] = x;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < kTacticalRows && nout[tid] > 0)  // too many: over the cap
+    base[tid] = atomicAdd(&g.count[tid], nout[tid] <= kGatherLds ? nout[tid] : kMergeCap + 1);
+  __syncthreads();
+  for (int r = 0; r < kTacticalRows; ++r) {
+    const int c = nout[r];
+    if (c > kGatherLds) continue;
+    for (int i = tid; i < c; i += kBlock)
+      if (base[r] + i < kMergeCap) g.list[(size_t)r * kMergeCap + base[r] + i] = out[r][i];
+  }
+}
+
+// The oldest `take` of row r into ms.X, oldest first, by the whole block.  The
+// listed members when there are enough of them and all are listed (always,
+// but for about one call in a million); otherwise the whole pool, sixteen
+// chunks at a time (slow, exact).
+__device__ void oldest_of_row(MergeShared& ms, const Gather& g, int r, int queue, int take, const int32_t* len,
+                              const float* arrival, int64_t n, const ewsjf_queue_table* tab) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int U = g.count[r];
+  if (U >= take && U <= kMergeCap) {  // uniform
+    constexpr int kR = (kMergeCap + kBlock - 1) / kBlock;
+    uint64_t v[kR];
+#pragma unroll
+    for (int i = 0; i < kR; ++i) v[i] = tid + i * kBlock < U ? g.list[(size_t)r * kMergeCap + tid + i * kBlock] : 0ull;
+    uint64_t unused;
+    rank_registers(ms, v, U, take, 0ull, &unused);
+    return;
+  }
+  const int L = tab->max_len;
+  const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  int have = 0;
+  uint64_t low = 1ull;
+  for (int64_t c0 = 0; c0 < nchunks; c0 += kWavesPerBlock) {
+    if (tid == 0) ms.cntS = 0;
+    __syncthreads();
+    const int64_t first = (c0 + wv) * kChunk;
+    const i32x4 l = chunk_load_i32x4(chunk_rsrc(len + first, n - first), lane);
+    const i32x4 a = chunk_load_i32x4(chunk_rsrc(arrival + first, n - first), lane);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int b = l[e];
+      if (b > 0 && route_queue(tab->route, min(b, L)) == queue) {
+        const uint64_t x = make_comp(fifo_key(__int_as_float(a[e])), (uint32_t)(first + 4 * lane + e));
+        if (x >= low) ms.S[atomicAdd(&ms.cntS, 1)] = x;  // at most kSortMax a round
+      }
+    }
+    __syncthreads();
+    have = merge_new(ms, have, ms.cntS, take);
+    __syncthreads();
+    low = have >= take ? ms.X[take - 1] : 1ull;
+  }
+}
+
 
 // ---------------------------------------------------------------------------
 // The batch, tombstones, and queue removal.
@@ -293,7 +590,9 @@ __global__ __launch_bounds__(kBlock) void tac_finish(const TacticalPlan* __restr
                                                      int32_t* tomb_len, int32_t* ids, int32_t* n_sel,
                                                      ewsjf_queue_table* tab, const uint32_t* __restrict__ cnt,
                                                      int32_t empty_threshold, int32_t* empty_cnt, double eps,
-                                                     int32_t* removed) {
+                                                     int32_t* removed, Gather g, const int32_t* len,
+                                                     const float* arrival, int64_t n) {
+  __shared__ MergeShared ms;
   __shared__ int64_t qn[EWSJF_MAX_QUEUES], qS[EWSJF_MAX_QUEUES];
   __shared__ int32_t qlo[EWSJF_MAX_QUEUES], qhi[EWSJF_MAX_QUEUES], qec[EWSJF_MAX_QUEUES], qorig[EWSJF_MAX_QUEUES];
   __shared__ int32_t qb[EWSJF_MAX_QUEUES];  // bounds: qb[i] separates queues i and i + 1
@@ -302,13 +601,32 @@ __global__ __launch_bounds__(kBlock) void tac_finish(const TacticalPlan* __restr
   const int tid = threadIdx.x;
   const TacticalPlan p = *plan;
   const int t0 = p.take[0], t1 = p.take[1], t2 = p.take[2];
-  for (int r = tid; r < B; r += kBlock) {
-    int id = -1;
-    if (r < t0) id = row_ids[r];
-    else if (r < t0 + t1) id = row_ids[B + (r - t0)];
-    else if (r < t0 + t1 + t2) id = row_ids[2 * B + (r - t0 - t1)];
-    ids[r] = id;
-    if (tomb_len != nullptr && id >= 0) tomb_len[id] = 0;
+  if (g.rank > 0) {
+    int at = 0;
+    for (int r = 0; r < kTacticalRows; ++r) {
+      const int take = p.take[r];
+      if (take == 0) continue;  // uniform
+      oldest_of_row(ms, g, r, p.q_sel[r], take, len, arrival, n, tab);
+      for (int i = tid; i < take; i += kBlock) ids[at + i] = (int32_t)comp_id(ms.X[i]);
+      at += take;
+      __syncthreads();
+    }
+    for (int i = at + tid; i < B; i += kBlock) ids[i] = -1;
+    // (emptied only once no row can read the pool any more)
+    if (tomb_len != nullptr) {
+      __threadfence_block();
+      __syncthreads();
+      for (int i = tid; i < at; i += kBlock) tomb_len[ids[i]] = 0;
+    }
+  } else {
+    for (int r = tid; r < B; r += kBlock) {
+      int id = -1;
+      if (r < t0) id = row_ids[r];
+      else if (r < t0 + t1) id = row_ids[B + (r - t0)];
+      else if (r < t0 + t1 + t2) id = row_ids[2 * B + (r - t0 - t1)];
+      ids[r] = id;
+      if (tomb_len != nullptr && id >= 0) tomb_len[id] = 0;
+    }
   }
   if (tid == 0) *n_sel = t0 + t1 + t2;
   const int k = p.k;
@@ -395,20 +713,25 @@ hipError_t launch_tactical_step(int32_t* len, const float* arrival, int64_t n, f
   TacWs w;
   carve_tac(n, B, ws, &w);
   const int G = scan_grid(n);
-  hipLaunchKernelGGL(tac_scan, dim3(G), dim3(kBlock), 0, stream, len, arrival, n, table, G, w.part_cnt, w.part_head);
+  hipLaunchKernelGGL(tac_scan, dim3(G), dim3(kBlock), 0, stream, len, arrival, n, table, G, w.part_cnt, w.part_head,
+                     w.g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(tac_reduce, dim3(EWSJF_MAX_QUEUES), dim3(kReduceThreads), 0, stream, w.part_cnt, w.part_head, G,
-                     len, arrival, now, table, theta, cost, w.cnt, w.head, w.score);
+  hipLaunchKernelGGL(tac_reduce, dim3(EWSJF_MAX_QUEUES), dim3(w.g.rank > 0 ? kBlock : kReduceThreads), 0, stream,
+                     w.part_cnt, w.part_head, G, len, arrival, now, table, theta, cost, w.cnt, w.head, w.score, w.g);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(tac_plan, dim3(1), dim3(EWSJF_MAX_QUEUES), 0, stream, table, w.cnt, w.score, B, empty_threshold,
-                     empty_cnt, w.plan, q_prim, head_score);
+                     empty_cnt, w.plan, q_prim, head_score, w.g);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_fifo_select(len, arrival, n, table, w.plan, B, w.row_ids, w.row_top, w.row_n, w.select_ws,
-                              stream)) != hipSuccess)
+  if (w.g.rank > 0) {
+    hipLaunchKernelGGL(tac_gather, dim3(G), dim3(kBlock), 0, stream, len, arrival, n, table, G, w.plan, w.g);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  } else if ((e = launch_fifo_select(len, arrival, n, table, w.plan, B, w.row_ids, w.row_top, w.row_n, w.select_ws,
+                                     stream)) != hipSuccess) {
     return e;
+  }
   hipLaunchKernelGGL(tac_finish, dim3(1), dim3(kBlock), 0, stream, w.plan, w.row_ids, B, tomb_len, ids, n_sel, table,
-                     w.cnt, empty_threshold, empty_cnt, eps, removed);
+                     w.cnt, empty_threshold, empty_cnt, eps, removed, w.g, len, arrival, n);
   return hipGetLastError();
 }
 
