@@ -15,8 +15,8 @@
 //                               at or above it, tac_finish orders them.
 //                               Otherwise local_candidates /
 //                               merge_candidates with FifoSource.
-//   tac_finish  (1 workgroup)   the batch in order, tombstones, and the
-//                               removal of queues empty past the threshold
+//   tac_finish  (1 workgroup,   the batch in order, tombstones, and the
+//                a row each)    removal of queues empty past the threshold
 //                               (re-absorbed by the neighbour of lower Eq. 3
 //                               utility), with the routing lut rebuilt.
 //
@@ -44,7 +44,7 @@ constexpr int kReduceThreads = 256;
 constexpr int kCountCopies = 8;        // of each queue's counter in tac_scan, by lane
 constexpr int kSampledChunks = 65536;  // at most, two requests of each
 constexpr int kSampleMax = 2 * kSampledChunks;
-constexpr int kGatherLds = 2048;       // members of one row that one workgroup of tac_gather holds
+constexpr int kGatherLds = 4096;       // members of one row that one workgroup of tac_gather holds
 
 // The oldest members of the plan's queues by an age threshold.
 struct Gather {
@@ -75,9 +75,13 @@ struct TacWs {
   void* select_ws;
 };
 
+// One chunk per wave up to 1M requests, so that small pools use many compute
+// units and one workgroup's share (4,096 requests there) always fits
+// tac_gather's lists: 1M requests 37 / 35 us a step (random / arrival order)
+// with four chunks per wave, 33 / 31 with one.
 int scan_grid(int64_t n) {
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
-  int64_t G = (nchunks + 4 * kWavesPerBlock - 1) / (4 * kWavesPerBlock);
+  int64_t G = (nchunks + kWavesPerBlock - 1) / kWavesPerBlock;
   if (G < 1) G = 1;
   if (G > kMaxGrid) G = kMaxGrid;
   return (int)G;
@@ -103,9 +107,9 @@ int sample_step(int64_t n) {
 // workgroup's list with five standard deviations to spare (B up to about 1,500
 // for pools up to 16M), unless every queue fits it anyway.  Measured (us a step,
 // random / arrival order, gathered against local_candidates and
-// merge_candidates with FifoSource): 32 / 35 against 54 / 39 at 4,096 requests
-// and B = 64, 36 / 33 against 55 / 60 at 65,536 and 64, 37 / 36 against 42 / 84
-// at 1M and 1,024, 57 / 57 against 61 / 105 at 8M and 256.
+// merge_candidates with FifoSource): 27 / 27 against 54 / 39 at 4,096 requests
+// and B = 64, 29 / 29 against 55 / 60 at 65,536 and 64, 34 / 31 against 42 / 84
+// at 1M and 1,024, 56 / 56 against 61 / 105 at 8M and 256.
 int gather_rank(int64_t n, int32_t B) {
   const double density = 2.0 / ((double)kChunk * (double)(1 << sample_step(n)));
   const double mean = B * density;
@@ -139,7 +143,7 @@ size_t carve_tac(int64_t n, int32_t B, void* ws, TacWs* w) {
   t.g.list = reinterpret_cast<uint64_t*>(take((size_t)kTacticalRows * kMergeCap * sizeof(uint64_t)));
   t.g.lg_step = sample_step(n);
   t.g.n = 2 * (int)(((n + kChunk - 1) / kChunk + (1ll << t.g.lg_step) - 1) >> t.g.lg_step);
-  t.g.lg_p = 0;
+  t.g.lg_p = 10;  // at least one vector per thread: few samples are few per thread
   while ((16 << t.g.lg_p) < t.g.n) ++t.g.lg_p;
   t.g.rank = gather_rank(n, B);
   t.select_ws = take(plan_select(n, kTacticalRows, B).ws_bytes);
@@ -529,15 +533,21 @@ __global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__
   }
 }
 
-// The oldest `take` of row r into ms.X, oldest first, by the whole block.  The
-// listed members when there are enough of them and all are listed (always,
-// but for about one call in a million); otherwise the whole pool, sixteen
-// chunks at a time (slow, exact).
+// Whether row r's listed members hold its oldest `take`: always, but for about
+// one call in a million.
+__device__ __forceinline__ bool row_listed(const Gather& g, int r, int take) {
+  const int U = g.count[r];
+  return U >= take && U <= kMergeCap;
+}
+
+// The oldest `take` of row r into ms.X, oldest first, by the whole block: from
+// the listed members, or (slow, exact) from the whole pool, sixteen chunks at a
+// time.
 __device__ void oldest_of_row(MergeShared& ms, const Gather& g, int r, int queue, int take, const int32_t* len,
                               const float* arrival, int64_t n, const ewsjf_queue_table* tab) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  const int U = g.count[r];
-  if (U >= take && U <= kMergeCap) {  // uniform
+  if (row_listed(g, r, take)) {  // uniform
+    const int U = g.count[r];
     constexpr int kR = (kMergeCap + kBlock - 1) / kBlock;
     uint64_t v[kR];
 #pragma unroll
@@ -602,22 +612,25 @@ __global__ __launch_bounds__(kBlock) void tac_finish(const TacticalPlan* __restr
   const TacticalPlan p = *plan;
   const int t0 = p.take[0], t1 = p.take[1], t2 = p.take[2];
   if (g.rank > 0) {
+    // A workgroup per row; the first goes on.  Rows that need the whole pool are
+    // all taken by the first, which rewrites the table only afterwards.
     int at = 0;
     for (int r = 0; r < kTacticalRows; ++r) {
       const int take = p.take[r];
-      if (take == 0) continue;  // uniform
-      oldest_of_row(ms, g, r, p.q_sel[r], take, len, arrival, n, tab);
-      for (int i = tid; i < take; i += kBlock) ids[at + i] = (int32_t)comp_id(ms.X[i]);
+      const int owner = r > 0 && row_listed(g, r, take) ? r : 0;
+      if (take > 0 && (int)blockIdx.x == owner) {  // uniform
+        oldest_of_row(ms, g, r, p.q_sel[r], take, len, arrival, n, tab);
+        for (int i = tid; i < take; i += kBlock) {
+          const int id = (int)comp_id(ms.X[i]);
+          ids[at + i] = id;
+          if (tomb_len != nullptr) tomb_len[id] = 0;  // (no member of another row's queue)
+        }
+        __syncthreads();
+      }
       at += take;
-      __syncthreads();
     }
+    if (blockIdx.x > 0) return;
     for (int i = at + tid; i < B; i += kBlock) ids[i] = -1;
-    // (emptied only once no row can read the pool any more)
-    if (tomb_len != nullptr) {
-      __threadfence_block();
-      __syncthreads();
-      for (int i = tid; i < at; i += kBlock) tomb_len[ids[i]] = 0;
-    }
   } else {
     for (int r = tid; r < B; r += kBlock) {
       int id = -1;
@@ -730,7 +743,7 @@ hipError_t launch_tactical_step(int32_t* len, const float* arrival, int64_t n, f
                                      stream)) != hipSuccess) {
     return e;
   }
-  hipLaunchKernelGGL(tac_finish, dim3(1), dim3(kBlock), 0, stream, w.plan, w.row_ids, B, tomb_len, ids, n_sel, table,
+  hipLaunchKernelGGL(tac_finish, dim3(w.g.rank > 0 ? kTacticalRows : 1), dim3(kBlock), 0, stream, w.plan, w.row_ids, B, tomb_len, ids, n_sel, table,
                      w.cnt, empty_threshold, empty_cnt, eps, removed, w.g, len, arrival, n);
   return hipGetLastError();
 }
