@@ -5,12 +5,15 @@
 //  local_candidates  (grid = G x n_theta workgroups of 1024 threads)
 //    Each workgroup owns the 256-request chunks c with c % G == blockIdx.x, so
 //    a run of old (high-scoring) requests with neighbouring ids is spread over
-//    many workgroups.  Each lane holds 16 requests' 64-bit composite keys in
-//    registers.  Every wave takes the m-th largest lane maximum as its bar,
-//    the workgroup the largest bar t; every element with key >= t goes to an
-//    LDS list, which is ranked and cut to its M largest entries.  The workgroup
+//    many workgroups.  Each lane holds up to 16 requests' keys in registers.
+//    Every wave takes the m-th largest lane maximum as its bar; every element
+//    at or above the workgroup's bound (its second largest bar) goes to an LDS
+//    list, which is ranked and cut to its M largest entries.  The workgroup
 //    writes the list and a completeness bound T: every element of its share
-//    whose composite is >= T is in the list.
+//    whose composite is >= T is in the list.  Shares of more than one pass go
+//    through local_stream, queue-order rows through local_clustered; a pool
+//    that one workgroup holds goes through select_small, in one launch; many
+//    vectors over one pool share a filter (theta_threshold and after).
 //
 //  merge_candidates  (grid = n_theta workgroups of 1024 threads)
 //    Loads all lists into LDS and selects the exact top-B of their union.  If
@@ -635,10 +638,10 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
 // The closing of a workgroup's list (every wave's region holds every element
 // of the wave at or above its bar): the bound, the entries at or above it in
 // list2, and the publication.  bar_l: wave (lane mod 16)'s bar; reg_l: this
-// wave's region entry `lane` (valid below wcnt).  kKeys && keys_held: key holds
-// all keys of the share (a single pass).
-template <bool kKeys>
-__device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, bool keys_held, int wcnt, uint32_t bar_l,
+// wave's region entry `lane` (valid below wcnt).  kKeys: the keys per lane that
+// `key` holds, all of the share's (a single pass), or 0.
+template <int kKeys>
+__device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, int wcnt, uint32_t bar_l,
                                            uint64_t reg_l, int G, int M, size_t slot, const CandBufs& cb) {
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
   // The workgroup's bound would be the largest wave bar t1 (lane i < 16
@@ -653,7 +656,7 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
   const uint32_t t1 = wave_max_u32(b);
   const int v1 = (int)__builtin_ctzll(__ballot(lane < kWavesPerBlock && b == t1));
   const uint32_t t2 = wave_max_u32(lane != v1 ? b : 0u);
-  const bool lower = kKeys && keys_held && t2 != 0u && t2 < t1;  // uniform
+  const bool lower = kKeys > 0 && t2 != 0u && t2 < t1;  // uniform
   const uint32_t T_bar = lower ? t2 : t1;
   const uint64_t lowc = (uint64_t)T_bar << 32;
   const uint64_t x = lane < wcnt ? reg_l : 0ull;
@@ -665,11 +668,11 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
   // extra keys cost every wave a few instructions rather than one wave a
   // long serial run.
   uint32_t* const held = reinterpret_cast<uint32_t*>(ls.spill);
-  static_assert(kElemsPerLane == kWavesPerBlock && kElemsPerLane * kWave * 4 <= sizeof(ls.spill),
-                "one handed-over key per wave and lane");
+  static_assert(kKeys <= kWavesPerBlock && kKeys * kWave * 4 <= sizeof(ls.spill),
+                "at most one handed-over key per wave and lane");
   if (lower && wv == v1) {  // uniform
 #pragma unroll
-    for (int e = 0; e < kElemsPerLane; ++e) held[e * kWave + lane] = key[e];
+    for (int e = 0; e < kKeys; ++e) held[e * kWave + lane] = key[e];
   }
   __syncthreads();
   const int kc = lane < kWavesPerBlock ? ls.wkeep[lane] : 0;
@@ -677,7 +680,7 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
   const int nreg = __builtin_amdgcn_readlane(incl, kWavesPerBlock - 1);
   const int off = __builtin_amdgcn_readlane(incl - kc, wv);
   if (keep) ls.list2[off + lanes_below(km)] = x;  // nreg <= kListCap: at most kWave per wave
-  if (lower) {  // uniform
+  if (lower && wv < kKeys) {  // wave-uniform
     // Keys of wave v1 in [t2, t1) go after the regions' entries, in any
     // order (the list is ranked by value when published).
     const uint32_t k = held[wv * kWave + lane];
@@ -702,14 +705,151 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
   publish_list<false>(ls, total, lowc, M, slot, cb);
 }
 
-// Chunks each wave has in flight when it starts scoring (2, 3 or 4).
-constexpr int kAhead = 2;
-// Stage the table before the first pool load is issued.
-constexpr bool kTableFirst = false;
-static_assert(kAhead >= 2 && kAhead <= kChunksPerPass, "chunks in flight");
+// The k-th largest of the wave's N x 64 keys (0 when fewer are nonzero).
+template <int N>
+__device__ __forceinline__ uint32_t wave_kth_of(const uint32_t* key, int k) {
+  uint32_t prefix = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = prefix | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) c += (int)__popcll(__ballot(key[e] >= cand));
+    if (c >= k) prefix = cand;
+  }
+  return prefix;
+}
 
-template <class Src>
+// ---------------------------------------------------------------------------
+// Per-workgroup lists of a share that one pass holds in registers: kChunks
+// chunks per wave (1, 2 or 4), for the sources whose high keys do not cluster.
+//
+// Up to 1M requests a wave has one chunk, up to 2M two: with four chunks
+// whatever the share (empty ones read as zeros and were scored like any other)
+// the kernel took 9.2 us at 262,144 requests, 11.2 us on a 1M ring; it takes 5.8
+// and 7.2 us.  4M requests, four chunks per wave: 11.0 us (3.05 TB/s).
+// ---------------------------------------------------------------------------
+template <class Src, int kChunks>
 __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
+  static_assert(!Src::kClustered && kChunks <= kChunksPerPass, "one pass of a source without clusters");
+  constexpr int kKeys = 4 * kChunks;
+  constexpr int kBarChunks = kChunks < 3 ? kChunks : 3;  // the bar comes from these
+  constexpr int kAhead = kChunks < 2 ? kChunks : 2;      // chunks in flight when scoring starts
+  __shared__ typename Src::Shared sh;
+  __shared__ ListShared ls;
+  EWSJF_STAMP(kStampLocal, 0);
+  const int t = blockIdx.y;
+  const Src src = bind_theta(src0, t);
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+
+  // A wave stalls at a vector load while the compute unit's memory pipeline
+  // is full, so a wave that issued all of its loads before scoring would
+  // score only once nearly the whole stream had arrived.  Instead each wave
+  // keeps two chunks in flight and scores one chunk per chunk it issues.
+  // The tables go first (loaded by the first kStageWaves waves; the compute
+  // unit serves a workgroup's loads roughly in issue order, and the first
+  // barrier, which does not wait for them, puts every table load ahead of
+  // every pool load); the barrier before scoring then waits only for them and
+  // for the first chunks of every wave.
+  const bool stager = wv < kStageWaves;  // wave-uniform
+  typename Src::Stage st;
+  if (stager) src.stage_load(st, t);
+  __builtin_amdgcn_s_barrier();
+  typename Src::Raw raw[kChunks];
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) load_one(src, n, G, 0, j, raw[j]);
+  if (stager) src.stage_store(sh, st);
+  if (threadIdx.x == 0) {
+    ls.ovf = 0;
+    ls.nout = 0;
+  }
+  if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
+  __syncthreads();
+  EWSJF_STAMP(kStampLocal, 1);
+  const auto km = src.key_mode(sh);
+
+  uint64_t* const region = ls.list + wv * kWaveCap;
+  uint32_t key[kKeys];
+  uint32_t my_bar = 0;
+  sched_fence();
+#pragma unroll
+  for (int j = 0; j < kChunks; ++j) {
+    src.keys4(raw[j], sh, km, key + 4 * j);
+    if (j + 1 == kBarChunks) {
+      // The bar is ready while the last chunk is still in flight; every
+      // element (the last chunk's too) at or above it is written.
+      uint32_t lmax = 0;
+#pragma unroll
+      for (int e = 0; e < 4 * kBarChunks; ++e) lmax = key[e] > lmax ? key[e] : lmax;
+      my_bar = wave_group_bar(lmax, lg);
+    }
+    sched_fence();
+    if (j + kAhead < kChunks) load_one(src, n, G, 0, j + kAhead, raw[j + kAhead]);
+    sched_fence();
+  }
+  // Per element slot: one compare; the wave's mask of qualifying lanes gives
+  // each lane its position, and the wave-uniform count advances.
+  int wcnt = 0;
+  auto emit = [&](uint32_t thr) {
+#pragma unroll
+    for (int e = 0; e < kKeys; ++e) {
+      const bool p = key[e] >= thr;
+      const uint64_t sm = __ballot(p);
+      if (sm != 0ull) {
+        const int pos = wcnt + lanes_below(sm);
+        if (p && pos < kWaveCap)
+          region[pos] = make_comp(key[e], (uint32_t)(chunk_of(G, 0, e / 4) * kChunk + lane * 4 + (e & 3)));
+        wcnt += __popcll(sm);
+      }
+    }
+  };
+  emit(my_bar > 1u ? my_bar : 1u);
+  if (wcnt > kWaveCap) {
+    // Too many for the wave's region: raise the bar just above the
+    // kWaveCap-th largest key, so fewer qualify, and emit again.  Only equal
+    // keys can still overflow (then the list is marked incomplete and the
+    // merge re-reads the share).
+    const uint32_t kth = wave_kth_of<kKeys>(key, kWaveCap);
+    if (kth != 0xFFFFFFFFu) {
+      my_bar = kth + 1u > my_bar ? kth + 1u : my_bar;
+      wcnt = 0;
+      emit(my_bar);
+    }
+  }
+  EWSJF_STAMP(kStampLocal, 2);
+  if (lane == 0) {
+    ls.bar[wv] = my_bar;
+    if (wcnt > kWaveCap) ls.ovf = 1;
+  }
+  __syncthreads();
+  EWSJF_STAMP(kStampLocal, 3);
+
+  const size_t slot = (size_t)t * G + blockIdx.x;
+  // The overflow flag, the wave bars (lane i reads wave i's) and this wave's
+  // region entry are read together: one LDS round trip.
+  const int any_ovf = ls.ovf;
+  const uint32_t bar_l = ls.bar[lane & (kWavesPerBlock - 1)];
+  const uint64_t reg_l = region[lane];  // valid for lane < wcnt
+  if (any_ovf != 0) {
+    for (int i = threadIdx.x; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
+    if (threadIdx.x == 0) {
+      cb.counts[slot] = 0u;
+      cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
+      cb.bounds2[slot] = ~0ull;
+      cb.over_cnt[slot] = 0u;
+    }
+    EWSJF_STAMP_FLUSH(kStampLocal);
+    return;
+  }
+  close_list<kKeys>(ls, key, wcnt, bar_l, reg_l, G, M, slot, cb);
+  EWSJF_STAMP(kStampLocal, 5);
+  EWSJF_STAMP_FLUSH(kStampLocal);
+}
+
+// The lists of a source whose high keys cluster (the queue-order rows): passes
+// of four chunks per wave, two of them in flight, a spill list for full wave
+// regions and a lowered bound.
+template <class Src>
+__global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
   __shared__ typename Src::Shared sh;
   __shared__ ListShared ls;
   const int t = blockIdx.y;
@@ -753,28 +893,13 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
     static_assert(kListCap == kBlock, "one spill entry per thread");
     if constexpr (Src::kClustered) ls.spill[threadIdx.x] = 0ull;
   };
-  if constexpr (kTableFirst) {
-    // The table lands in LDS before any pool load is issued, and the only
-    // barrier before scoring comes first too: a wave stalls at a vector load
-    // while the compute unit's memory queue is full, so a barrier behind pool
-    // loads waits until most of them have been served.
-    if (stager) src.stage_store(sh, st);
-    init_list();
-    __syncthreads();
-    EWSJF_STAMP(kStampLocal, 1);
-    load_one(src, n, G, 0, 0, raw[0]);
-    load_one(src, n, G, 0, 1, raw[1]);
-    if constexpr (kAhead >= 3) load_one(src, n, G, 0, 2, raw[2]);
-    if constexpr (kAhead >= 4) load_one(src, n, G, 0, 3, raw[3]);
-  } else {
+  {
     // The compute unit serves a workgroup's loads roughly in issue order; this
     // barrier (which does not wait for the loads) puts every table load ahead
     // of every pool load.
     __builtin_amdgcn_s_barrier();
     load_one(src, n, G, 0, 0, raw[0]);
     load_one(src, n, G, 0, 1, raw[1]);
-    if constexpr (kAhead >= 3) load_one(src, n, G, 0, 2, raw[2]);
-    if constexpr (kAhead >= 4) load_one(src, n, G, 0, 3, raw[3]);
     if (stager) src.stage_store(sh, st);
     init_list();
     __syncthreads();
@@ -797,16 +922,15 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
     // A wave stalls at a load while the memory pipeline is full, so it
     // scores a chunk that has arrived before it issues the next load; the
     // other waves keep the pipeline full meanwhile.
-    // Chunk j >= kAhead is issued once chunk j - kAhead is scored.
+    // Chunk j >= 2 is issued once chunk j - 2 is scored.
     sched_fence();
     src.keys4(raw[0], sh, km, key + 0);
     sched_fence();
-    if constexpr (kAhead == 2) load_one(src, n, G, pass, 2, raw[2]);
-    if constexpr (kAhead == 3) load_one(src, n, G, pass, 3, raw[3]);
+    load_one(src, n, G, pass, 2, raw[2]);
     sched_fence();
     src.keys4(raw[1], sh, km, key + 4);
     sched_fence();
-    if constexpr (kAhead == 2) load_one(src, n, G, pass, 3, raw[3]);
+    load_one(src, n, G, pass, 3, raw[3]);
     sched_fence();
     src.keys4(raw[2], sh, km, key + 8);
     // The bar comes from the first three chunks, so it is ready while the
@@ -824,8 +948,6 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
     if (pass + 1 < passes) {
       load_one(src, n, G, pass + 1, 0, raw[0]);
       load_one(src, n, G, pass + 1, 1, raw[1]);
-      if constexpr (kAhead >= 3) load_one(src, n, G, pass + 1, 2, raw[2]);
-      if constexpr (kAhead >= 4) load_one(src, n, G, pass + 1, 3, raw[3]);
     }
     sched_fence();
     my_bar = bar > my_bar ? bar : my_bar;
@@ -919,12 +1041,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
   // Publish into the workgroup's M fixed slots (unused slots hold 0).
   const size_t slot = (size_t)t * G + blockIdx.x;
   uint64_t* out_list = cb.lists + slot * (size_t)M;
-  // The overflow flag, the wave bars (lane i reads wave i's) and this wave's
-  // region entry are read together: one LDS round trip.
-  const int any_ovf = ls.ovf;
-  const uint32_t bar_l = ls.bar[lane & (kWavesPerBlock - 1)];
-  const uint64_t reg_l = region[lane];  // the wave's region entry (valid for lane < wcnt)
-  if (any_ovf != 0) {
+  if (ls.ovf != 0) {
     for (int i = threadIdx.x; i < M; i += kBlock) out_list[i] = 0ull;
     if (threadIdx.x == 0) {
       cb.counts[slot] = 0u;
@@ -932,12 +1049,6 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
       cb.bounds2[slot] = ~0ull;
       cb.over_cnt[slot] = 0u;
     }
-    EWSJF_STAMP_FLUSH(kStampLocal);
-    return;
-  }
-  if constexpr (!Src::kClustered) {
-    close_list<true>(ls, key, passes == 1, wcnt, bar_l, reg_l, G, M, slot, cb);
-    EWSJF_STAMP(kStampLocal, 5);
     EWSJF_STAMP_FLUSH(kStampLocal);
     return;
   }
@@ -1037,20 +1148,6 @@ __device__ __forceinline__ uint32_t lds_peek(const uint32_t* p) {
 }
 __device__ __forceinline__ void lds_poke(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// The k-th largest of the wave's N x 64 keys (0 when fewer are nonzero).
-template <int N>
-__device__ __forceinline__ uint32_t wave_kth_of(const uint32_t* key, int k) {
-  uint32_t prefix = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = prefix | (1u << bit);
-    int c = 0;
-#pragma unroll
-    for (int e = 0; e < N; ++e) c += (int)__popcll(__ballot(key[e] >= cand));
-    if (c >= k) prefix = cand;
-  }
-  return prefix;
 }
 
 template <class Src>
@@ -1207,7 +1304,7 @@ __global__ __launch_bounds__(kBlock) void local_stream(Src src0, int64_t n, int 
     }
     return;
   }
-  close_list<false>(ls, nullptr, false, wcnt, bar_l, reg_l, G, M, slot, cb);
+  close_list<0>(ls, nullptr, wcnt, bar_l, reg_l, G, M, slot, cb);
 }
 
 // ---------------------------------------------------------------------------
@@ -2012,7 +2109,7 @@ template <class Src>
 static void launch_local(const SelectPlan& p, int rows, hipStream_t stream, hipEvent_t e0, hipEvent_t e1, const Src& src,
                          int64_t n, const CandBufs& cb) {
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
-  const bool one_pass = (nchunks + p.G - 1) / p.G <= kWavesPerBlock * kChunksPerPass;
+  const int64_t per_wave = (nchunks + (int64_t)p.G * kWavesPerBlock - 1) / ((int64_t)p.G * kWavesPerBlock);
   const dim3 grid(p.G, rows), block(kBlock);
   auto go = [&](auto kern) {
     if (e0 != nullptr)
@@ -2020,7 +2117,9 @@ static void launch_local(const SelectPlan& p, int rows, hipStream_t stream, hipE
     else
       hipLaunchKernelGGL(kern, grid, block, 0, stream, src, n, p.G, p.lg, p.M, cb);
   };
-  if (one_pass) go(local_candidates<Src>);
+  if (per_wave <= 1) go(local_candidates<Src, 1>);
+  else if (per_wave <= 2) go(local_candidates<Src, 2>);
+  else if (per_wave <= kChunksPerPass) go(local_candidates<Src, kChunksPerPass>);
   else go(local_stream<Src>);
 }
 
@@ -2387,7 +2486,7 @@ hipError_t launch_fifo_select(const int32_t* len, const float* arrival, int64_t 
   src.arrival = arrival;
   src.table = table;
   src.plan = plan;
-  hipLaunchKernelGGL(local_candidates<FifoSource>, dim3(p.G, kTacticalRows), dim3(kBlock), 0, stream, src, n, p.G,
+  hipLaunchKernelGGL(local_clustered<FifoSource>, dim3(p.G, kTacticalRows), dim3(kBlock), 0, stream, src, n, p.G,
                      p.lg, p.M, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -13,7 +13,7 @@
 //                               sample, tac_reduce takes an age threshold per
 //                               queue from it, tac_gather lists the members
 //                               at or above it, tac_finish orders them.
-//                               Otherwise local_candidates /
+//                               Otherwise local_clustered /
 //                               merge_candidates with FifoSource.
 //   tac_finish  (1 workgroup,   the batch in order, tombstones, and the
 //                a row each)    removal of queues empty past the threshold
@@ -106,7 +106,7 @@ int sample_step(int64_t n) {
 // members at or above the threshold (rank / density of them) must fit a
 // workgroup's list with five standard deviations to spare (B up to about 1,500
 // for pools up to 16M), unless every queue fits it anyway.  Measured (us a step,
-// random / arrival order, gathered against local_candidates and
+// random / arrival order, gathered against local_clustered and
 // merge_candidates with FifoSource): 27 / 27 against 54 / 39 at 4,096 requests
 // and B = 64, 29 / 29 against 55 / 60 at 65,536 and 64, 34 / 31 against 42 / 84
 // at 1M and 1,024, 56 / 56 against 61 / 105 at 8M and 256.
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(EWSJF_MAX_QUEUES) void tac_plan(const ewsjf_queue_t
 // The members of the plan's queues at or above their thresholds, one pass over
 // the pool (four chunks in flight).  4M requests: 10.9 us (3.1 TB/s), and
 // tac_finish orders the 2,000 to 4,500 members in 5 us more than it took; the
-// lists of local_candidates took 16.9 us and their merge 24 to 40 us, since the
+// lists of local_clustered took 16.9 us and their merge 24 to 40 us, since the
 // oldest of a queue sit together in a pool in arrival order.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__ len, const float* __restrict__ arrival,
