@@ -226,11 +226,8 @@ ewsjf_status ewsjf_trial_step(int32_t* len, float* arrival, int64_t capacity, in
   const ewsjf_status ds = check_device();
   if (ds != EWSJF_OK) return ds;
   const auto* tab = static_cast<const ewsjf_queue_table*>(table);
-  const hipError_t e = ewsjf::launch_trial_select(len, arrival, capacity, n_pools, pos, new_len, new_arrival, n_new,
-                                                  now, tab, theta, *cost, B, ids, top, n_sel, ws, stream);
-  if (e != hipSuccess) return EWSJF_ERR_LAUNCH;
-  return launched(ewsjf::launch_trial_stats(len, arrival, capacity, n_pools, now, tab, B, ids, n_sel, stats,
-                                            queue_admits, stream));
+  return launched(ewsjf::launch_trial_select(len, arrival, capacity, n_pools, pos, new_len, new_arrival, n_new, now,
+                                             tab, theta, *cost, B, ids, top, n_sel, stats, queue_admits, ws, stream));
 }
 
 ewsjf_status ewsjf_trial_finish(const int32_t* len, const float* arrival, int64_t capacity, int32_t n_pools, float now,

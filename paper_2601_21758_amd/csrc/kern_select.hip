@@ -33,6 +33,7 @@
 #include "ewsjf_launch.h"
 #include "ewsjf_merge.h"
 #include "ewsjf_stamps.h"
+#include "ewsjf_trial.h"
 
 namespace ewsjf {
 
@@ -357,6 +358,8 @@ struct RingSource : PoolSource {
 // and every pool takes the same arrivals (bind_theta moves the pointers).
 struct TrialSource : RingSource {
   int64_t stride;
+  double* stats;          // [pools][EWSJF_TRIAL_STATS]
+  int64_t* queue_admits;  // [pools][EWSJF_MAX_QUEUES]
 };
 
 struct ScoreSource {
@@ -1785,10 +1788,11 @@ struct MergeLds {
   uint64_t sT2[kMaxGrid];
 };
 
-// The exact top-B of row t (one workgroup): the union of the lists, then the
+// The exact top-B of row t (one workgroup; the number selected, left in
+// lds.ms.X): the union of the lists, then the
 // recovery of shares whose lists could miss members of the top-B.
 template <class Src>
-__device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int B, const CandBufs& cb,
+__device__ int merge_exact(const Src& src0, int t, int64_t n, int G, int M, int B, const CandBufs& cb,
                             int32_t* __restrict__ ids, float* __restrict__ top, int32_t* __restrict__ n_sel,
                             int32_t* tomb_len, MergeLds<Src>& lds) {
   EWSJF_STAMP(kStampMergeExact, 0);
@@ -1806,7 +1810,7 @@ __device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int
     }
     if (tid == 0) n_sel[t] = 0;
     EWSJF_STAMP_FLUSH(kStampMergeExact);
-    return;
+    return 0;
   }
 
   // One round trip: every list slot (G x M, empty slots hold 0) and the
@@ -1944,9 +1948,11 @@ __device__ void merge_exact(const Src& src0, int t, int64_t n, int G, int M, int
     __syncthreads();
   }
 
-  publish_row(ms, U < B ? U : B, B, t, ids, top, n_sel, tomb_len);
+  const int sel = U < B ? U : B;
+  publish_row(ms, sel, B, t, ids, top, n_sel, tomb_len);
   EWSJF_STAMP(kStampMergeExact, 2);
   EWSJF_STAMP_FLUSH(kStampMergeExact);
+  return sel;  // the selected entries are ms.X[0..sel)
 }
 
 template <class Src>
@@ -1955,7 +1961,13 @@ __global__ __launch_bounds__(kBlock) void merge_candidates(Src src0, int64_t n, 
                                                            int32_t* n_sel, int32_t* tomb_len, const int32_t* only) {
   __shared__ MergeLds<Src> lds;
   if (only != nullptr && only[blockIdx.x] >= 0) return;  // uniform; only may be n_sel (each row reads its own entry first)
-  merge_exact(src0, (int)blockIdx.x, n, G, M, B, cb, ids, top, n_sel, tomb_len, lds);
+  const int t = (int)blockIdx.x;
+  const int sel = merge_exact(src0, t, n, G, M, B, cb, ids, top, n_sel, tomb_len, lds);
+  if constexpr (std::is_same_v<Src, TrialSource>) {
+    const TrialSource src = bind_theta(src0, t);
+    trial_account(lds.ms, sel, src.ring_len, src.ring_arrival, src.now, src.table, src.stats + (size_t)t * EWSJF_TRIAL_STATS,
+                  src.queue_admits + (size_t)t * EWSJF_MAX_QUEUES);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2447,7 +2459,8 @@ hipError_t launch_ring_step(int32_t* ring_len, float* ring_arrival, int64_t capa
 hipError_t launch_trial_select(int32_t* len, float* arrival, int64_t capacity, int32_t n_pools, int64_t pos,
                                const int32_t* new_len, const float* new_arrival, int64_t n_new, float now,
                                const ewsjf_queue_table* table, const ewsjf_theta* theta, const ewsjf_cost& cost,
-                               int32_t B, int32_t* ids, float* top, int32_t* n_sel, void* ws, hipStream_t stream) {
+                               int32_t B, int32_t* ids, float* top, int32_t* n_sel, double* stats,
+                               int64_t* queue_admits, void* ws, hipStream_t stream) {
   const SelectPlan p = plan_trial(capacity, n_pools, B);
   const CandBufs cb = carve(p, ws);
   TrialSource src;
@@ -2468,6 +2481,8 @@ hipError_t launch_trial_select(int32_t* len, float* arrival, int64_t capacity, i
   src.new_arrival = new_arrival;
   src.n_new = n_new;
   src.stride = capacity;
+  src.stats = stats;
+  src.queue_admits = queue_admits;
   launch_local(p, n_pools, stream, nullptr, nullptr, src, capacity, cb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -3,10 +3,11 @@
 // its own pool for a trial of several steps; these kernels keep the trial's
 // statistics (Eq. 5's reward is built from them at the end).
 //
-//   trial_stats_kernel    one workgroup per pool: wait, tokens and queue of
-//                         every admitted request, reduced in a fixed order
-//                         (the sums are deterministic), added to the pool's
-//                         statistics; then the admitted slots are emptied.
+//   trial_account         (ewsjf_trial.h, at the end of each pool's merge) wait,
+//                         tokens and queue of every admitted request, reduced
+//                         in a fixed order (the sums are deterministic), added
+//                         to the pool's statistics; then the admitted slots
+//                         are emptied.
 //   trial_pending_kernel  the pending requests at the trial's end: count and
 //                         largest wait (integer-valued adds and a maximum, so
 //                         the order of the atomics does not matter).
@@ -17,89 +18,11 @@
 
 #include "ewsjf_device.h"
 #include "ewsjf_launch.h"
+#include "ewsjf_trial.h"
 
 namespace ewsjf {
 
 namespace {
-
-constexpr int kStatThreads = 256;
-enum {
-  kAdmitted = 0,
-  kTokens,
-  kWaitSum,
-  kWaitSqSum,
-  kWaitMax,
-  kPending,
-  kPendingWaitMax,
-  kSteps,
-};
-static_assert(kSteps + 1 == EWSJF_TRIAL_STATS, "statistics layout");
-
-// Wait W = max(0, now - arrival) in binary64; a NaN arrival waits 0.
-__device__ __forceinline__ double wait_of(float now, float a) {
-  const double w = (double)now - (double)a;
-  return w > 0.0 ? w : 0.0;
-}
-
-__global__ __launch_bounds__(kStatThreads) void trial_stats_kernel(int32_t* __restrict__ len,
-                                                                   const float* __restrict__ arrival, int64_t cap,
-                                                                   float now, const ewsjf_queue_table* tab, int B,
-                                                                   const int32_t* __restrict__ ids,
-                                                                   const int32_t* __restrict__ n_sel,
-                                                                   double* __restrict__ stats,
-                                                                   int64_t* __restrict__ queue_admits) {
-  __shared__ uint32_t qc[EWSJF_MAX_QUEUES];
-  __shared__ double rw[kStatThreads], rw2[kStatThreads], rmax[kStatThreads];
-  __shared__ int64_t rtok[kStatThreads];
-  const int p = blockIdx.x, tid = threadIdx.x;
-  int32_t* L = len + (int64_t)p * cap;
-  const float* A = arrival + (int64_t)p * cap;
-  const int32_t* id = ids + (int64_t)p * B;
-  const int sel = n_sel[p];
-  const int k = tab->k, Lmax = tab->max_len;
-  for (int q = tid; q < EWSJF_MAX_QUEUES; q += kStatThreads) qc[q] = 0u;
-  __syncthreads();
-  double w1 = 0.0, w2 = 0.0, wm = 0.0;
-  int64_t tok = 0;
-  for (int r = tid; r < sel; r += kStatThreads) {
-    const int i = id[r];
-    const int b = L[i];  // admitted, so b >= 1
-    const double w = wait_of(now, A[i]);
-    w1 += w;
-    w2 += w * w;
-    wm = w > wm ? w : wm;
-    tok += b;
-    atomicAdd(&qc[tab->lut[b < Lmax ? b : Lmax]], 1u);
-  }
-  rw[tid] = w1;
-  rw2[tid] = w2;
-  rmax[tid] = wm;
-  rtok[tid] = tok;
-  __syncthreads();
-  for (int s = kStatThreads / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      rw[tid] += rw[tid + s];
-      rw2[tid] += rw2[tid + s];
-      rmax[tid] = rmax[tid + s] > rmax[tid] ? rmax[tid + s] : rmax[tid];
-      rtok[tid] += rtok[tid + s];
-    }
-    __syncthreads();
-  }
-  // every read of the admitted slots is done (barrier above): empty them
-  for (int r = tid; r < sel; r += kStatThreads) L[id[r]] = 0;
-  if (tid == 0) {
-    double* st = stats + (int64_t)p * EWSJF_TRIAL_STATS;
-    st[kAdmitted] += (double)sel;
-    st[kTokens] += (double)rtok[0];
-    st[kWaitSum] += rw[0];
-    st[kWaitSqSum] += rw2[0];
-    st[kWaitMax] = rmax[0] > st[kWaitMax] ? rmax[0] : st[kWaitMax];
-    st[kSteps] += 1.0;
-  }
-  int64_t* qa = queue_admits + (int64_t)p * EWSJF_MAX_QUEUES;
-  for (int q = tid; q < k; q += kStatThreads)
-    if (qc[q]) qa[q] += (int64_t)qc[q];
-}
 
 __global__ void trial_pending_reset(double* stats, int n_pools) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -176,14 +99,6 @@ __global__ __launch_bounds__(kStatThreads) void trial_reward_kernel(const ewsjf_
 }
 
 }  // namespace
-
-hipError_t launch_trial_stats(int32_t* len, const float* arrival, int64_t capacity, int32_t n_pools, float now,
-                              const ewsjf_queue_table* table, int32_t B, const int32_t* ids, const int32_t* n_sel,
-                              double* stats, int64_t* queue_admits, hipStream_t stream) {
-  hipLaunchKernelGGL(trial_stats_kernel, dim3(n_pools), dim3(kStatThreads), 0, stream, len, arrival, capacity, now,
-                     table, B, ids, n_sel, stats, queue_admits);
-  return hipGetLastError();
-}
 
 hipError_t launch_trial_finish(const int32_t* len, const float* arrival, int64_t capacity, int32_t n_pools,
                                float now, const ewsjf_queue_table* table, const int64_t* queue_admits,
