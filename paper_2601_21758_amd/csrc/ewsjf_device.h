@@ -213,20 +213,18 @@ __device__ __forceinline__ int block_exclusive_scan_n(int x, int* scratch, int* 
   return wave_base + incl - x;
 }
 
+// The same over the whole block.  Each wave combines the waves' sums itself,
+// one per lane: one LDS read and a scan rather than a read per wave.
 __device__ __forceinline__ int block_exclusive_scan(int x, int* scratch, int* total) {
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int incl = wave_incl_scan_add(x);
   if (lane == kWave - 1) scratch[wv] = incl;
   __syncthreads();
-  int wave_base = 0, sum = 0;
-#pragma unroll
-  for (int i = 0; i < kWavesPerBlock; ++i) {
-    const int si = scratch[i];
-    wave_base += i < wv ? si : 0;
-    sum += si;
-  }
+  const int si = lane < kWavesPerBlock ? scratch[lane] : 0;
+  const int sums = wave_incl_scan_add(si);
+  const int wave_base = __builtin_amdgcn_readlane(sums - si, wv);
+  *total = __builtin_amdgcn_readlane(sums, kWavesPerBlock - 1);
   __syncthreads();
-  *total = sum;
   return wave_base + incl - x;
 }
 

@@ -531,11 +531,11 @@ __device__ __forceinline__ uint64_t dbits(double x) { return (uint64_t)__double_
 // with the test itself; a level is then one compare per value against its
 // segment's threshold.  With the test evaluated for every gap a level took
 // 14 us (two conversions and two binary64 products per gap, 32 gaps per
-// thread whatever V), the kernel 78-87 us; it takes 36-51 us now.
+// thread whatever V), the kernel 78-87 us; it takes 34-46 us now, about 5 us a level.
 // ---------------------------------------------------------------------------
 constexpr int kGroups = EWSJF_MAX_LEN / kWave;  // 512
 constexpr int kNoCut = 0xFFFF;                  // above every gap
-constexpr int kGroupBatch = 4;                  // groups a wave has in flight
+constexpr int kGroupsPerWave = kGroups / kWavesPerBlock;  // 32: group wv + 16 u is wave wv's u-th
 
 struct RpShared {
   uint16_t v[EWSJF_MAX_LEN];
@@ -546,28 +546,29 @@ struct RpShared {
   int iscr[kWavesPerBlock];
 };
 
+// The value of lane `src` (uniform) of a 64-bit register.
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t x, int src) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, src);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), src);
+  return ((uint64_t)hi << 32) | lo;
+}
+
 // The segments' starts in order, sm.seg[0..nseg), from the start bits `mine`
 // of group tid (tid < kGroups, also in sm.start); returns nseg.
 __device__ int list_segments(RpShared& sm, uint64_t mine, int ng) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   int nseg = 0;
   const int before = block_exclusive_scan((int)__popcll(mine), sm.iscr, &nseg);
   if (tid < kGroups) sm.first[tid] = (uint16_t)before;  // below 32768 wherever the group has a start
   __syncthreads();
-  for (int g0 = wv; g0 < ng; g0 += kGroupBatch * kWavesPerBlock) {
-    uint64_t m[kGroupBatch];
-    int f[kGroupBatch];
-#pragma unroll
-    for (int u = 0; u < kGroupBatch; ++u) {
-      const int g = min(g0 + u * kWavesPerBlock, kGroups - 1);
-      m[u] = sm.start[g];
-      f[u] = sm.first[g];
-    }
-#pragma unroll
-    for (int u = 0; u < kGroupBatch; ++u) {
-      const int g = g0 + u * kWavesPerBlock;
-      if (g < ng && ((m[u] >> lane) & 1ull)) sm.seg[f[u] + lanes_below(m[u])] = (uint16_t)(g * kWave + lane);
-    }
+  const uint64_t gstart = lane < kGroupsPerWave ? sm.start[wv + lane * kWavesPerBlock] : 0ull;  // 0 past the groups in use
+  const int gfirst = lane < kGroupsPerWave ? (int)sm.first[wv + lane * kWavesPerBlock] : 0;
+  for (int u = 0; wv + u * kWavesPerBlock < ng; ++u) {
+    const uint64_t m = readlane_u64(gstart, u);  // in scalar registers, as the lane mask of the store
+    const int f = __builtin_amdgcn_readlane(gfirst, u);
+    if (__builtin_amdgcn_inverse_ballot_w64(m))
+      sm.seg[f + lanes_below(m)] = (uint16_t)((wv + u * kWavesPerBlock) * kWave + lane);
   }
   __syncthreads();
   return nseg;
@@ -605,7 +606,8 @@ __device__ void write_queues(ewsjf_queue_table* tab, int k, const int64_t* N, co
 __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partition_params p, int64_t n_window,
                                                           ewsjf_queue_table* tab) {
   __shared__ RpShared sm;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int V = w.meta[0];
   const int L = p.max_len;
   if (V == 0) {
@@ -625,14 +627,14 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
   }
 
   {
-    // Eight loads in flight per thread (bounded: past V they read 0).
+    // Sixteen loads in flight per thread (bounded: past V they read 0).
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(w.v, (short)0, V * 4, kBufferWord3);
-    for (int j0 = tid; j0 < V; j0 += 8 * kBlock) {
-      uint32_t x[8];
+    for (int j0 = tid; j0 < V; j0 += 16 * kBlock) {
+      uint32_t x[16];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, (j0 + k * kBlock) * 4, 0, 0);
+      for (int k = 0; k < 16; ++k) x[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, (j0 + k * kBlock) * 4, 0, 0);
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
+      for (int k = 0; k < 16; ++k)
         if (j0 + k * kBlock < V) sm.v[j0 + k * kBlock] = (uint16_t)x[k];
     }
   }
@@ -672,6 +674,15 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
   const int n_coarse = nl;
 
   // ---- Stage 2: level-synchronous refinement --------------------------------
+  // The gap after each value (0 past the last: never cut), lane l of group
+  // wv + 16 u in gap[u].
+  int gap[kGroupsPerWave];
+#pragma unroll
+  for (int u = 0; u < kGroupsPerWave; ++u) {
+    const int j = (wv + u * kWavesPerBlock) * kWave + lane;
+    gap[u] = 0;
+    if (wv + u * kWavesPerBlock < ng) gap[u] = (int)sm.v[min(j + 1, V - 1)] - (int)sm.v[min(j, V - 1)];
+  }
   const bool distinct = p.gap_mode == EWSJF_GAPS_DISTINCT;
   const int min_distinct = distinct ? 3 : 2;
   for (;;) {
@@ -690,22 +701,31 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
       if (i < nl) sm.seg[i] = (uint16_t)t;
     }
     __syncthreads();
-    // Every gap against its segment's threshold.
-    for (int g0 = wv; g0 < ng; g0 += kGroupBatch * kWavesPerBlock) {
-      int gap[kGroupBatch], thr[kGroupBatch];
+    // Every gap against its segment's threshold (one LDS read per gap: the
+    // gaps stay in registers and the groups' words come from other lanes).
+    {
+      const uint64_t gstart = lane < kGroupsPerWave ? sm.start[wv + lane * kWavesPerBlock] : 0ull;
+      const int gfirst = lane < kGroupsPerWave ? (int)sm.first[wv + lane * kWavesPerBlock] : 0;
+      uint64_t cuts = 0;  // lane u: the cuts of the wave's u-th group
 #pragma unroll
-      for (int u = 0; u < kGroupBatch; ++u) {
-        const int g = min(g0 + u * kWavesPerBlock, ng - 1);
-        const int j = g * kWave + lane;
-        gap[u] = (int)sm.v[min(j + 1, V - 1)] - (int)sm.v[min(j, V - 1)];  // 0 past the last value: never cut
-        const uint64_t upto = sm.start[g] & (~0ull >> (kWave - 1 - lane));
-        thr[u] = sm.seg[(int)sm.first[g] + (int)__popcll(upto) - 1];
-      }
+      for (int u0 = 0; u0 < kGroupsPerWave; u0 += 8) {
+        if (wv + u0 * kWavesPerBlock < ng) {  // uniform; eight reads in flight (groups past the last read its segment)
+          int thr[8];
 #pragma unroll
-      for (int u = 0; u < kGroupBatch; ++u) {
-        const uint64_t cm = __ballot(gap[u] > thr[u]);
-        if (lane == 0 && g0 + u * kWavesPerBlock < ng) sm.cut[g0 + u * kWavesPerBlock] = cm;
+          for (int k = 0; k < 8; ++k) {
+            // the starts up to this lane, this one included: bit 0 and the bits of m >> 1 below it
+            const uint64_t m = readlane_u64(gstart, u0 + k);
+            const int before = __builtin_amdgcn_readlane(gfirst, u0 + k) + (int)(m & 1ull) - 1;  // scalar
+            thr[k] = sm.seg[before + lanes_below(m >> 1)];
+          }
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const uint64_t cm = __ballot(gap[u0 + k] > thr[k]);
+            cuts = lane == u0 + k ? cm : cuts;
+          }
+        }
       }
+      if (lane < kGroupsPerWave) sm.cut[wv + lane * kWavesPerBlock] = cuts;
     }
     __syncthreads();
     // A cut gap starts a segment at the next value (a gap between two
@@ -732,8 +752,7 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
     w.gN[nl] = w.PN[V];
     w.gS[nl] = w.PS[V];
   }
-  __threadfence();
-  __syncthreads();
+  __syncthreads();  // (write_queues reads them back in this workgroup)
   if (tid == 0) {
     w.meta[3] = nl;
     tab->max_len = L;
@@ -767,9 +786,9 @@ __global__ __launch_bounds__(kBlock) void rp_refine_prune(PartWs w, ewsjf_partit
 // where another pair is the lowest are committed together.
 //
 // Measured (rp_merge alone): the 1M window of two modes into 256 queues
-// 50 us, where one merge at a time took 253 us; a 65,536 window into 64
-// queues 30 us against 363 us; the 262,144 window of three modes into 64
-// queues 22 us against 1,119 us.  One merge at a time (merge_list) is bound
+// 37 us, where one merge at a time took 253 us; a 65,536 window into 64
+// queues 24 us against 363 us; the 262,144 window of three modes into 64
+// queues 19 us against 1,119 us.  One merge at a time (merge_list) is bound
 // by latency, about 0.75 us each: two dependent divisions, two reductions
 // over the wave and three rounds of LDS reads.
 //
@@ -1008,9 +1027,11 @@ __device__ __forceinline__ uint64_t wave_incl_min_u64(uint64_t x) {
 
 // PM and SM from U[0..np), and st.x = the lowest pair, the leftmost of
 // equals.  The whole block; a tile of PM from the left and the mirrored tile
-// of SM from the right share their barriers.
+// of SM from the right share their barriers, and each wave combines the waves'
+// minima itself with one read and one scan.
 __device__ void chain_minima(const ChainArrays& c, int np, ChainState& st) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   uint64_t pc = kNoPair, sc = kNoPair;
   for (int t0 = 0; t0 < np; t0 += kBlock) {
     const int i = t0 + tid, j = np - 1 - i;
@@ -1021,21 +1042,25 @@ __device__ void chain_minima(const ChainArrays& c, int np, ChainState& st) {
       st.smin[wv] = sm;
     }
     __syncthreads();
-    uint64_t pb = pc, sb = sc;
-#pragma unroll
-    for (int q = 0; q < kWavesPerBlock; ++q) {
-      const uint64_t pq = st.pmin[q], sq = st.smin[q];
-      pb = min_u64(pb, q < wv ? pq : kNoPair);
-      sb = min_u64(sb, q < wv ? sq : kNoPair);
-      pc = min_u64(pc, pq);
-      sc = min_u64(sc, sq);
-    }
-    if (i < np) c.PM[i] = min_u64(pb, pm);
+    const bool pl = lane < kWavesPerBlock;
+    const uint64_t ps = wave_incl_min_u64(pl ? st.pmin[lane] : kNoPair);
+    const uint64_t ss = wave_incl_min_u64(pl ? st.smin[lane] : kNoPair);
+    const uint64_t pb = wv > 0 ? min_u64(pc, readlane_u64(ps, wv - 1)) : pc;  // before this wave
+    const uint64_t sb = wv > 0 ? min_u64(sc, readlane_u64(ss, wv - 1)) : sc;
+    pc = min_u64(pc, readlane_u64(ps, kWavesPerBlock - 1));
+    sc = min_u64(sc, readlane_u64(ss, kWavesPerBlock - 1));
+    const uint64_t here = min_u64(pb, pm);
+    if (i < np) c.PM[i] = here;
     if (j >= 0) c.SM[j] = min_u64(sb, sm);
+    if (np <= kBlock) {
+      // One tile: pc is the lowest utility; the first place where the running
+      // minimum reaches it.
+      const uint64_t m = __ballot(i < np && here == pc);
+      if (m != 0ull && pb != pc && lane == (int)__builtin_ctzll(m)) st.x = i;
+    }
     __syncthreads();
   }
-  // pc is the lowest utility: the first place where the running minimum
-  // reaches it.
+  if (np <= kBlock) return;
   for (int i = tid; i < np; i += kBlock)
     if (c.PM[i] == pc && (i == 0 || c.PM[i - 1] != pc)) st.x = i;
   __syncthreads();
@@ -1155,7 +1180,7 @@ __device__ int chain_merge(const ChainArrays& c, int nl, const ewsjf_partition_p
     const int x = st.x, d = st.y - x;
     m -= d;
     chain_compact(c, x, d, m, st);
-    // A new chain costs about 3 us (the scans and the move), merge_list 0.75 us
+    // A new chain costs about 2.5 us (the scans and the move), merge_list 0.75 us
     // a merge: chains pay from about four merges on.  Windows of the workloads
     // start with up to 20 short chains before their long one, so the first 32
     // are not judged; data without any chain loses about 0.1 ms here.
