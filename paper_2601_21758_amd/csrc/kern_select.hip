@@ -1987,11 +1987,14 @@ __global__ __launch_bounds__(kBlock) void merge_candidates(Src src0, int64_t n, 
 // same slots and bounds.
 // ---------------------------------------------------------------------------
 // Own slots per workgroup: 16 up to 4,096 slots in all, so that the workgroups
-// fill the chip; 32 above, because the exact merge's LDS admits one workgroup
-// per compute unit and 16 own slots each would take two rounds of them
-// (8,192 slots: 12.0 us, 7.4 us with 32).
-constexpr int kRankPer = 16, kRankPerMany = 32;
+// fill the chip; 32 up to 8,192 and 36 above, because the exact merge's LDS
+// admits one workgroup per compute unit and more than 256 of them would take
+// two rounds (8,192 slots: 12.0 us with 16 own slots, 7.4 us with 32; 8,960
+// slots: 8.3 us with 36, and a 1M step with B = 4,096 takes 16.4 us, 21.5 us
+// with 32).
+constexpr int kRankPer = 16, kRankPerMany = 32, kRankPerMost = 36;
 constexpr int kRankR = (kMergeCap + kBlock - 1) / kBlock;  // most slots per thread
+static_assert(kRankPerMost * 256 >= kMergeCap && kRankPerMost <= kWave, "one round of workgroups, a lane per own slot");
 
 // NR: slots per thread, a compile-time bound >= ceil(G M / kBlock).  PER: own
 // slots per workgroup.
@@ -2010,7 +2013,7 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
   const bool pl = lane < kWavesPerBlock;  // lane i reads wave i's partial
   const int GM = G * M;
-  const int p0 = (int)blockIdx.x * PER;
+  const int nwg = (int)gridDim.x;
 
   // One round trip: the slots (slot tid + r kBlock in v[r]; past GM reads 0),
   // the bounds and this workgroup's own slots.
@@ -2022,16 +2025,13 @@ __global__ __launch_bounds__(kBlock) void merge_rank(Src src, int64_t n, int G, 
     v[r] = ((uint64_t)w[1] << 32) | w[0];
   }
   const uint64_t bnd = tid < G ? cb.bounds[tid] : 0ull;
-  // Own slots: with M = PER and G a multiple of it, workgroup w takes
-  // entry k of list 16 (w / 16) + (w + k) % 16, one entry of each rank from
-  // 16 lists (a bijection on each group of 16 lists).  Lists hold their
-  // entries by rank, so every workgroup gets a similar number of slots at or
-  // above T to count, rather than all of one list's.
-  int os = p0 + tid;
-  if (M == PER && (G & (PER - 1)) == 0) {
-    const int w = (int)blockIdx.x;
-    os = ((w & ~(PER - 1)) | ((w + tid) & (PER - 1))) * M + tid;
-  }
+  // Own slots: slot k of every workgroup lies in the k-th run of nwg slots,
+  // rotated by k (nwg / PER + 1) places (a bijection on each run).  Lists hold
+  // their entries by rank, and the odd step takes a workgroup through all
+  // ranks, so every workgroup gets a similar number of slots at or above T to
+  // count, rather than all of one list's (262,144 requests, B = 1,024: a step
+  // takes 11.9 us with consecutive slots, 11.7 us with these).
+  const int os = tid * nwg + ((int)blockIdx.x + tid * (nwg / PER + 1)) % nwg;
   const uint64_t own = tid < PER && os < GM ? cb.lists[os] : 0ull;
   if (tid < PER) {
     s_c[tid] = own;
@@ -2155,7 +2155,7 @@ static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_
                               int64_t n, int B, const CandBufs& cb, int32_t* ids, float* top, int32_t* n_sel,
                               int32_t* tomb_len) {
   const int nr = (p.G * p.M + kBlock - 1) / kBlock;
-  const int per = nr <= 4 ? kRankPer : kRankPerMany;
+  const int per = nr <= 4 ? kRankPer : nr <= 8 ? kRankPerMany : kRankPerMost;
   const dim3 grid((p.G * p.M + per - 1) / per), block(kBlock);
   auto go = [&](auto kern) {
     if (e0 != nullptr)
@@ -2168,7 +2168,7 @@ static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_
   else if (nr <= 2) go(merge_rank<Src, 2, kRankPer>);
   else if (nr <= 4) go(merge_rank<Src, 4, kRankPer>);
   else if (nr <= 8) go(merge_rank<Src, 8, kRankPerMany>);
-  else go(merge_rank<Src, kRankR, kRankPerMany>);
+  else go(merge_rank<Src, kRankR, kRankPerMost>);
 }
 
 // ---------------------------------------------------------------------------
