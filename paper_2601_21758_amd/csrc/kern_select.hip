@@ -708,6 +708,33 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
   publish_list<false>(ls, total, lowc, M, slot, cb);
 }
 
+// A bar above `lo` that at most `cap` of the wave's N x 64 keys reach, `lo`
+// being one that more reach: halving between lo and the largest key, until
+// three quarters of cap or more reach it or no bar between is left.  Any bar is
+// valid, so the search need not find the cap-th key: some rounds of N ballots,
+// where its 32 bits took 32 (a step over 4M requests with B = 4,096, where a few
+// waves overflow: 28.9 us, 23.9 us with this search).
+template <int N>
+__device__ __forceinline__ uint32_t wave_bar_that_fits(const uint32_t* key, uint32_t lo, int cap) {
+  uint32_t hi = 0;
+#pragma unroll
+  for (int e = 0; e < N; ++e) hi = key[e] > hi ? key[e] : hi;
+  hi = wave_max_u32(hi) + 1u;  // keys are at most +inf's, 0xFF800000
+  while (hi - lo > 1u) {
+    const uint32_t mid = lo + (hi - lo) / 2u;
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) c += (int)__popcll(__ballot(key[e] >= mid));
+    if (c > cap) {
+      lo = mid;
+    } else {
+      hi = mid;
+      if (4 * c >= 3 * cap) break;
+    }
+  }
+  return hi;
+}
+
 // The k-th largest of the wave's N x 64 keys (0 when fewer are nonzero).
 template <int N>
 __device__ __forceinline__ uint32_t wave_kth_of(const uint32_t* key, int k) {
@@ -761,10 +788,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
 #pragma unroll
   for (int j = 0; j < kAhead; ++j) load_one(src, n, G, 0, j, raw[j]);
   if (stager) src.stage_store(sh, st);
-  if (threadIdx.x == 0) {
-    ls.ovf = 0;
-    ls.nout = 0;
-  }
+  if (threadIdx.x == 0) ls.nout = 0;
   if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
   __syncthreads();
   EWSJF_STAMP(kStampLocal, 1);
@@ -807,42 +831,22 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
   };
   emit(my_bar > 1u ? my_bar : 1u);
   if (wcnt > kWaveCap) {
-    // Too many for the wave's region: raise the bar just above the
-    // kWaveCap-th largest key, so fewer qualify, and emit again.  Only equal
-    // keys can still overflow (then the list is marked incomplete and the
-    // merge re-reads the share).
-    const uint32_t kth = wave_kth_of<kKeys>(key, kWaveCap);
-    if (kth != 0xFFFFFFFFu) {
-      my_bar = kth + 1u > my_bar ? kth + 1u : my_bar;
-      wcnt = 0;
-      emit(my_bar);
-    }
+    // Too many for the wave's region: raise the bar so that they fit, and
+    // emit again (keys equal to each other and too many all fall below it).
+    my_bar = wave_bar_that_fits<kKeys>(key, my_bar, kWaveCap);
+    wcnt = 0;
+    emit(my_bar);
   }
   EWSJF_STAMP(kStampLocal, 2);
-  if (lane == 0) {
-    ls.bar[wv] = my_bar;
-    if (wcnt > kWaveCap) ls.ovf = 1;
-  }
+  if (lane == 0) ls.bar[wv] = my_bar;
   __syncthreads();
   EWSJF_STAMP(kStampLocal, 3);
 
   const size_t slot = (size_t)t * G + blockIdx.x;
-  // The overflow flag, the wave bars (lane i reads wave i's) and this wave's
-  // region entry are read together: one LDS round trip.
-  const int any_ovf = ls.ovf;
+  // The wave bars (lane i reads wave i's) and this wave's region entry are
+  // read together: one LDS round trip.
   const uint32_t bar_l = ls.bar[lane & (kWavesPerBlock - 1)];
   const uint64_t reg_l = region[lane];  // valid for lane < wcnt
-  if (any_ovf != 0) {
-    for (int i = threadIdx.x; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
-    if (threadIdx.x == 0) {
-      cb.counts[slot] = 0u;
-      cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
-      cb.bounds2[slot] = ~0ull;
-      cb.over_cnt[slot] = 0u;
-    }
-    EWSJF_STAMP_FLUSH(kStampLocal);
-    return;
-  }
   close_list<kKeys>(ls, key, wcnt, bar_l, reg_l, G, M, slot, cb);
   EWSJF_STAMP(kStampLocal, 5);
   EWSJF_STAMP_FLUSH(kStampLocal);
@@ -2182,8 +2186,11 @@ static void launch_merge_rank(const SelectPlan& p, hipStream_t stream, hipEvent_
 // density d = B / n, a group of E / 2^lg keys holds one with probability
 // 1 - exp(-d E / 2^lg).  The workgroup's bound is its second largest bar, so
 // two such waves in one workgroup are needed, which must be expected in fewer
-// than one step in a thousand.  Data that breaks the assumption only sends the
-// merge back to the share (exact, slower).
+// than one step in a thousand (one in 32 was 3 to 10 us faster at B >= 2,048 on
+// mixed pools, but in arrival order, where the B are dense in few waves, some
+// steps went back to the share: 262,144 requests, B = 4,096: 78 us, 19 us).
+// Data that breaks the assumption only sends the merge back to the share
+// (exact, slower).
 static int spread_lg(int64_t n, int G, int B, bool one_pass, int64_t chunks_per_wave, int worst) {
   const double d = (double)B / (double)n;
   const double E = (double)kChunk * (double)(one_pass && chunks_per_wave > 3 ? 3 : chunks_per_wave);

@@ -1,6 +1,6 @@
 """The rank merge's own slots: every count of slots per thread, lists longer
 and shorter than a workgroup's own slots, slot counts that are no multiple of
-them, and the largest slot count."""
+them, and the largest slot count; waves whose keys overflow their region."""
 import numpy as np
 import pytest
 
@@ -26,12 +26,12 @@ def test_every_slot_has_one_owner(slots):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["mixed", "arrival", "oldest_first"])
+@pytest.mark.parametrize("kind", ["mixed", "arrival", "oldest_first", "all_equal"])
 @pytest.mark.parametrize("n,B", [(8195, 64), (12001, 500), (50000, 16), (131072, 2048), (262144, 1024), (262144, 4096),
                                  (524288, 3000), (1048577, 3000), (1048576, 4096)])
 def test_rank_of_many_slots(n, B, kind):
     from paper_2601_21758_amd import ewsjf as E
-    if kind == "oldest_first":
+    if kind in ("oldest_first", "all_equal"):
         L, A, now = W.adversarial(kind, n, 6)
     else:
         p = W.make_pool("three", n, 6, arrivals="uniform", horizon=300.0, K=16)
