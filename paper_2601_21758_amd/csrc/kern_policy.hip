@@ -10,13 +10,15 @@ namespace ewsjf {
 
 // lut[b] = the queue holding length b under the table's reading: the number
 // of bounds <= b (contiguous cover; Section 3.2 Dispatcher), or the gapped
-// rule of lo/hi (Section 4.3).
-// One lut word per thread (the searches and walks read the queue starts from
-// LDS: a search over the table itself is eight dependent loads) and, in the
-// first workgroups, one routing-map word: 8.3-9.2 us, against 12.3-15.6 us with
-// four words per thread searched for in the table.
+// rule of lo/hi (Section 4.3), and the compact routing map (the words that
+// route_fill writes).  Bound by latency: the launch, one read of the queue
+// starts and one search of them in LDS.  One length per thread, and a wave's
+// 64 lengths are two words of the map, whose rises are one ballot; a thread
+// per word walked its 32 lengths one after the other.  4.7 us, 8.3-9.2 us with
+// the walks.
 constexpr int kLutThreads = 256;
-constexpr int kLutBlocks = (kLutWords + kLutThreads - 1) / kLutThreads;  // 33
+constexpr int kLutBlocks = (4 * kLutWords + kLutThreads - 1) / kLutThreads;  // 129
+static_assert(kLutBlocks * kLutThreads >= 32 * kRouteWords, "every map word has its lanes");
 
 __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(ewsjf_queue_table* tab) {
   __shared__ int32_t bounds[EWSJF_MAX_QUEUES], lo[EWSJF_MAX_QUEUES], hi[EWSJF_MAX_QUEUES];
@@ -27,10 +29,19 @@ __global__ __launch_bounds__(kLutThreads) void build_lut_kernel(ewsjf_queue_tabl
   const int L = tab->max_len, k = tab->k;
   const bool gapped = tab->gapped != 0;
   __syncthreads();
-  const int t = blockIdx.x * kLutThreads + threadIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int x = blockIdx.x * kLutThreads + threadIdx.x;
   const int32_t *b = bounds, *l = lo, *h = hi;
-  lut_fill(tab->lut, t, kLutBlocks * kLutThreads, L, gapped, b, l, h, k);
-  route_fill(tab->route, t, kLutBlocks * kLutThreads, L, gapped, b, l, h, k);
+  // the map's queue of length y: 0 below 1, that of L past L
+  auto queue_at = [&](int y) { return (int)lut_entry(min(y, L), L, gapped, b, l, h, k); };
+  const int q = queue_at(x), before = queue_at(x - lane - 1);  // of the length before the wave's
+  const int up = __shfl_up(q, 1);
+  const uint64_t rise = __ballot(q != (lane == 0 ? before : up));
+  const int mid = __shfl(q, 31);
+  if (x < 4 * kLutWords) tab->lut[x] = x <= L ? (uint8_t)q : (uint8_t)0;
+  const int w = x >> 5;
+  if ((lane & 31) == 0 && w < kRouteWords)
+    tab->route[w] = ((uint64_t)(uint32_t)(lane == 0 ? before : mid) << 32) | (uint32_t)(rise >> lane);
 }
 
 hipError_t launch_build_lut(ewsjf_queue_table* table, hipStream_t stream) {
