@@ -250,8 +250,9 @@ __global__ __launch_bounds__(kBlock) void window_hist_move(const int32_t* __rest
 // Distinct values and exact prefix sums.  Workgroup w takes the bins (lengths)
 // 1024 w + 1 .. 1024 w + 1024, one per thread, and sums the bins before them
 // itself (at most 31 loads per thread, from L2 after the first workgroup), so
-// no workgroup waits for another.  One workgroup over all bins, with four
-// scattered stores per distinct value, took 30-45 us; this takes 8.9 us.
+// no workgroup waits for another.  Bound by latency: one round of loads and
+// one of LDS, 6.2 us (8.9 us with eight loads in flight and every thread
+// reading all waves' partials; 30-45 us on one workgroup over all bins).
 __global__ __launch_bounds__(kBlock) void rp_distinct(PartWs w, int L) {
   __shared__ int64_t sN[kWavesPerBlock], sS[kWavesPerBlock], tN[kWavesPerBlock], tS[kWavesPerBlock];
   __shared__ int sV[kWavesPerBlock], tV[kWavesPerBlock];
@@ -260,23 +261,21 @@ __global__ __launch_bounds__(kBlock) void rp_distinct(PartWs w, int L) {
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(w.hist), (short)0, (L + 1) * 4, kBufferWord3);
   const uint32_t h = __builtin_amdgcn_raw_buffer_load_b32(rs, b * 4, 0, 0);  // past bin L: 0
-  // the bins of the workgroups before this one
+  // The bins of the workgroups before this one, all loads in flight together
+  // (an offset past the buffer reads 0).
+  constexpr int kBefore = EWSJF_MAX_LEN / kBlock - 1;
+  static_assert(EWSJF_MAX_LEN % kBlock == 0, "at most kBefore workgroups before one");
+  uint32_t x[kBefore];
+#pragma unroll
+  for (int q = 0; q < kBefore; ++q)
+    x[q] = __builtin_amdgcn_raw_buffer_load_b32(rs, q < (int)blockIdx.x ? (q * kBlock + tid + 1) * 4 : (L + 1) * 4, 0, 0);
   int v0 = 0;
   int64_t n0 = 0, s0 = 0;
-  for (int q0 = 0; q0 < (int)blockIdx.x; q0 += 8) {
-    uint32_t x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u;
-      x[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, (min(q, (int)blockIdx.x - 1) * kBlock + tid + 1) * 4, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (q0 + u < (int)blockIdx.x) {
-        v0 += x[u] != 0u;
-        n0 += x[u];
-        s0 += (int64_t)x[u] * ((q0 + u) * kBlock + tid + 1);
-      }
+  for (int q = 0; q < kBefore; ++q) {
+    v0 += x[q] != 0u;
+    n0 += x[q];
+    s0 += (int64_t)x[q] * (q * kBlock + tid + 1);
   }
   // Inclusive scans over the wave of this workgroup's bins, wave sums of the
   // bins before it.
@@ -301,13 +300,17 @@ __global__ __launch_bounds__(kBlock) void rp_distinct(PartWs w, int L) {
     tS[wv] = s0;
   }
   __syncthreads();
-  int pos = 0;
-  int64_t pn = 0, ps = 0;
+  // Each wave sums the partials before it itself, one wave's per lane.
+  static_assert(kWavesPerBlock == 16, "the sums below are over 16 lanes");
+  const int p = lane & (kWavesPerBlock - 1);
+  const bool mine = p < wv;
+  int pos = tV[p] + (mine ? sV[p] : 0);
+  int64_t pn = tN[p] + (mine ? sN[p] : 0), ps = tS[p] + (mine ? sS[p] : 0);
 #pragma unroll
-  for (int q = 0; q < kWavesPerBlock; ++q) {
-    pos += tV[q] + (q < wv ? sV[q] : 0);
-    pn += tN[q] + (q < wv ? sN[q] : 0);
-    ps += tS[q] + (q < wv ? sS[q] : 0);
+  for (int off = 1; off < kWavesPerBlock; off <<= 1) {
+    pos += __shfl_xor(pos, off);
+    pn += __shfl_xor(pn, off);
+    ps += __shfl_xor(ps, off);
   }
   pos += lanes_below(live);
   if (h != 0u) {
