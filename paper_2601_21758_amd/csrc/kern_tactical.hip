@@ -96,7 +96,7 @@ __device__ __forceinline__ uint32_t sample_place(uint32_t i) { return i * 0x9E37
 int sample_step(int64_t n) {
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
   int lg = 0;
-  while ((nchunks >> lg) > kSampledChunks) ++lg;
+  while (((nchunks + (1ll << lg) - 1) >> lg) > kSampledChunks) ++lg;  // the first chunk of an incomplete group counts
   return lg;
 }
 
@@ -748,4 +748,25 @@ hipError_t launch_tactical_step(int32_t* len, const float* arrival, int64_t n, f
   return hipGetLastError();
 }
 
+#ifdef EWSJF_STAMPS
+// Instrumented build only: the sizes of a step's sample, and where its
+// workspace keeps the rows' member counts.
+void debug_tactical(int64_t n, int32_t B, int64_t* out) {
+  char* const base = reinterpret_cast<char*>((uintptr_t)256);  // for offsets only
+  TacWs w;
+  carve_tac(n, B, base, &w);
+  out[0] = w.g.rank;
+  out[1] = w.g.lg_step;
+  out[2] = w.g.n;
+  out[3] = 16ll << w.g.lg_p;
+  out[4] = kSampleMax;
+  out[5] = reinterpret_cast<char*>(w.g.count) - base;
+  out[6] = kMergeCap;
+}
+#endif
+
 }  // namespace ewsjf
+
+#ifdef EWSJF_STAMPS
+extern "C" void ewsjf_debug_tactical(int64_t n, int32_t B, int64_t* out) { ewsjf::debug_tactical(n, B, out); }
+#endif

@@ -1,0 +1,28 @@
+"""The sizes that the library's host side chooses, read from the instrumented
+build (the same sources; its debug exports launch nothing)."""
+import ctypes as C
+
+from paper_2601_21758_amd.build import LIB_STAMPS
+
+_lib = None
+
+
+def _debug():
+    global _lib
+    if _lib is None:
+        _lib = C.CDLL(LIB_STAMPS)
+    return _lib
+
+
+def _call(name, args, fields):
+    out = (C.c_int64 * len(fields))()
+    getattr(_debug(), name)(*args, out)
+    return dict(zip(fields, out))
+
+
+def tactical(n, B):
+    """Algorithm 1's sample: the thresholds' rank (0: none taken), every 2^lg_step-th chunk, samples, the places they
+    are spread over and the places there is room for; the workspace offset of the rows' member counts (int32) and
+    the most members a row may have."""
+    return _call("ewsjf_debug_tactical", (C.c_int64(n), C.c_int32(B)),
+                 ("rank", "lg_step", "samples", "places", "room", "count_at", "list_cap"))

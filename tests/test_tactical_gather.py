@@ -42,7 +42,9 @@ def _pool(kind, n, rng):
 CASES = [(1, 3, "mixed"), (9088, 4096, "mixed"), (9089, 4096, "mixed"), (65536, 64, "mixed"), (65537, 1500, "oldest_first"), (300001, 2048, "mixed"),
          (1 << 20, 1024, "oldest_first"), (1 << 20, 1024, "oldest_last"), (200003, 700, "equal"), (150000, 300, "nan"),
          (500000, 1024, "one_length"), (400000, 1024, "long_only"), (100000, 500, "unsampled"),
-         (4194304 + 513, 256, "mixed")]
+         (4194304 + 513, 256, "mixed"),
+         # every second chunk sampled; and the size whose last chunk starts a pair by itself
+         (16777216 + 77, 300, "mixed"), (33554432 + 5, 100, "mixed")]
 
 
 @pytest.mark.parametrize("n,B,kind", CASES)
