@@ -93,11 +93,15 @@ int hist_blocks(int64_t n) {
   return (int)g;
 }
 
-// Workgroups of window_hist_add: one round of loads each up to 262,144 entries
-// (the largest grid), more beyond.  The 65,536-length recount and its
-// repartition take 77.5 us with these 16 workgroups, 79.4 us with four.
+// Workgroups of window_hist_add: 4,096 entries each up to 16 of them (one round
+// of loads; the 65,536-length recount and its repartition take 77.5 us with 16,
+// 79.4 us with four), 16,384 each from then on: every workgroup adds each of
+// its lengths to the histogram once, so smaller shares only add the same
+// lengths more often (262,144 and 524,288 uniform lengths: 12.5 and 14.1 us with
+// 64 workgroups, 11.9 and 12.2 us with 16 and 32).
 int add_blocks(int64_t n) {
-  return (int)std::clamp<int64_t>((n + 4 * kBlock - 1) / (4 * kBlock), 1, kMaxHistBlocks);
+  const int64_t small = std::clamp<int64_t>((n + 4 * kBlock - 1) / (4 * kBlock), 1, 16);
+  return std::max((int)small, hist_blocks(n));
 }
 
 // Entries of one partial histogram: L + 1 bins, padded to whole 16-byte vectors.
@@ -204,12 +208,12 @@ __global__ __launch_bounds__(kBlock) void window_hist_add(const int32_t* __restr
   __shared__ i32x4 hv[kHistVecs];
   uint32_t* h = reinterpret_cast<uint32_t*>(hv);
   lds_window_hist(ring, cap, begin, n, L, h);
-  for (int i = threadIdx.x; i < hist_row(L) / 4; i += kBlock) {
-    const i32x4 x = hv[i];
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (x[e] != 0) atomicAdd(&hist[4 * i + e], (uint32_t)x[e]);  // none past bin L
-  }
+  // A wave adds to 64 neighbouring bins: two cache lines an instruction.  Four
+  // bins per thread (vector reads of LDS) are eight lines, each touched four
+  // times: 1M lengths of two modes took 18.3 us, uniform ones 47.8 us; 10.5 and
+  // 15.6 us with these.
+  for (int b = threadIdx.x; b <= L; b += kBlock)
+    if (h[b] != 0u) atomicAdd(&hist[b], h[b]);
 }
 
 // Column sums of the partial histograms.  Four bins per thread and four
