@@ -15,6 +15,7 @@ struct SelectPlan {
   int G = 1;        // streaming workgroups
   int lg = 2;       // log2 of the lane groups per wave that set the candidate bar
   int M = 16;       // list entries kept per workgroup
+  int fit = 48;     // entries a wave keeps at least when its keys overflow its region
   int n_theta = 1;
   size_t lists_bytes = 0, counts_bytes = 0, bounds_bytes = 0;
   size_t over_bytes = 0, over_cnt_bytes = 0, bounds2_bytes = 0;

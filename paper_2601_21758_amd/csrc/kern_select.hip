@@ -710,12 +710,12 @@ __device__ __forceinline__ void close_list(ListShared& ls, const uint32_t* key, 
 
 // A bar above `lo` that at most `cap` of the wave's N x 64 keys reach, `lo`
 // being one that more reach: halving between lo and the largest key, until
-// three quarters of cap or more reach it or no bar between is left.  Any bar is
-// valid, so the search need not find the cap-th key: some rounds of N ballots,
-// where its 32 bits took 32 (a step over 4M requests with B = 4,096, where a few
-// waves overflow: 28.9 us, 23.9 us with this search).
+// `enough` or more reach it (the plan's `fit`) or no bar between is left.  Any
+// bar is valid, so the search need not find the cap-th key: some rounds of N
+// ballots, where its 32 bits took 32 (a step over 4M requests with B = 4,096,
+// where a few waves overflow: 28.9 us, 23.9 us with this search).
 template <int N>
-__device__ __forceinline__ uint32_t wave_bar_that_fits(const uint32_t* key, uint32_t lo, int cap) {
+__device__ __forceinline__ uint32_t wave_bar_that_fits(const uint32_t* key, uint32_t lo, int cap, int enough) {
   uint32_t hi = 0;
 #pragma unroll
   for (int e = 0; e < N; ++e) hi = key[e] > hi ? key[e] : hi;
@@ -729,7 +729,7 @@ __device__ __forceinline__ uint32_t wave_bar_that_fits(const uint32_t* key, uint
       lo = mid;
     } else {
       hi = mid;
-      if (4 * c >= 3 * cap) break;
+      if (c >= enough) break;
     }
   }
   return hi;
@@ -759,7 +759,8 @@ __device__ __forceinline__ uint32_t wave_kth_of(const uint32_t* key, int k) {
 // and 7.2 us.  4M requests, four chunks per wave: 11.0 us (3.05 TB/s).
 // ---------------------------------------------------------------------------
 template <class Src, int kChunks>
-__global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
+__global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, int G, int lg, int M, CandBufs cb,
+                                                           int fit) {
   static_assert(!Src::kClustered && kChunks <= kChunksPerPass, "one pass of a source without clusters");
   constexpr int kKeys = 4 * kChunks;
   constexpr int kBarChunks = kChunks < 3 ? kChunks : 3;  // the bar comes from these
@@ -833,7 +834,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
   if (wcnt > kWaveCap) {
     // Too many for the wave's region: raise the bar so that they fit, and
     // emit again (keys equal to each other and too many all fall below it).
-    my_bar = wave_bar_that_fits<kKeys>(key, my_bar, kWaveCap);
+    my_bar = wave_bar_that_fits<kKeys>(key, my_bar, kWaveCap, fit);
     wcnt = 0;
     emit(my_bar);
   }
@@ -2127,15 +2128,15 @@ static void launch_local(const SelectPlan& p, int rows, hipStream_t stream, hipE
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
   const int64_t per_wave = (nchunks + (int64_t)p.G * kWavesPerBlock - 1) / ((int64_t)p.G * kWavesPerBlock);
   const dim3 grid(p.G, rows), block(kBlock);
-  auto go = [&](auto kern) {
+  auto go = [&](auto kern, auto... more) {
     if (e0 != nullptr)
-      hipExtLaunchKernelGGL(kern, grid, block, 0, stream, e0, e1, 0, src, n, p.G, p.lg, p.M, cb);
+      hipExtLaunchKernelGGL(kern, grid, block, 0, stream, e0, e1, 0, src, n, p.G, p.lg, p.M, cb, more...);
     else
-      hipLaunchKernelGGL(kern, grid, block, 0, stream, src, n, p.G, p.lg, p.M, cb);
+      hipLaunchKernelGGL(kern, grid, block, 0, stream, src, n, p.G, p.lg, p.M, cb, more...);
   };
-  if (per_wave <= 1) go(local_candidates<Src, 1>);
-  else if (per_wave <= 2) go(local_candidates<Src, 2>);
-  else if (per_wave <= kChunksPerPass) go(local_candidates<Src, kChunksPerPass>);
+  if (per_wave <= 1) go(local_candidates<Src, 1>, p.fit);
+  else if (per_wave <= 2) go(local_candidates<Src, 2>, p.fit);
+  else if (per_wave <= kChunksPerPass) go(local_candidates<Src, kChunksPerPass>, p.fit);
   else go(local_stream<Src>);
 }
 
@@ -2226,6 +2227,16 @@ SelectPlan plan_select(int64_t n, int32_t n_theta, int32_t B, bool packed, int m
     lg = spread_lg(n, p.G, B, my_chunks <= per_pass, (my_chunks + kWavesPerBlock - 1) / kWavesPerBlock, lg);
   }
   p.lg = lg;
+  // A wave whose keys overflow its region keeps three quarters of it or more.
+  // Where its even share of the B, with two deviations, passes that but not the
+  // region, it fills the region: most bars would lie above the B-th key, and
+  // the merge would go back to the shares (a share of 51, 20,000 scores and B =
+  // 4,096: 74 us, 26 us filled; a share of 43, 9,000 and 2,048: 53 us, 35 us).
+  // Elsewhere the longer lists only cost their ranking (a share of 13, 40,000
+  // and 2,048: 15 us, 45 us filled; of 85, 9,000 and 4,096: 102 us, 110 us).
+  const double share = (double)B / ((double)p.G * kWavesPerBlock);
+  const bool fill = share + 2.0 * std::sqrt(share) > 0.75 * kWaveCap && share <= (double)kWaveCap;
+  p.fit = fill ? kWaveCap - 1 : kWaveCap - kWaveCap / 4;
   int M = pow2_ceil(4 * per);
   if (M < 16) M = 16;
   const int cap = kMergeCap / p.G;
@@ -2548,6 +2559,16 @@ extern "C" int ewsjf_debug_stamps(uint64_t* host, size_t count) {
   if (count > (size_t)ewsjf::kStampSlots) count = ewsjf::kStampSlots;
   return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(ewsjf::g_stamps), count * sizeof(uint64_t), 0,
                                   hipMemcpyDeviceToHost);
+}
+// The selection plan of an operation (EWSJF_OP_STEP, _SELECT or _TRIAL).
+extern "C" void ewsjf_debug_plan(int op, int64_t n, int32_t rows, int32_t B, int64_t* out) {
+  const ewsjf::SelectPlan p = op == EWSJF_OP_TRIAL    ? ewsjf::plan_trial(n, rows, B)
+                              : op == EWSJF_OP_SELECT ? ewsjf::plan_scores(n, rows, B)
+                                                      : ewsjf::plan_select(n, rows, B, ewsjf::step_packed(n, rows), 0, true);
+  out[0] = p.G;
+  out[1] = p.lg;
+  out[2] = p.M;
+  out[3] = p.fit;
 }
 extern "C" int ewsjf_debug_stamps_clear(void) {
   static uint64_t zeros[ewsjf::kStampSlots];

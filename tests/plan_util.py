@@ -26,3 +26,9 @@ def tactical(n, B):
     the most members a row may have."""
     return _call("ewsjf_debug_tactical", (C.c_int64(n), C.c_int32(B)),
                  ("rank", "lg_step", "samples", "places", "room", "count_at", "list_cap"))
+
+
+def plan(op, n, rows, B):
+    """The selection plan of an operation (_lib.OP_STEP, OP_SELECT, OP_TRIAL): workgroups per row, bar groups per wave
+    (log2), list entries per workgroup, entries a wave keeps at least when its region overflows."""
+    return _call("ewsjf_debug_plan", (C.c_int(op), C.c_int64(n), C.c_int32(rows), C.c_int32(B)), ("G", "lg", "M", "fit"))
