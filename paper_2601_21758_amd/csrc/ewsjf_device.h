@@ -18,7 +18,7 @@ constexpr int kChunksPerPass = 4;            // chunks a wave holds in registers
 constexpr int kElemsPerLane = 4 * kChunksPerPass;
 constexpr int kMaxGrid = 256;                // streaming workgroups (one per CU)
 constexpr int kListCap = 1024;               // per-workgroup candidate list in LDS
-constexpr int kShortList = 512;              // lists ranked by all waves at once (up to 8 entries per lane)
+constexpr int kRankRun = 512;                // list entries ranked by all waves at once (up to 8 per lane)
 constexpr int kWaveCap = kListCap / (kBlock / kWave);  // one region of the list per wave
 constexpr int kOverCap = 128;                // overflow entries kept per workgroup
 constexpr int kDenseWave = 32;              // region entries that mark a wave holding a cluster of high keys
@@ -302,18 +302,6 @@ __device__ inline uint32_t wave_kth_largest(const uint32_t* key, int k) {
 // Number of lanes below this one whose bit is set in the wave mask sm.
 __device__ __forceinline__ int lanes_below(uint64_t sm) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(sm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)sm, 0u));
-}
-
-// xor_lane_u32 for a wave-uniform distance j in {1, 2, 4, 8, 16, 32}.
-__device__ __forceinline__ uint32_t xor_lane_u32_dyn(uint32_t x, int j) {
-  switch (j) {
-    case 1: return xor_lane_u32<1>(x);
-    case 2: return xor_lane_u32<2>(x);
-    case 4: return xor_lane_u32<4>(x);
-    case 8: return xor_lane_u32<8>(x);
-    case 16: return xor_lane_u32<16>(x);
-    default: return xor_lane_u32<32>(x);
-  }
 }
 
 template <int J>

@@ -463,7 +463,7 @@ struct ListShared {
   uint32_t hist[256];
   uint64_t red[kWavesPerBlock];
   int iscan[kWavesPerBlock];
-  int rank[kShortList];  // ranks of a short list, summed over the waves
+  int rank[kListCap];  // ranks of the list, summed over the waves
   uint32_t bar[kWavesPerBlock];
   uint32_t thr[kWavesPerBlock];  // local_stream: the threshold each wave has listed down to
   int wcnt[kWavesPerBlock];
@@ -546,7 +546,7 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
     // add up in LDS, and after one barrier the first two waves place the
     // entries.  Straight-line code: no loop and no per-entry branch.
     constexpr int kSmallPer = 2 * kWave / kWavesPerBlock;
-    static_assert(kSmallPer * kWavesPerBlock == 2 * kWave && 2 * kWave <= kShortList, "one slice per wave");
+    static_assert(kSmallPer * kWavesPerBlock == 2 * kWave && 2 * kWave <= kListCap, "one slice per wave");
     const uint64_t x0 = lane < cnt ? ls.list2[lane] : 0ull;
     const uint64_t x1 = kWave + lane < cnt ? ls.list2[kWave + lane] : 0ull;
     const int j0 = kSmallPer * wv;
@@ -578,17 +578,21 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
     if (threadIdx.x == 0) cb.over_cnt[slot] = (uint32_t)(listed - M);
     return;
   }
-  if (cnt <= kShortList) {
-    // Longer lists: every wave holds all entries (up to 8 per lane),
-    // compares them with its own few (entries w, w + 16, ...) and adds its
-    // counts into LDS, so no wave runs a long serial chain.
-    constexpr int kG = kShortList / kWave;
-    const int ng = (cnt + kWave - 1) / kWave;  // entries per lane in use
+  // Longer lists, kRankRun entries at a time: every wave holds a run of them (up
+  // to 8 per lane), compares it with its own few entries (w, w + 16, ...) and
+  // adds its counts into LDS, so no wave runs a long serial chain.  Bound by the
+  // compares of the longest lists, a million of 64 bits for 1,024 entries
+  // (65,536 scores, B = 1,024: 31.2 us, 33.0 us with a thread per entry that
+  // reads the whole list).
+  constexpr int kG = kRankRun / kWave;
+  for (int b0 = 0; b0 < cnt; b0 += kRankRun) {  // uniform: one run, or two
+    const int ng = (min(cnt - b0, kRankRun) + kWave - 1) / kWave;  // entries per lane in use
     uint64_t x[kG];
     int part[kG];
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      x[g] = g < ng && g * kWave + lane < cnt ? ls.list2[g * kWave + lane] : 0ull;
+      const int i = b0 + g * kWave + lane;
+      x[g] = g < ng && i < cnt ? ls.list2[i] : 0ull;
       part[g] = 0;
     }
     // This wave's entries j = wv + 16 i, four reads at a time (an entry past
@@ -608,33 +612,17 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
         }
     }
 #pragma unroll
-    for (int g = 0; g < kG; ++g)
-      if (g < ng && g * kWave + lane < cnt && part[g] != 0) atomicAdd(&ls.rank[g * kWave + lane], part[g]);
-    __syncthreads();
-    if (wv < kG && threadIdx.x < cnt) {
-      place(ls.list2[threadIdx.x], ls.rank[threadIdx.x]);
-      if (kClearRank) ls.rank[threadIdx.x] = 0;  // ready for the next list
+    for (int g = 0; g < kG; ++g) {
+      const int i = b0 + g * kWave + lane;
+      if (g < ng && i < cnt && part[g] != 0) atomicAdd(&ls.rank[i], part[g]);
     }
-    if (threadIdx.x == 0) cb.over_cnt[slot] = (uint32_t)(listed - M);
-    return;
   }
-  // Longer lists: tpe consecutive lanes count each element's rank, each over
-  // a slice of the list, and sum with lane exchanges.
-  int tpe = 1;
-  if (cnt > 128)
-    while (tpe < kWave && 2 * tpe * cnt <= kBlock) tpe *= 2;
-  const int e = threadIdx.x / tpe, part = threadIdx.x & (tpe - 1);
-  const int per = (cnt + tpe - 1) / tpe;
-  uint64_t x = 0;
-  int rank = 0;
-  if (e < cnt) {
-    x = ls.list2[e];
-    const int j0 = part * per, j1 = min(cnt, j0 + per);
-#pragma unroll 8
-    for (int j = j0; j < j1; ++j) rank += ls.list2[j] > x;
+  __syncthreads();
+  static_assert(kListCap <= kBlock, "a thread per entry");
+  if ((int)threadIdx.x < cnt) {
+    place(ls.list2[threadIdx.x], ls.rank[threadIdx.x]);
+    if (kClearRank) ls.rank[threadIdx.x] = 0;  // ready for the next list
   }
-  for (int o = 1; o < tpe; o <<= 1) rank += (int)xor_lane_u32_dyn((uint32_t)rank, o);
-  if (e < cnt && part == 0) place(x, rank);
   if (threadIdx.x == 0) cb.over_cnt[slot] = (uint32_t)(listed - M);
 }
 
@@ -790,7 +778,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
   for (int j = 0; j < kAhead; ++j) load_one(src, n, G, 0, j, raw[j]);
   if (stager) src.stage_store(sh, st);
   if (threadIdx.x == 0) ls.nout = 0;
-  if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
+  ls.rank[threadIdx.x] = 0;
   __syncthreads();
   EWSJF_STAMP(kStampLocal, 1);
   const auto km = src.key_mode(sh);
@@ -897,7 +885,7 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
       ls.nspill = 0;
       ls.lowbar = 0u;
     }
-    if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
+    ls.rank[threadIdx.x] = 0;
     static_assert(kListCap == kBlock, "one spill entry per thread");
     if constexpr (Src::kClustered) ls.spill[threadIdx.x] = 0ull;
   };
@@ -1184,7 +1172,7 @@ __global__ __launch_bounds__(kBlock) void local_stream(Src src0, int64_t n, int 
     ls.nout = 0;
   }
   if (threadIdx.x < kWavesPerBlock) ls.bar[threadIdx.x] = 0u;
-  if (threadIdx.x < kShortList) ls.rank[threadIdx.x] = 0;
+  ls.rank[threadIdx.x] = 0;
   __syncthreads();
   const auto km = src.key_mode(sh);
 
@@ -1367,7 +1355,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates_multi(PoolSource src,
     s_ovf[tid] = 0;
     s_nout[tid] = 0;
   }
-  if (tid < kShortList) ls.rank[tid] = 0;
+  ls.rank[tid] = 0;
   __syncthreads();
 
   // Per request: queue (-1 for an empty slot) and the three terms.
