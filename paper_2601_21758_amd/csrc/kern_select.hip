@@ -2338,16 +2338,32 @@ SelectPlan plan_trial(int64_t capacity, int32_t n_pools, int32_t B) {
 
 // Scores given by the caller: one row takes a workgroup per 16 chunks (one
 // chunk per wave); several rows take up to four chunks per wave when that
-// leaves one round of the
-// chip: four rows of 1,000,003 scores
-// take 10.1 us with four chunks per wave (248 workgroups), 23.2 us with one
-// (980: four rounds, each with its own list to close).
+// leaves one round of the chip (four rows of 1,000,003 scores, B = 256: 10.1 us
+// with four chunks per wave and 248 workgroups, 23.2 us with one and 980, each
+// with its own list to close), but for two limits:
+//  - fewer workgroups must not turn short lists into long ones that have to be
+//    ranked.  Lists are short up to 12 of the B per workgroup (eight bar groups
+//    a wave): 64 rows of 65,536, B = 64, take 27.6 us with one chunk, 38.0 us
+//    with four; four rows of 1M, B = 1,024, 28.6 and 37.8.  Lists that are long
+//    anyway gain: 64 rows of 65,536, B = 256: 46 us and 34 us.
+//  - a wave's region of 64 entries must hold its share of the B (40, with room
+//    for the deviation), or the merge goes back to the pool: 64 rows of 32,768,
+//    B = 4,096: 57 us with one chunk, 119 us with four.
 SelectPlan plan_scores(int64_t n, int32_t n_theta, int32_t B) {
+  constexpr int kShortPer = 12, kFitShare = 40;
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
+  auto groups = [&](int per_wave) {
+    const int64_t g = (nchunks + kWavesPerBlock * per_wave - 1) / (kWavesPerBlock * per_wave);
+    return (int)std::clamp<int64_t>(g, 1, kMaxGrid);
+  };
+  const bool long_lists = B > kShortPer * groups(1);
   int per_wave = 1;
-  while (per_wave < kChunksPerPass && (nchunks / (kWavesPerBlock * per_wave)) * n_theta > kMaxGrid) per_wave *= 2;
-  const int64_t G = (nchunks + kWavesPerBlock * per_wave - 1) / (kWavesPerBlock * per_wave);
-  SelectPlan p = plan_select(n, n_theta, B, false, (int)std::max<int64_t>(1, std::min<int64_t>(G, kMaxGrid)));
+  while (per_wave < kChunksPerPass && (nchunks / (kWavesPerBlock * per_wave)) * n_theta > kMaxGrid) {
+    const int g = groups(2 * per_wave);
+    if ((!long_lists && B > kShortPer * g) || B > kFitShare * kWavesPerBlock * g) break;
+    per_wave *= 2;
+  }
+  SelectPlan p = plan_select(n, n_theta, B, false, groups(per_wave));
   p.ws_bytes = std::max(p.ws_bytes, plan_select(n, n_theta, B).ws_bytes);
   return p;
 }

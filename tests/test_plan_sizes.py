@@ -24,3 +24,19 @@ def test_regions_are_filled_where_the_admissions_need_them(op, n, B):
         assert p["fit"] < REGION  # no list holds it
     else:
         assert p["fit"] >= min(need, REGION - 1)
+
+
+@pytest.mark.parametrize("n,rows,B", [(20000, 100, 4096), (9000, 256, 2048), (32768, 64, 4096), (65536, 256, 4096),
+                                      (100003, 64, 4096), (65536, 64, 64), (1 << 20, 4, 1024), (1 << 20, 4, 2048),
+                                      (262144, 16, 512), (1000003, 4, 256), (65536, 64, 512)])
+def test_rows_keep_room_for_the_admissions(n, rows, B):
+    """Several rows take larger shares per workgroup, but the slots and the waves' regions hold the B where one chunk
+    per wave would hold them, and short lists stay short."""
+    p = plan_util.plan(L.OP_SELECT, n, rows, B)
+    G1 = min(256, -(-n // 4096))  # one chunk per wave
+    slots1 = G1 * min(1024, 9088 // G1)
+    if slots1 >= B:
+        assert p["G"] * p["M"] >= B
+    assert B / (p["G"] * WAVES) <= max(40, B / (G1 * WAVES))
+    if -(-B // G1) <= 12:
+        assert p["lg"] <= 3 and B <= 12 * p["G"]

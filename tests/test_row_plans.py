@@ -37,9 +37,9 @@ def test_score_rows(n, nt):
     assert np.array_equal(E.route(dev(L), tab).cpu().numpy(), oracle.route(L, t))
 
 
-# chunks per wave: 1 (one round of the chip), 2, 4, and rows beyond one round
+# chunks per wave: 1 (one round of the chip), 2, 4, and rows beyond one round; more of the B than larger shares hold
 @pytest.mark.parametrize("n,rows,B", [(65536, 4, 64), (300001, 6, 700), (524287, 4, 256), (1000003, 4, 4096),
-                                      (700001, 9, 33)])
+                                      (700001, 9, 33), (20000, 100, 4096), (9000, 256, 2048)])
 def test_select_rows(n, rows, B):
     from paper_2601_21758_amd import ewsjf as E
     rng = np.random.default_rng(rows)
