@@ -2322,18 +2322,34 @@ SelectPlan plan_step(int64_t n, int32_t n_theta, int32_t B) {
   return p;
 }
 
-// Trials: as many workgroups per pool as make one round of the chip, each
-// walking its share with chunks in flight (local_stream), so a workgroup's
-// table staging and list publication are paid once per compute unit; at least
-// one per 32 admissions (a wave's region holds 64 entries) and no more than
-// one full pass each needs.  16 pools of 1M slots: 37.8 us (3.6 TB/s) with 16
-// workgroups per pool, 57.6 us with one pass each (64 per pool, four rounds).
+// Trials: workgroups per pool in whole rounds of the chip (local_stream's
+// workgroups fill a compute unit each), as few rounds as leave a wave four of
+// the B at most (its region holds 64 entries), each workgroup walking its share
+// with chunks in flight, so table staging and list publication are paid once
+// per round.  16 pools of 1M slots: 37.8 us (3.6 TB/s) in one round of 16
+// workgroups per pool, 57.6 us with one pass of local_candidates each (64 per
+// pool, four rounds).  A round that leaves over a quarter of the chip idle is not
+// taken: one pass each, whose many short workgroups need no whole rounds, or,
+// where its lists would be long (more than eight of the B per workgroup), the
+// next number of rounds.  us a step, B = 32 / 512, this rule and at least 32 of
+// the B per workgroup whatever the rounds:
+//   1M slots    17 pools 40 / 44, 38 / 69    129 pools 183 / 228, 288 / 253
+//   262,144     17 pools 24 / 25, 21 / 51    257 pools 113 / 165, 174 / 311
 SelectPlan plan_trial(int64_t capacity, int32_t n_pools, int32_t B) {
   const int64_t per_pass = (int64_t)kWavesPerBlock * kChunksPerPass * kChunk;
   const int full = (int)std::min<int64_t>((capacity + per_pass - 1) / per_pass, kMaxGrid);
-  int G = std::max(kMaxGrid / n_pools, (B + 31) / 32);
-  G = std::max(1, std::min(G, full));
-  return plan_select(capacity, n_pools, B, true, G, true);
+  const int least = (B + 63) / 64;
+  int G = full;
+  for (int rounds = (least * n_pools + kMaxGrid - 1) / kMaxGrid;; ++rounds) {
+    const int g = rounds * kMaxGrid / n_pools;
+    if (g >= full) break;
+    if (4 * g * n_pools >= 3 * rounds * kMaxGrid) {
+      G = g;
+      break;
+    }
+    if (B <= 8 * full) break;
+  }
+  return plan_select(capacity, n_pools, B, true, std::max(G, 1), true);
 }
 
 // Scores given by the caller: one row takes a workgroup per 16 chunks (one

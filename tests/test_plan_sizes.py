@@ -40,3 +40,18 @@ def test_rows_keep_room_for_the_admissions(n, rows, B):
     assert B / (p["G"] * WAVES) <= max(40, B / (G1 * WAVES))
     if -(-B // G1) <= 12:
         assert p["lg"] <= 3 and B <= 12 * p["G"]
+
+
+@pytest.mark.parametrize("cap", [4, 16384, 65536, 262144, 1 << 20, 1 << 23])
+@pytest.mark.parametrize("B", [1, 32, 512, 2048, 4096])
+def test_trials_run_in_whole_rounds(cap, B):
+    """One pass per workgroup, or rounds of the chip that are at least three quarters full, with a region's room for
+    every wave's share of the B."""
+    full = min(256, -(-cap // 16384))
+    for pools in (1, 2, 15, 16, 17, 33, 64, 65, 100, 129, 160, 200, 255, 256, 257, 300, 511, 513, 1000, 1024):
+        G = plan_util.plan(L.OP_TRIAL, cap, pools, B)["G"]
+        assert 1 <= G <= full
+        if G < full:
+            rounds = -(-G * pools // 256)
+            assert G * pools >= 0.75 * 256 * rounds, (pools, G)
+            assert B <= 64 * G

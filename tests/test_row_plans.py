@@ -56,9 +56,9 @@ def test_select_rows(n, rows, B):
         assert np.array_equal(top[r], s[r][want])
 
 
-# capacity, pools, B: shares of one pass, of two, of many; few workgroups per pool
+# capacity, pools, B: shares of one pass, of two, of many; few workgroups per pool; one pool past a round of the chip
 @pytest.mark.parametrize("cap,pools,B", [(65536, 3, 64), (262144, 40, 100), (1 << 20, 16, 512), (1 << 19, 100, 64),
-                                         (100004, 70, 300)])
+                                         (100004, 70, 300), (262144, 17, 513), (131072, 257, 32), (65536, 129, 64)])
 def test_trial_shares(cap, pools, B):
     from paper_2601_21758_amd import ewsjf as E
     from paper_2601_21758_amd.trial import Trial
