@@ -48,8 +48,7 @@ constexpr int kGatherLds = 4096;       // members of one row that one workgroup 
 
 // The oldest members of the plan's queues by an age threshold.
 struct Gather {
-  // Sample s sits at place 16 (s mod 2^lg_p) + s / 2^lg_p, so the 16 a thread
-  // loads as vectors are far apart in the pool.
+  // Sample s sits at place sample_slot(s).
   uint32_t* skey;   // [kSampleMax] FIFO keys of the sampled requests (0 = empty slot)
   uint8_t* sq;      // [kSampleMax] their queues
   uint64_t* tau;    // [EWSJF_MAX_QUEUES] the queue's members at or above it hold its oldest B
@@ -92,6 +91,21 @@ size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 // The sampled places of a chunk, by its number among the sampled chunks: at
 // and 128 + at, at in 0..127.
 __device__ __forceinline__ uint32_t sample_place(uint32_t i) { return i * 0x9E3779B1u >> 25; }
+
+// Where sample s lies: place 16 v + j, thread v reading the 16 places from 16 v
+// on, and back.  The thresholds come from maxima over the threads with one v mod
+// 256, and two of the oldest in one group put a threshold deeper.  So samples
+// next to each other fall into different groups (v follows s, and neighbours
+// share cache lines), and so do samples a power of two apart: the high part of s
+// and j are mixed in.  With v = s mod 2^lg_p, a queue that lives in every 256th
+// chunk fell into two groups, its threshold let every member through, and one
+// workgroup read the pool (4M requests: 2.0 ms; 41 us so).
+__device__ __forceinline__ int sample_slot(int s, int lg_p) {
+  const int j = s >> lg_p, low = s & ((1 << lg_p) - 1);
+  return 16 * (low ^ (low >> 8) ^ (17 * j)) + j;
+}
+// vv: v ^ (v >> 8); 17 j lies below 256.
+__device__ __forceinline__ int sample_of_slot(int vv, int j, int lg_p) { return (vv ^ (17 * j)) + (j << lg_p); }
 
 int sample_step(int64_t n) {
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
@@ -194,11 +208,12 @@ __global__ __launch_bounds__(kBlock) void tac_scan(const int32_t* __restrict__ l
     for (int j = 0; j < 4; ++j) {
       const int64_t c = (int64_t)blockIdx.x + (int64_t)G * (lc0 + (int64_t)j * kWavesPerBlock);
       const int64_t first = c * kChunk;
-      // the sampled element of lanes with this low part, -1 elsewhere
-      int pick = -1;
+      // the sampled element of lanes with this low part, -1 elsewhere, and its place
+      int pick = -1, place = 0;
       if (g.rank > 0 && c < nchunks && (c & ((1ll << g.lg_step) - 1)) == 0) {  // uniform
-        const uint32_t at = sample_place((uint32_t)(c >> g.lg_step));
+        const uint32_t i = (uint32_t)(c >> g.lg_step), at = sample_place(i);
         pick = (int)(at >> 2) == (lane & 31) ? (int)(at & 3u) : -1;
+        place = sample_slot(2 * (int)i, g.lg_p) ^ ((lane >> 5) << 4);  // sample 2 i + lane / 32 differs in v's lowest bit
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -212,8 +227,6 @@ __global__ __launch_bounds__(kBlock) void tac_scan(const int32_t* __restrict__ l
           if (hk < head[q]) atomicMin(reinterpret_cast<unsigned long long*>(&head[q]), (unsigned long long)hk);
         }
         if (pick == e) {
-          const int s = 2 * (int)(c >> g.lg_step) + (lane >> 5);
-          const int place = 16 * (s & ((1 << g.lg_p) - 1)) + (s >> g.lg_p);
           g.skey[place] = b > 0 ? ~ak : 0u;
           g.sq[place] = (uint8_t)q;
         }
@@ -343,11 +356,12 @@ __global__ __launch_bounds__(kBlock) void tac_reduce(const uint32_t* __restrict_
     return;
   }
   // The largest composite (the oldest) of this queue among each thread's
-  // samples, neighbours in the pool in different threads.
+  // samples.
   uint64_t best = 0;
   const i32x4* kv = reinterpret_cast<const i32x4*>(g.skey);
   const i32x4* qv = reinterpret_cast<const i32x4*>(g.sq);
   for (int v = tid; v < (1 << g.lg_p); v += kBlock) {
+    const int vv = v ^ (v >> 8);
     const i32x4 sq = qv[v];
     i32x4 key[4];
 #pragma unroll
@@ -356,14 +370,17 @@ __global__ __launch_bounds__(kBlock) void tac_reduce(const uint32_t* __restrict_
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int s = v + ((4 * u + e) << g.lg_p);
+        const int s = sample_of_slot(vv, 4 * u + e, g.lg_p);
         if (s < g.n && (int)(((uint32_t)sq[u] >> (8 * e)) & 0xFFu) == q && key[u][e] != 0) {
-          const uint32_t i = (uint32_t)s >> 1;  // its chunk among the sampled ones
-          const uint32_t id = ((i << g.lg_step) * (uint32_t)kChunk) + sample_place(i) + 128u * ((uint32_t)s & 1u);
-          const uint64_t x = make_comp((uint32_t)key[u][e], id);
+          const uint64_t x = make_comp((uint32_t)key[u][e], (uint32_t)s);  // (ids rise with s)
           best = x > best ? x : best;
         }
       }
+  }
+  if (best != 0ull) {
+    const uint32_t s = comp_id(best), i = s >> 1;  // its chunk among the sampled ones
+    const uint32_t id = ((i << g.lg_step) * (uint32_t)kChunk) + sample_place(i) + 128u * (s & 1u);
+    best = make_comp((uint32_t)(best >> 32), id);
   }
   oldest[tid] = best;
   __syncthreads();
@@ -483,51 +500,67 @@ __global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__
     qs[r] = plan->take[r] > 0 ? plan->q_sel[r] : -2;  // no request's queue
     tau[r] = qs[r] >= 0 ? g.tau[qs[r]] : ~0ull;
   }
+  // The least key any row takes: most requests are younger and need no route.
+  uint32_t min_key = ~0u;
+#pragma unroll
+  for (int r = 0; r < kTacticalRows; ++r) min_key = min(min_key, (uint32_t)(tau[r] >> 32));
   if (tid < kTacticalRows) nout[tid] = 0;
   __syncthreads();
   const int64_t nchunks = (n + kChunk - 1) / kChunk;
-  for (int64_t lc0 = wv;; lc0 += 4 * kWavesPerBlock) {
-    const int64_t c0 = (int64_t)blockIdx.x + (int64_t)G * lc0;
-    if (c0 >= nchunks) break;
-    i32x4 l[4], a[4];
+  auto pass = [&](auto some) {  // some: not every age is taken
+    for (int64_t lc0 = wv;; lc0 += 4 * kWavesPerBlock) {
+      const int64_t c0 = (int64_t)blockIdx.x + (int64_t)G * lc0;
+      if (c0 >= nchunks) break;
+      i32x4 l[4], a[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {  // chunks past the end read zeros
-      const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
-      l[j] = chunk_load_i32x4(chunk_rsrc(len + first, n - first), lane);
-      a[j] = chunk_load_i32x4(chunk_rsrc(arrival + first, n - first), lane);
-    }
+      for (int j = 0; j < 4; ++j) {  // chunks past the end read zeros
+        const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
+        l[j] = chunk_load_i32x4(chunk_rsrc(len + first, n - first), lane);
+        a[j] = chunk_load_i32x4(chunk_rsrc(arrival + first, n - first), lane);
+      }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
-      if (first >= n) break;  // uniform
+      for (int j = 0; j < 4; ++j) {
+        const int64_t first = (c0 + (int64_t)G * kWavesPerBlock * j) * kChunk;
+        if (first >= n) break;  // uniform
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int b = l[j][e];
-        const int q = b > 0 ? route_queue(route, min(b, L)) : -1;
-        const uint64_t x = make_comp(fifo_key(__int_as_float(a[j][e])), (uint32_t)(first + 4 * lane + e));
-        int row = -1;
+        for (int e = 0; e < 4; ++e) {
+          const int b = l[j][e];
+          const uint32_t key = fifo_key(__int_as_float(a[j][e]));
+          if (decltype(some)::value && __ballot(b > 0 && key >= min_key) == 0ull) continue;  // uniform
+          const int q = b > 0 ? route_queue(route, min(b, L)) : -1;
+          const uint64_t x = make_comp(key, (uint32_t)(first + 4 * lane + e));
+          int row = -1;
 #pragma unroll
-        for (int r = 0; r < kTacticalRows; ++r) row = q == qs[r] && x >= tau[r] ? r : row;  // the rows' queues differ
-        if (__ballot(row >= 0) != 0ull) {
-          for (int r = 0; r < kTacticalRows; ++r) {
-            const uint64_t m = __ballot(row == r);
-            if (m == 0ull) continue;
-            int at = 0;
-            if (lane == 0) at = atomicAdd(&nout[r], (int)__popcll(m));
-            at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);  // lane 0 (the whole wave is active)
-            if (row == r && at < kGatherLds) out[r][at] = x;
+          for (int r = 0; r < kTacticalRows; ++r) row = q == qs[r] && x >= tau[r] ? r : row;  // the rows' queues differ
+          if (__ballot(row >= 0) != 0ull) {
+            for (int r = 0; r < kTacticalRows; ++r) {
+              const uint64_t m = __ballot(row == r);
+              if (m == 0ull) continue;
+              int at = 0;
+              if (lane == 0) at = atomicAdd(&nout[r], (int)__popcll(m));
+              at = __builtin_amdgcn_readfirstlane(at);  // lane 0 (the whole wave is active)
+              const int i = at + lanes_below(m);
+              if (row == r && i < kGatherLds) out[r][i] = x;
+              if (at + (int)__popcll(m) > kGatherLds) {  // uniform; most of a queue's oldest in one share
+                const uint64_t past = __ballot(row == r && i >= kGatherLds);
+                int to = 0;
+                if (lane == 0) to = atomicAdd(&g.count[r], (int)__popcll(past));
+                to = __builtin_amdgcn_readfirstlane(to) + lanes_below(past);
+                if (row == r && i >= kGatherLds && to < kMergeCap) g.list[(size_t)r * kMergeCap + to] = x;
+              }
+            }
           }
         }
       }
     }
-  }
+  };
+  if (min_key != 0u) pass(std::true_type{});
+  else pass(std::false_type{});
   __syncthreads();
-  if (tid < kTacticalRows && nout[tid] > 0)  // too many: over the cap
-    base[tid] = atomicAdd(&g.count[tid], nout[tid] <= kGatherLds ? nout[tid] : kMergeCap + 1);
+  if (tid < kTacticalRows && nout[tid] > 0) base[tid] = atomicAdd(&g.count[tid], min(nout[tid], kGatherLds));
   __syncthreads();
   for (int r = 0; r < kTacticalRows; ++r) {
-    const int c = nout[r];
-    if (c > kGatherLds) continue;
+    const int c = min(nout[r], kGatherLds);
     for (int i = tid; i < c; i += kBlock)
       if (base[r] + i < kMergeCap) g.list[(size_t)r * kMergeCap + base[r] + i] = out[r][i];
   }
