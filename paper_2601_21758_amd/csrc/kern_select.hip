@@ -2280,9 +2280,12 @@ static bool step_packed(int64_t n, int32_t n_theta) {
 //    1 - (1 - rank / 1,024)^(1/8).  They must fit theta_select's list, and
 //    three times as many the survivors' room.
 //  - Six launches against two, and one read of the pool either way: measured
-//    (us a step, B = 128, filtered / plain) 26 / 71 at 131,072 requests and 2
-//    vectors, 26 / 36 at 262,144 and 2, 28 / 21 at 524,288 and 2, 31 / 29 at 1M
-//    and 4, 31 / 37 at 1M and 6, 41 / 34 at 4M and 4, 41 / 42 at 4M and 6.
+//    (us a step, B = 128, filtered / plain) 26 / 83 at 131,072 requests and 2
+//    vectors, 26 / 36 at 262,144 and 2, 28 / 21 at 524,288 and 2, 30 / 29 at 1M
+//    and 4, 30 / 37 at 1M and 6, 35 / 34 at 4M and 4, 35 / 39 at 4M and 6.  The
+//    plain step is cheap where a workgroup's share of the B is at most four and
+//    its lists stay short: at 262,144 and B = 64 26 / 19 with 2 vectors, 26 / 23
+//    with 3, 26 / 24-27 with 4, and the same at 24,000 and B = 8.
 struct FilterPlan {
   int rank = 0;         // 0: not filtered
   size_t head = 0;      // bytes before the survivors
@@ -2291,6 +2294,8 @@ struct FilterPlan {
 static FilterPlan filter_plan(int64_t n, int32_t n_theta, int32_t B) {
   FilterPlan f;
   if (n_theta < 2 || n <= kSmallPool || (n_theta < 6 && n > kFilterFewMax) || !step_packed(n, n_theta)) return f;
+  constexpr int64_t kPass = (int64_t)kWavesPerBlock * kChunksPerPass * kChunk;  // requests per workgroup of the plain step
+  if (n_theta < 4 && B <= 4 * ((n + kPass - 1) / kPass)) return f;
   const double share = (double)B * kSample / (double)n;
   const int rank = (int)std::ceil(share + 4.0 * std::sqrt(share) + 8.0);
   if (rank > kSampleMaxRank) return f;
@@ -2589,6 +2594,9 @@ extern "C" void ewsjf_debug_plan(int op, int64_t n, int32_t rows, int32_t B, int
   out[1] = p.lg;
   out[2] = p.M;
   out[3] = p.fit;
+  const ewsjf::FilterPlan f = ewsjf::filter_plan(n, rows, B);
+  out[4] = op == EWSJF_OP_STEP ? f.rank : 0;
+  out[5] = op == EWSJF_OP_STEP && f.rank > 0 ? ewsjf::carve_filter(f, rows, ewsjf::plan_step(n, rows, B).ws_bytes, nullptr).cap : 0;
 }
 extern "C" int ewsjf_debug_stamps_clear(void) {
   static uint64_t zeros[ewsjf::kStampSlots];

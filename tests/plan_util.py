@@ -30,5 +30,8 @@ def tactical(n, B):
 
 def plan(op, n, rows, B):
     """The selection plan of an operation (_lib.OP_STEP, OP_SELECT, OP_TRIAL): workgroups per row, bar groups per wave
-    (log2), list entries per workgroup, entries a wave keeps at least when its region overflows."""
-    return _call("ewsjf_debug_plan", (C.c_int(op), C.c_int64(n), C.c_int32(rows), C.c_int32(B)), ("G", "lg", "M", "fit"))
+    (log2), list entries per workgroup, entries a wave keeps at least when its region overflows; of a step under
+    several vectors, the filter's rank (0: not filtered) and the survivors it has room for (their number is the
+    workspace's first int32, the vectors' thresholds its float32 from byte 256 on)."""
+    return _call("ewsjf_debug_plan", (C.c_int(op), C.c_int64(n), C.c_int32(rows), C.c_int32(B)),
+                 ("G", "lg", "M", "fit", "filter", "room"))

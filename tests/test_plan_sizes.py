@@ -55,3 +55,10 @@ def test_trials_run_in_whole_rounds(cap, B):
             rounds = -(-G * pools // 256)
             assert G * pools >= 0.75 * 256 * rounds, (pools, G)
             assert B <= 64 * G
+
+
+@pytest.mark.parametrize("n,nt,B,filtered", [(262144, 2, 64, False), (262144, 3, 64, False), (262144, 4, 64, True),
+                                             (262144, 2, 65, True), (24000, 2, 8, False), (24000, 2, 9, True),
+                                             (131072, 2, 128, True), (524288, 2, 128, False), (1 << 20, 6, 128, True)])
+def test_few_vectors_are_filtered_where_lists_are_long(n, nt, B, filtered):
+    assert (plan_util.plan(L.OP_STEP, n, nt, B)["filter"] > 0) == filtered

@@ -49,7 +49,7 @@ def _pool(kind, n, rng):
 # n, vectors, B: one workgroup's pool (8,192 requests, the sample's size) and, for fewer than 6 vectors,
 # 262,144 requests are the rule's edges
 CASES = [(8192, 3, 40, "uniform", ""), (8193, 3, 40, "uniform", ""), (8195, 64, 200, "arrival", ""),
-         (12001, 2, 128, "uniform", ""), (262144, 2, 64, "uniform", ""), (262145, 5, 64, "uniform", ""),
+         (12001, 2, 128, "uniform", ""), (262144, 2, 64, "uniform", ""), (262144, 2, 65, "uniform", ""), (131072, 3, 33, "arrival", ""), (262145, 5, 64, "uniform", ""),
          (262145, 6, 1000, "arrival", ""), (30000, 9, 4096, "uniform", ""), (65537, 63, 64, "uniform", ""),
          (100003, 48, 700, "arrival", "wide"), (70001, 64, 300, "just_arrived", ""), (65536, 64, 256, "few_live", ""),
          (300001, 17, 256, "hidden", ""), (131072, 40, 100, "tombstones", "mixed"), (90000, 64, 64, "uniform", "fair_only"),
