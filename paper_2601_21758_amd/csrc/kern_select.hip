@@ -1531,7 +1531,9 @@ __global__ __launch_bounds__(kBlock) void select_small(Src src0, int64_t n, int 
 //   theta_threshold  per vector t, tau_t = a score that about r / m of the
 //                    pool reaches: the r-th largest of 1,024 lane maxima over
 //                    a sample of m = 8,192 requests (16 at a time, evenly
-//                    spread), r a few above the sample's share of the B.
+//                    spread), r a few above the sample's share of the B.  Fewer
+//                    than r live requests in the sample: tau_t = -1, every live
+//                    request is taken.
 //   theta_bound      per queue, the largest weights over the vectors, each in
 //                    units of its tau_t: u = max_t w_t / tau_t, 0 at least.
 //   pool_filter      one pass over the pool: with the request's three terms
@@ -1540,7 +1542,7 @@ __global__ __launch_bounds__(kBlock) void select_small(Src src0, int64_t n, int 
 //                    tau_t under all of them.  The others are the survivors.
 //   theta_select     per vector: the survivors' keys (the same two functions
 //                    as everywhere), those at or above tau_t, their exact
-//                    top B.  At least B of them: the answer.  Otherwise, and
+//                    top B.  At least B of them, or all: the answer.  Otherwise, and
 //                    when the survivors exceed their buffer or tau_t says
 //                    nothing, n_sel[t] = -1.
 //   local_candidates_multi + merge_candidates  for the vectors left at -1
@@ -1572,7 +1574,7 @@ struct Survivor {
 // In the candidate buffers' room (written only by the fallback, after the
 // last use of these).
 struct FilterBufs {
-  float* tau;       // [n_theta]: 0 = says nothing
+  float* tau;       // [n_theta]: 0 = says nothing, -1 = every live request is taken
   f32x4* u;         // [EWSJF_MAX_QUEUES]: base, urgency, fairness (log2) weights over tau
   int32_t* count;   // survivors found (more than cap: some were dropped)
   Survivor* list;   // [cap]
@@ -1632,7 +1634,12 @@ __global__ __launch_bounds__(kBlock) void theta_threshold(PoolSource src, int64_
     for (int e = 0; e < kWavesPerBlock; ++e) key[e] = best[e * kWave + lane];
     const uint32_t kth = wave_kth_of_1024(key, rank);
     const float x = kth != 0u ? float_of_ukey(kth) : 0.0f;
-    if (tid == 0) tau[t] = x > 1e-30f && x < 1e30f ? x : 0.0f;  // finite, and no w / tau can overflow into doubt
+    // Few live requests in the sample are few in the pool (a drained ring): the
+    // survivors' room holds them all, and no threshold is needed.
+    int live = 0;
+#pragma unroll
+    for (int e = 0; e < kWavesPerBlock; ++e) live += (int)__popcll(__ballot(key[e] != 0u));
+    if (tid == 0) tau[t] = live < rank ? -1.0f : x > 1e-30f && x < 1e30f ? x : 0.0f;  // finite, and no w / tau can overflow into doubt
   }
 }
 
@@ -1648,6 +1655,7 @@ __global__ __launch_bounds__(kBoundThreads) void theta_bound(const ewsjf_queue_t
   float u[3] = {0.0f, 0.0f, 0.0f};
   for (int t = tid; t < n_theta; t += kBoundThreads) {
     const float x = fb.tau[t];
+    if (x < 0.0f) u[0] = u[1] = u[2] = __builtin_inff();
     if (x > 0.0f) {
       const QParams w = make_qparams(theta[t], mean, q);
       const float inv = 1.0f / x;
@@ -1731,7 +1739,8 @@ __global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, Fi
   const int tid = threadIdx.x, lane = tid & (kWave - 1), t = blockIdx.x;
   const int S = *fb.count;
   const float tau = fb.tau[t];
-  if (S < B || S > fb.cap || tau == 0.0f) {  // uniform
+  const bool all = tau < 0.0f;  // the survivors are the pool's live requests
+  if ((S < B && !all) || S > fb.cap || tau == 0.0f) {  // uniform
     if (tid == 0) n_sel[t] = -1;
     return;
   }
@@ -1742,7 +1751,7 @@ __global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, Fi
   }
   if (tid == 0) ms.cntX = 0;
   __syncthreads();
-  const uint32_t low = ukey_of(tau);
+  const uint32_t low = all ? 1u : ukey_of(tau);
   const int L = __builtin_amdgcn_readfirstlane(sh.L);
   for (int i0 = 0; i0 < S; i0 += kBlock) {
     const int i = i0 + tid;
@@ -1759,7 +1768,7 @@ __global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, Fi
   }
   __syncthreads();
   const int U = ms.cntX;
-  if (U < B || U > kMergeCap) {  // uniform
+  if ((U < B && !all) || U > kMergeCap) {  // uniform
     if (tid == 0) n_sel[t] = -1;
     return;
   }
@@ -1768,8 +1777,8 @@ __global__ __launch_bounds__(kBlock) void theta_select(PoolSource src, int B, Fi
 #pragma unroll
   for (int r = 0; r < kR; ++r) v[r] = tid + r * kBlock < U ? ms.X[tid + r * kBlock] : 0ull;
   uint64_t unused;
-  rank_registers(ms, v, U, B, 0ull, &unused);
-  publish_row(ms, B, B, t, ids, top, n_sel, nullptr);
+  const int sel = rank_registers(ms, v, U, B, 0ull, &unused);
+  publish_row(ms, sel, B, t, ids, top, n_sel, nullptr);
 }
 
 // LDS of the exact merge.
