@@ -58,6 +58,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "pending requests routed+scored+selected per sec at 4M pool; % HBM peak"
 HBM_PEAK_GBS = 8000.0
+ONE_KERNEL_POOL = 8192  # requests; ewsjf_step_timed has no second kernel to time up to here
 BYTES_PER_REQUEST = 8  # int32 prompt length + float32 arrival, each read once
 PROFILE = os.path.join(ROOT, "profiles", "fused_step_large_mixed_4m.pmc.txt")
 KERNEL_SOURCES = ("paper_2601_21758_amd/csrc/kern_select.hip", "paper_2601_21758_amd/csrc/ewsjf_merge.h",
@@ -343,13 +344,14 @@ def config_step_bench(hip, idx: int, steps: int = 200, chunk: int = 50, draws: i
     for e in ev:
         hip.rt.hipEventDestroy(e)
     del g
+    # a pool that one workgroup holds is one kernel; the second pair of events times none
+    kernels = {"select_small": k1} if n <= ONE_KERNEL_POOL else {"local_candidates": k1, "merge_candidates": k2}
     return {"workload": f"{pool.name}: {n:,} pending requests, {pool.init_queues}-queue policy, top B={B}",
             "ms_per_step": ms, "requests_per_s": n / (ms * 1e-3),
             "step_hbm_frac": 8 * n / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-            "kernels_ms": {"local_candidates": float(np.mean(k1)), "merge_candidates": float(np.mean(k2))},
+            "kernels_ms": {name: float(np.mean(k)) for name, k in kernels.items()},
             "step_percentiles_us": {"graph_per_replay": pct(per_rep),
-                                    "local_candidates": pct([x * 1e3 for x in k1]),
-                                    "merge_candidates": pct([x * 1e3 for x in k2])},
+                                    **{name: pct([x * 1e3 for x in k]) for name, k in kernels.items()}},
             "pool_draws": draws, "execution": f"HIP graph, {chunk} steps per graph, {reps} replays",
             "input_sha256": pool.digest()[:16]}
 

@@ -317,7 +317,10 @@ ewsjf_status ewsjf_step(int32_t* len, const float* arrival, int64_t n, float now
  * the streaming kernel (routing, scoring and per-workgroup candidates),
  * marks[2]/marks[3] the start/end of the merge kernel (exact top-B).  Where
  * several vectors share one filter of the pool, these are the filter's pass
- * over the pool and the kernel that selects each vector's top-B.  For
+ * over the pool and the kernel that selects each vector's top-B.  A pool of up
+ * to 8,192 requests is one kernel, timed by marks[0]/marks[1]; marks[2] and
+ * marks[3] are recorded behind it one after the other, with no kernel between
+ * them, and their distance is the events' own (about 4.5 us).  For
  * per-phase timing by a monitor; marks == NULL behaves as ewsjf_step. */
 ewsjf_status ewsjf_step_timed(int32_t* len, const float* arrival, int64_t n, float now, const void* table,
                               const ewsjf_theta* theta, int32_t n_theta, const ewsjf_cost* cost, int32_t B,

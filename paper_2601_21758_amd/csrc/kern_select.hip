@@ -2416,7 +2416,7 @@ hipError_t launch_step(const int32_t* len, const float* arrival, int64_t n, floa
     launch_small(n_theta, stream, marks ? marks[0] : nullptr, marks ? marks[1] : nullptr, src, n, B, ids, top, n_sel,
                  tomb_len);
     hipError_t e = hipGetLastError();
-    // no second kernel: its events take one moment
+    // no second kernel: its events only follow one another
     if (marks != nullptr && e == hipSuccess) e = hipEventRecord(marks[2], stream);
     if (marks != nullptr && e == hipSuccess) e = hipEventRecord(marks[3], stream);
     return e;

@@ -42,3 +42,33 @@ def test_small_pool(n, nt, B, kind):
         i2, t2, n2 = (x.cpu().numpy() for x in E.select(s, B))
         assert np.array_equal(i2, ids) and np.array_equal(n2, nsel)
         assert np.array_equal(t2.view(np.int32), top.view(np.int32))
+
+
+@pytest.mark.parametrize("n", [4096, 8192, 8193])
+def test_step_timed(n):
+    """The same step with four events; up to 8,192 requests the first pair times the one kernel."""
+    import ctypes as C
+
+    from paper_2601_21758_amd import _lib as lib
+    from paper_2601_21758_amd import ewsjf as E
+    p = W.make_pool("two", n, 4, arrivals="uniform", horizon=300.0, K=16)
+    t = oracle.partition(p.window, init_queues=16, max_queues=16)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    tab = E.upload_table(t.bounds, t.mean, 32768, t.lo, t.hi, t.count, t.sum)
+    L, A, th = dev(p.length), dev(p.arrival), dev(p.theta)
+    want = E.step(L, A, p.now, tab, th, 64)
+    out = E._outs(1, 64, "cuda", None)
+    ws = torch.empty(E.workspace_bytes(lib.OP_STEP, n, 1, 64), dtype=torch.uint8, device="cuda")
+    events = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in events:
+        e.record()
+    marks = (C.c_void_p * 4)(*[e.cuda_event for e in events])
+    c = E.cost()
+    print(f"timed step n={n}", flush=True)
+    lib.check(lib.lib().ewsjf_step_timed(L.data_ptr(), A.data_ptr(), n, p.now, tab.data_ptr(), th.data_ptr(), 1,
+                                         C.byref(c), 64, 0, *[x.data_ptr() for x in out], ws.data_ptr(), ws.numel(),
+                                         torch.cuda.current_stream().cuda_stream, marks), "ewsjf_step_timed")
+    torch.cuda.synchronize()
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out, want))
+    assert 0.0 < events[0].elapsed_time(events[1]) < 1.0
+    assert 0.0 <= events[1].elapsed_time(events[2]) and 0.0 <= events[2].elapsed_time(events[3])
