@@ -17,7 +17,7 @@ struct SelectPlan {
   int M = 16;       // list entries kept per workgroup
   int fit = 48;     // entries a wave keeps at least when its keys overflow its region
   int n_theta = 1;
-  size_t lists_bytes = 0, counts_bytes = 0, bounds_bytes = 0;
+  size_t lists_bytes = 0, bounds_bytes = 0;
   size_t over_bytes = 0, over_cnt_bytes = 0, bounds2_bytes = 0;
   size_t ws_bytes = 0;
 };
@@ -26,7 +26,6 @@ struct SelectPlan {
 // slot = theta * G + workgroup.
 struct CandBufs {
   uint64_t* lists;     // [slot][M]: the M largest composites (0 = empty)
-  uint32_t* counts;    // [slot]
   uint64_t* bounds;    // [slot]: every composite >= bound of the share is in its M slots
   uint64_t* over;      // [slot][kOverCap]: the next entries below the M slots
   uint32_t* over_cnt;  // [slot]

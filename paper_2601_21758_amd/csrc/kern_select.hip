@@ -296,9 +296,9 @@ struct FifoSource {
 
   __device__ __forceinline__ bool skip(int t) const { return t > 0 && plan->take[t] == 0; }
   // The oldest requests of a queue sit together in an arrival-ordered pool:
-  // the streaming kernel keeps a spill list for full wave regions and lowers
-  // the workgroup bound past a clustered wave (both cost the score sources
-  // time and registers, so they are compiled in for this source only).
+  // local_clustered keeps a spill list for full wave regions and lowers the
+  // workgroup bound past a clustered wave (both would cost the score sources
+  // time and registers).
   static constexpr bool kClustered = true;
 };
 
@@ -507,7 +507,6 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
   if (cnt > kListCap) {
     for (int i = threadIdx.x; i < M; i += kBlock) out_list[i] = 0ull;
     if (threadIdx.x == 0) {
-      cb.counts[slot] = 0u;
       cb.bounds[slot] = ~0ull;
       cb.bounds2[slot] = ~0ull;
       cb.over_cnt[slot] = 0u;
@@ -517,7 +516,6 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
   if (cnt <= M) {
     for (int i = threadIdx.x; i < M; i += kBlock) out_list[i] = i < cnt ? ls.list2[i] : 0ull;
     if (threadIdx.x == 0) {
-      cb.counts[slot] = (uint32_t)cnt;
       cb.bounds[slot] = lowc;
       cb.bounds2[slot] = lowc;
       cb.over_cnt[slot] = 0u;
@@ -534,7 +532,6 @@ __device__ __forceinline__ void publish_list(ListShared& ls, int cnt, uint64_t l
     if (rank < M) out_list[rank] = x;
     else if (rank < listed) over_list[rank - M] = x;
     if (rank == M - 1) {
-      cb.counts[slot] = (uint32_t)M;
       cb.bounds[slot] = x > lowc ? x : lowc;
     }
     if (rank == listed - 1) cb.bounds2[slot] = (cnt <= M + kOverCap || x < lowc) ? lowc : x;
@@ -846,6 +843,7 @@ __global__ __launch_bounds__(kBlock) void local_candidates(Src src0, int64_t n, 
 // regions and a lowered bound.
 template <class Src>
 __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
+  static_assert(Src::kClustered, "the other sources use local_candidates and local_stream");
   __shared__ typename Src::Shared sh;
   __shared__ ListShared ls;
   const int t = blockIdx.y;
@@ -854,7 +852,6 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
     const size_t slot = (size_t)t * G + blockIdx.x;
     for (int i = threadIdx.x; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
     if (threadIdx.x == 0) {
-      cb.counts[slot] = 0u;
       cb.bounds[slot] = 0ull;
       cb.bounds2[slot] = 0ull;
       cb.over_cnt[slot] = 0u;
@@ -887,7 +884,7 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
     }
     ls.rank[threadIdx.x] = 0;
     static_assert(kListCap == kBlock, "one spill entry per thread");
-    if constexpr (Src::kClustered) ls.spill[threadIdx.x] = 0ull;
+    ls.spill[threadIdx.x] = 0ull;
   };
   {
     // The compute unit serves a workgroup's loads roughly in issue order; this
@@ -965,7 +962,7 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
     };
     const uint32_t thr = my_bar > 1u ? my_bar : 1u;
     emit(thr);
-    if (Src::kClustered && wcnt > kWaveCap) {
+    if (wcnt > kWaveCap) {
       // Too many keys at or above the bar for the wave's region (data whose
       // high keys cluster in this wave): the rest goes to the workgroup's
       // spill list if it has room (one reservation per wave; a reservation
@@ -1040,7 +1037,6 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
   if (ls.ovf != 0) {
     for (int i = threadIdx.x; i < M; i += kBlock) out_list[i] = 0ull;
     if (threadIdx.x == 0) {
-      cb.counts[slot] = 0u;
       cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
       cb.bounds2[slot] = ~0ull;
       cb.over_cnt[slot] = 0u;
@@ -1068,7 +1064,7 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
   }
   const uint32_t lo2 = t2 > 1u ? t2 : 1u;
   uint32_t T_bar = t1;
-  if (Src::kClustered && passes == 1 && lo2 < t1 && ls.wcnt[v1] >= kDenseWave) {  // uniform
+  if (passes == 1 && lo2 < t1 && ls.wcnt[v1] >= kDenseWave) {  // uniform
     if (wv == v1) {
       int need = 0;
 #pragma unroll
@@ -1109,7 +1105,7 @@ __global__ __launch_bounds__(kBlock) void local_clustered(Src src0, int64_t n, i
     }
   };
   keep_into_list2(lane < ls.wcnt[wv] ? ls.list[threadIdx.x] : 0ull);
-  if (Src::kClustered && ls.nspill != 0) keep_into_list2(ls.spill[threadIdx.x]);  // uniform
+  if (ls.nspill != 0) keep_into_list2(ls.spill[threadIdx.x]);  // uniform
   __syncthreads();
   EWSJF_STAMP(kStampLocal, 4);
   EWSJF_STAMP_VALUE(kStampLocal, 6, ls.nout);
@@ -1148,7 +1144,7 @@ __device__ __forceinline__ void lds_poke(uint32_t* p, uint32_t v) {
 
 template <class Src>
 __global__ __launch_bounds__(kBlock) void local_stream(Src src0, int64_t n, int G, int lg, int M, CandBufs cb) {
-  static_assert(!Src::kClustered, "clustered sources use local_candidates");
+  static_assert(!Src::kClustered, "clustered sources use local_clustered");
   __shared__ typename Src::Shared sh;
   __shared__ ListShared ls;
   const int t = blockIdx.y;
@@ -1293,7 +1289,6 @@ __global__ __launch_bounds__(kBlock) void local_stream(Src src0, int64_t n, int 
   if (ls.ovf != 0) {
     for (int i = threadIdx.x; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
     if (threadIdx.x == 0) {
-      cb.counts[slot] = 0u;
       cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
       cb.bounds2[slot] = ~0ull;
       cb.over_cnt[slot] = 0u;
@@ -1428,7 +1423,6 @@ __global__ __launch_bounds__(kBlock) void local_candidates_multi(PoolSource src,
     if (s_ovf[pb] != 0) {  // uniform
       for (int i = tid; i < M; i += kBlock) cb.lists[slot * (size_t)M + i] = 0ull;
       if (tid == 0) {
-        cb.counts[slot] = 0u;
         cb.bounds[slot] = ~0ull;  // nothing guaranteed: the merge re-reads this share
         cb.bounds2[slot] = ~0ull;
         cb.over_cnt[slot] = 0u;
@@ -2242,13 +2236,12 @@ SelectPlan plan_select(int64_t n, int32_t n_theta, int32_t B, bool packed, int m
   p.M = M;
   p.n_theta = n_theta;
   p.lists_bytes = (size_t)n_theta * p.G * p.M * sizeof(uint64_t);
-  p.counts_bytes = (size_t)n_theta * p.G * sizeof(uint32_t);
   p.bounds_bytes = (size_t)n_theta * p.G * sizeof(uint64_t);
   p.over_bytes = (size_t)n_theta * p.G * kOverCap * sizeof(uint64_t);
   p.over_cnt_bytes = (size_t)n_theta * p.G * sizeof(uint32_t);
   p.bounds2_bytes = (size_t)n_theta * p.G * sizeof(uint64_t);
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  p.ws_bytes = up(p.lists_bytes) + up(p.counts_bytes) + up(p.bounds_bytes) + up(p.over_bytes) +
+  p.ws_bytes = up(p.lists_bytes) + up(p.bounds_bytes) + up(p.over_bytes) +
                up(p.over_cnt_bytes) + up(p.bounds2_bytes);
   return p;
 }
@@ -2260,8 +2253,6 @@ static CandBufs carve(const SelectPlan& p, void* ws) {
   size_t o = 0;
   c.lists = reinterpret_cast<uint64_t*>(b + o);
   o += up(p.lists_bytes);
-  c.counts = reinterpret_cast<uint32_t*>(b + o);
-  o += up(p.counts_bytes);
   c.bounds = reinterpret_cast<uint64_t*>(b + o);
   o += up(p.bounds_bytes);
   c.over = reinterpret_cast<uint64_t*>(b + o);
