@@ -1,6 +1,6 @@
 """Several rows at once: scores of a group of vectors with rows at every
 alignment, selection with one to four chunks per wave, trials with shares of
-one pass and of more."""
+one pass and of more and the statistics their merge keeps."""
 import numpy as np
 import pytest
 
@@ -80,3 +80,11 @@ def test_trial_shares(cap, pools, B):
         left[ids[p][:nsel[p]]] = 0
         assert np.array_equal(tr.len[p].cpu().numpy(), left)
         assert np.array_equal(tr.arr[p].cpu().numpy(), A2)
+        # the statistics of the admitted requests, which the merge keeps: whole numbers exactly, the sums of at most
+        # B terms within B roundings of binary64
+        i = ids[p][:nsel[p]]
+        wait = np.maximum(0.0, np.float64(np.float32(now)) - A2[i].astype(np.float64))
+        st = tr.stats[p].cpu().numpy()
+        assert st[0] == nsel[p] and st[1] == L2[i].astype(np.int64).sum() and st[7] == 1 and st[4] == wait.max()
+        assert np.allclose(st[2:4], [wait.sum(), (wait * wait).sum()], rtol=B * 2.3e-16, atol=0)
+        assert np.array_equal(tr.queue_admits[p].cpu().numpy()[:t.k], np.bincount(oracle.route(L2[i], t), minlength=t.k))
