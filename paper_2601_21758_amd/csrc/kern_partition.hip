@@ -557,7 +557,7 @@ __device__ __forceinline__ uint64_t dbits(double x) { return (uint64_t)__double_
 // with the test itself; a level is then one compare per value against its
 // segment's threshold.  With the test evaluated for every gap a level took
 // 14 us (two conversions and two binary64 products per gap, 32 gaps per
-// thread whatever V), the kernel 78-87 us; it takes 34-46 us now, about 5 us a level.
+// thread whatever V), the kernel 78-87 us; it takes 34-46 us now, 5 to 7 us a level.
 // ---------------------------------------------------------------------------
 constexpr int kGroups = EWSJF_MAX_LEN / kWave;  // 512
 constexpr int kNoCut = 0xFFFF;                  // above every gap

@@ -1549,10 +1549,12 @@ __global__ __launch_bounds__(kBlock) void select_small(Src src0, int64_t n, int 
 // Scores of one pool under the vectors of a meta-optimizer's batch order it
 // alike (the wait dominates), so survivors are few: 1,300-1,800 of 1M for 256
 // vectors with B = 256, where each vector has that many at or above tau_t.
-// 256 vectors over 1M requests take 32 us a step, where the plain kernels
-// took 278: 9.0 us for the thresholds, 3.4 for the bounds, 7.6 for the pass
-// over the pool, 11.1 for the vectors' top B, 5.3 for the two that find nothing
-// to do.
+// 256 vectors over 1M requests take 31 us a step, where the plain kernels
+// took 278.  Traced one by one: 8.5 us for the thresholds, 3.9 for the bounds,
+// 7.5 for the pass over the pool, 9.1 for the vectors' top B, 3.9 and 4.0 for the
+// two that find nothing to do; back to back their starts overlap.  Where no
+// threshold can be had (every score zero or negative, nearly all of them equal)
+// the filter's 17 to 25 us come on top of the plain kernels.
 // ---------------------------------------------------------------------------
 constexpr int kSample = 8192;        // requests in the sample, 8 per thread of theta_threshold
 constexpr int kSampleRun = 16;       // consecutive requests of one sample place

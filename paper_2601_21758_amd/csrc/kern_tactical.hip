@@ -9,12 +9,13 @@
 //                               requests GreedyFill and Backfill take from the
 //                               queue and its two neighbours.
 //   queue-order selection       the oldest requests of each of the (up to)
-//                               three queues.  Large pools: tac_scan collects a
-//                               sample, tac_reduce takes an age threshold per
-//                               queue from it, tac_gather lists the members
-//                               at or above it, tac_finish orders them.
-//                               Otherwise local_clustered /
-//                               merge_candidates with FifoSource.
+//                               three queues.  tac_scan collects a sample,
+//                               tac_reduce takes an age threshold per queue
+//                               from it, tac_gather lists the members at or
+//                               above it, tac_finish orders them.  For the
+//                               largest B and pools (gather_rank):
+//                               local_clustered / merge_candidates with
+//                               FifoSource.
 //   tac_finish  (1 workgroup,   the batch in order, tombstones, and the
 //                a row each)    removal of queues empty past the threshold
 //                               (re-absorbed by the neighbour of lower Eq. 3
@@ -118,12 +119,15 @@ int sample_step(int64_t n) {
 // gather is not used.  The rank: the mean number of the B oldest in the sample
 // (about a Poisson count), four standard deviations and a few more.  The
 // members at or above the threshold (rank / density of them) must fit a
-// workgroup's list with five standard deviations to spare (B up to about 1,500
-// for pools up to 16M), unless every queue fits it anyway.  Measured (us a step,
-// random / arrival order, gathered against local_clustered and
-// merge_candidates with FifoSource): 27 / 27 against 54 / 39 at 4,096 requests
+// workgroup's list with five standard deviations to spare, unless every queue
+// fits it anyway: any B up to 9,088 requests, B up to 1,962 for pools up to
+// 16,777,216 (every chunk sampled), up to 443 for pools up to 33,554,432 (every
+// second), none beyond.  Measured (us a step, random / arrival order, gathered
+// against the lists of FifoSource): 27 / 27 against 54 / 39 at 4,096 requests
 // and B = 64, 29 / 29 against 55 / 60 at 65,536 and 64, 34 / 31 against 42 / 84
-// at 1M and 1,024, 56 / 56 against 61 / 105 at 8M and 256.
+// at 1M and 1,024, 38 / 35 against 40 / 55 at 4M and 64, 53 / 51 against 56 / 73
+// at 8M and 64, 80 / 77 against 86 / 114 at 16M and 64; with queues that
+// overflow the lists up to 100 times as much.
 int gather_rank(int64_t n, int32_t B) {
   const double density = 2.0 / ((double)kChunk * (double)(1 << sample_step(n)));
   const double mean = B * density;
@@ -169,7 +173,7 @@ size_t carve_tac(int64_t n, int32_t B, void* ws, TacWs* w) {
 // Head-of-line pass.  Chunk c of workgroup w at local index lc is
 // c = w + G * lc; each wave keeps four chunks in flight.  Counters are kept
 // once per lane of eight: most requests of a workload fall in a few queues, and
-// lanes adding to one counter are served one after the other (4M requests: 12.4
+// lanes adding to one counter are served one after the other (4M requests: 12.2
 // us, 14.5 us with one counter per queue, the sample included).
 //
 // Two requests of every sampled chunk go to the sample, 128 slots apart, at a
@@ -478,10 +482,12 @@ __global__ __launch_bounds__(EWSJF_MAX_QUEUES) void tac_plan(const ewsjf_queue_t
 
 // ---------------------------------------------------------------------------
 // The members of the plan's queues at or above their thresholds, one pass over
-// the pool (four chunks in flight).  4M requests: 10.9 us (3.1 TB/s), and
-// tac_finish orders the 2,000 to 4,500 members in 5 us more than it took; the
-// lists of local_clustered took 16.9 us and their merge 24 to 40 us, since the
-// oldest of a queue sit together in a pool in arrival order.
+// the pool (four chunks in flight).  Bound by HBM and, behind it, by the handling
+// of what arrives: a wave's requests are tested for age first, and routed only
+// where one of them is old enough.  4M requests: 8.6 us (3.9 TB/s), 10.2 us with
+// every request routed; tac_finish orders the 2,000 to 4,500 members in 5 us more
+// than it took.  The lists of local_clustered took 16.9 us and their merge 24 to
+// 40 us, since the oldest of a queue sit together in a pool in arrival order.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__ len, const float* __restrict__ arrival,
                                                      int64_t n, const ewsjf_queue_table* __restrict__ tab, int G,
@@ -567,15 +573,15 @@ __global__ __launch_bounds__(kBlock) void tac_gather(const int32_t* __restrict__
 }
 
 // Whether row r's listed members hold its oldest `take`: always, but for about
-// one call in a million.
+// one call in a million, and for pools laid out against the sample's places.
 __device__ __forceinline__ bool row_listed(const Gather& g, int r, int take) {
   const int U = g.count[r];
   return U >= take && U <= kMergeCap;
 }
 
 // The oldest `take` of row r into ms.X, oldest first, by the whole block: from
-// the listed members, or (slow, exact) from the whole pool, sixteen chunks at a
-// time.
+// the listed members, or (exact) from the whole pool, sixteen chunks at a time,
+// a load and three barriers each: 2.0 ms for 4M requests.
 __device__ void oldest_of_row(MergeShared& ms, const Gather& g, int r, int queue, int take, const int32_t* len,
                               const float* arrival, int64_t n, const ewsjf_queue_table* tab) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
