@@ -211,9 +211,16 @@ __global__ __launch_bounds__(kBlock) void window_hist_add(const int32_t* __restr
   // A wave adds to 64 neighbouring bins: two cache lines an instruction.  Four
   // bins per thread (vector reads of LDS) are eight lines, each touched four
   // times: 1M lengths of two modes took 18.3 us, uniform ones 47.8 us; 10.5 and
-  // 15.6 us with these.
-  for (int b = threadIdx.x; b <= L; b += kBlock)
-    if (h[b] != 0u) atomicAdd(&hist[b], h[b]);
+  // 16.1 us with these.  Eight reads of LDS in flight.
+  constexpr int kFlush = 8;
+  for (int b0 = threadIdx.x; b0 <= L; b0 += kFlush * kBlock) {
+    uint32_t x[kFlush];
+#pragma unroll
+    for (int u = 0; u < kFlush; ++u) x[u] = b0 + u * kBlock <= L ? h[b0 + u * kBlock] : 0u;
+#pragma unroll
+    for (int u = 0; u < kFlush; ++u)
+      if (x[u] != 0u) atomicAdd(&hist[b0 + u * kBlock], x[u]);
+  }
 }
 
 // Column sums of the partial histograms.  Four bins per thread and four
